@@ -10,6 +10,8 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -18,7 +20,9 @@ LIB_PATH = os.path.join(HERE, "libadasum.so")
 # a measuring tool (the memory system's ceiling for the combine pass's access pattern)
 CEILING_PATH = os.path.join(HERE, "pattern_ceiling")
 
-SOURCES = ["adasum_kernels.hip", "adasum_api.cpp", "adasum_plan.cpp"]
+# (source, defines): the resident kernels are compiled once per storage type of the gradients
+SOURCES = [("adasum_resident.hip", [f"-DADASUM_LEAF_TYPE={t}"]) for t in (0, 1, 2, 3)] + [
+    ("adasum_kernels.hip", []), ("adasum_api.cpp", []), ("adasum_plan.cpp", [])]
 
 # -packed-fp32-ops off: the compiler must not form packed fp32 instructions.
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -32,13 +36,24 @@ def hipcc() -> str:
 
 
 def build_library(verbose: bool = True, extra_flags=(), out_path: str = LIB_PATH) -> str:
-    cmd = [hipcc(), "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-unused-command-line-argument",
-           *DEVICE_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, *extra_flags]
-    cmd += [os.path.join(CSRC, s) for s in SOURCES]
-    cmd += ["-o", out_path]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    """Compiles every source to an object (side by side: the resident kernels of the four storage types take most
+    of the time) and links them."""
+    flags = ["-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-Wno-unused-command-line-argument",
+             *DEVICE_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, *extra_flags]
+    with tempfile.TemporaryDirectory() as tmp:
+        objects, commands = [], []
+        for i, (source, defines) in enumerate(SOURCES):
+            objects.append(os.path.join(tmp, f"{i}.o"))
+            commands.append([hipcc(), *flags, *defines, "-c", os.path.join(CSRC, source), "-o", objects[-1]])
+
+        def run(cmd):
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            subprocess.run(cmd, check=True)
+
+        with ThreadPoolExecutor(min(len(commands), os.cpu_count() or 1, 8)) as pool:
+            list(pool.map(run, commands))
+        run([hipcc(), "-shared", "-fPIC", *DEVICE_FLAGS, "-Wno-unused-command-line-argument", *objects, "-o", out_path])
     return out_path
 
 

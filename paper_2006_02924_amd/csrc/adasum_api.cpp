@@ -208,6 +208,9 @@ struct Plan {
     std::vector<int64_t> offsets;
     TileTable gram_tiles;                 // capacity kTile
     TileTable wide_spans;                 // the span table of a wide first pass (else empty)
+    ResidentPlan resident;                // the whole reduction as one resident pass (form 0: the other passes run)
+    TileTable unit_tiles;                 // its units in element order
+    ResidentUnit* d_units = nullptr;      // and in launch order
     std::map<int, TileTable> comb_tables; // by capacity, built on first use
     std::vector<int> radices;
     std::vector<SmallLayer> small;        // layers reduced by the definition in fp64 (see kSmallLayer)
@@ -270,6 +273,8 @@ struct Plan {
         if (done) (void)hipEventDestroy(done);
         gram_tiles.release();
         wide_spans.release();
+        unit_tiles.release();
+        if (d_units && !borrowed) (void)hipFree(d_units);
         for (auto& kv : comb_tables) kv.second.release();
         if (borrowed) return;
         if (d_small) (void)hipFree(d_small);
@@ -281,7 +286,6 @@ std::mutex g_mutex;
 std::vector<std::unique_ptr<Plan>> g_plans;   // least recently used first
 constexpr size_t kMaxPlans = 64;
 
-// Builds a plan (host tables, their device copies; no workspace yet) on the current device.
 // Capacity of the combine tile table pass lv uses, reading operands of type `dtype`: a pass that feeds
 // the next one works with one wave per group whatever its radix.
 int table_capacity(bool feed, const std::vector<int>& radices, size_t lv, int dtype) {
@@ -289,9 +293,27 @@ int table_capacity(bool feed, const std::vector<int>& radices, size_t lv, int dt
                                                 : combine_tile_capacity(dtype, radices[lv]);
 }
 
+// Takes the reduction as a resident pass, and lays out its section of the workspace, where the layer table suits one
+// and the device is one it is made for (the section is there all the same: adasum_workspace_bytes asks no device).
+int take_resident(Plan* p, int dtype, bool delta, const int64_t* offsets, int n_layers) {
+    const ResidentPlan r = plan_resident(p->K, p->radices, dtype, delta, offsets, n_layers);
+    if (r.form == 0) return ADASUM_OK;
+    int device = 0, cus = 0;
+    ADASUM_HIP(hipGetDevice(&device));
+    ADASUM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+    add_resident(p->lay, r);
+    if (cus < kResidentCus) return ADASUM_OK;
+    p->resident = r;
+    p->unit_tiles.capacity = r.capacity;
+    return ADASUM_OK;
+}
+
+// Builds a plan (host tables, their device copies; no workspace yet) on the current device.
 // `no_feed`: the delta form, the step plans and separate_passes: no pass feeds the next.
-int make_plan(int K, int radix, int order, int node_type, bool fuse, bool no_feed, const int64_t* offsets, int n_layers,
-              std::unique_ptr<Plan>& out) {
+// `whole`: the plan is for whole reductions that may be taken as a resident pass (not a step, not separate_passes).
+int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, bool no_feed, bool whole,
+              const int64_t* offsets, int n_layers, std::unique_ptr<Plan>& out) {
+    const int node_type = node_dtype(dtype);
     int device = 0;
     ADASUM_HIP(hipGetDevice(&device));
     std::unique_ptr<Plan> p(new (std::nothrow) Plan());
@@ -325,6 +347,12 @@ int make_plan(int K, int radix, int order, int node_type, bool fuse, bool no_fee
                              : p->feed ? next_entries_bound(Kv, offsets, n_layers, p->radices, node_type)
                                        : 0,
                              static_cast<int64_t>(p->wide_spans.tiles.size()));
+        if (whole) {
+            const int rc = take_resident(p.get(), dtype, delta, offsets, n_layers);
+            if (rc != ADASUM_OK) return rc;
+            if (p->resident.form > 0)
+                build_tiles(offsets, n_layers, p->resident.capacity, p->unit_tiles.tiles, p->unit_tiles.layer_begin);
+        }
     } catch (const std::bad_alloc&) {
         return ADASUM_ERR_OUT_OF_MEMORY;
     }
@@ -333,6 +361,19 @@ int make_plan(int K, int radix, int order, int node_type, bool fuse, bool no_fee
     if (p->wide_spans.n_parts > 0) {
         rc = p->wide_spans.upload();
         if (rc != ADASUM_OK) return rc;
+    }
+    if (p->resident.form > 0) {
+        rc = p->unit_tiles.upload();
+        if (rc != ADASUM_OK) return rc;
+        try {
+            std::vector<ResidentUnit> units;
+            order_units(p->unit_tiles.tiles, p->unit_tiles.layer_begin, p->resident.form, units);
+            const size_t bytes = units.size() * sizeof(ResidentUnit);
+            ADASUM_HIP(hipMalloc(reinterpret_cast<void**>(&p->d_units), bytes));
+            ADASUM_HIP(hipMemcpy(p->d_units, units.data(), bytes, hipMemcpyHostToDevice));
+        } catch (const std::bad_alloc&) {
+            return ADASUM_ERR_OUT_OF_MEMORY;
+        }
     }
     if (!p->small.empty()) {
         const size_t bytes = p->small.size() * sizeof(SmallLayer);
@@ -369,8 +410,9 @@ int find_or_make_plan(int K, int radix, int order, int in_dtype, int out_dtype, 
     // a bounded cache: the least recently used plan goes (hipFree waits for work in flight)
     while (g_plans.size() >= kMaxPlans) g_plans.erase(g_plans.begin());
     std::unique_ptr<Plan> p;
-    const int rc = make_plan(K, radix, order == kStepPlans ? ADASUM_ORDER_TREE : order, node_type, fuse,
-                             delta || separate || order == kStepPlans, offsets, n_layers, p);
+    const int rc = make_plan(K, radix, order == kStepPlans ? ADASUM_ORDER_TREE : order, in_dtype, delta, fuse,
+                             delta || separate || order == kStepPlans, !separate && order != kStepPlans, offsets,
+                             n_layers, p);
     if (rc != ADASUM_OK) return rc;
     p->order = order;
     p->in_dtype = in_dtype;
@@ -389,7 +431,23 @@ int plan_workspace(Plan* p, const Opts& o, char** ws) {
         return ADASUM_OK;
     }
     if (p->d_ws == nullptr && p->lay.total > 0) {
-        ADASUM_HIP(hipMalloc(reinterpret_cast<void**>(&p->d_ws), p->lay.total));
+        char* mem = nullptr;
+        ADASUM_HIP(hipMalloc(reinterpret_cast<void**>(&mem), p->lay.total));
+        if (p->resident.form > 0) {
+            // the resident pass's section starts at zero; what a call leaves there carries that call's tag
+            hipError_t e = hipErrorOutOfMemory;
+            try {
+                const std::vector<char> zeros(p->lay.total - p->lay.off_resident, 0);
+                e = hipMemcpy(mem + p->lay.off_resident, zeros.data(), zeros.size(), hipMemcpyHostToDevice);
+            } catch (const std::bad_alloc&) {
+            }
+            if (e != hipSuccess) {
+                (void)hipFree(mem);
+                g_last_hip_error = static_cast<int>(e);
+                return e == hipErrorOutOfMemory ? ADASUM_ERR_OUT_OF_MEMORY : ADASUM_ERR_HIP;
+            }
+        }
+        p->d_ws = mem;
     }
     *ws = p->d_ws;
     return ADASUM_OK;
@@ -523,9 +581,55 @@ int small_reduce(Plan* p, char* ws, void* out, const Opts& o, void* stream) {
     return ADASUM_OK;
 }
 
+// ---- the resident pass ----------------------------------------------------------
+
+// The whole reduction as one pass that reads every operand once.
+int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* out, const Opts& o, void* stream) {
+    const Layout& lay = p->lay;
+    const int L = lay.n_layers, K = p->K;
+    const TileSet tiles = p->unit_tiles.view();
+    const int rc = small_gather(p, ws, grads, dtype, o, stream);
+    if (rc != ADASUM_OK) return rc;
+    ResidentCall c;
+    c.out_dtype = o.out_dtype;
+    c.R = p->resident.R;
+    c.leaves = K;
+    c.form = p->resident.form;
+    c.n_units = static_cast<int>(p->resident.n_units);
+    std::memset(&c.ops, 0, sizeof(c.ops));
+    // (an operand that only fills up the kernel's number repeats the first and gets weight 0)
+    for (int r = 0; r < c.R; ++r) c.ops.pack[r] = grads[r < K ? r : 0];
+    c.out = out;
+    c.units = p->d_units;
+    c.state.epoch = reinterpret_cast<int32_t*>(ws + lay.off_resident);
+    c.state.skipped = c.state.epoch + 1;
+    c.state.partials = reinterpret_cast<unsigned long long*>(ws + lay.off_words);
+    c.state.sums = c.state.partials + lay.partial_words;
+    c.gram = o.layer_stats ? reinterpret_cast<double*>(ws + lay.off_gram) : nullptr;
+    c.normparts = o.layer_stats ? reinterpret_cast<double*>(ws + lay.off_normparts) : nullptr;
+    c.start = o.delta_start;
+    c.order = o.order;
+    if (o.workspace != nullptr || p->borrowed) {
+        // memory that is not the plan's own holds anything
+        ADASUM_LAUNCH(launch_zero_words(c.state.epoch, static_cast<int64_t>((lay.total - lay.off_resident) / sizeof(int32_t)), stream));
+    }
+    char namebuf[48];
+    kernel_name("resident", dtype, o.out_dtype, c.R, false, namebuf, sizeof(namebuf));
+    const double bytes = static_cast<double>(lay.N) * ((K + (o.delta_start ? 1 : 0)) * elem_bytes(dtype) + elem_bytes(o.out_dtype));
+    auto* launch = dtype == ADASUM_F32    ? launch_resident_f32
+                   : dtype == ADASUM_BF16 ? launch_resident_bf16
+                   : dtype == ADASUM_F16  ? launch_resident_f16
+                                          : launch_resident_f64;
+    ADASUM_TIMED(namebuf, bytes, stream, launch(c, stream));
+    if (o.layer_stats != nullptr)
+        ADASUM_LAUNCH(launch_resident_stats(c.normparts, tiles, c.gram, c.R, K, L, o.layer_stats, stream));
+    return small_reduce(p, ws, out, o, stream);
+}
+
 // ---- the level scheduler -------------------------------------------------------
 
 int run_tree(Plan* p, char* ws, const void* const* grads, int dtype, void* out, const Opts& o, void* stream) {
+    if (p->resident.form > 0) return run_resident(p, ws, grads, dtype, out, o, stream);
     const Layout& lay = p->lay;
     const int L = lay.n_layers;
     const int64_t N = lay.N;
@@ -716,6 +820,7 @@ int run_tree(Plan* p, char* ws, const void* const* grads, int dtype, void* out, 
 // operand 0, updated in place) with the next leaves, which are read in their own
 // storage type.
 int run_linear(Plan* p, char* ws, const void* const* grads, int dtype, void* out, const Opts& o, void* stream) {
+    if (p->resident.form > 0) return run_resident(p, ws, grads, dtype, out, o, stream);
     const Layout& lay = p->lay;
     const int L = lay.n_layers;
     const TileSet gt = p->gram_tiles.view();
@@ -879,7 +984,7 @@ int launch_as_graph(Plan* p, char* ws, const void* const* grads, int dtype, void
         ADASUM_HIP(hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking));
     }
     // everything that allocates happens before the capture starts
-    {
+    if (p->resident.form == 0) {
         const int rc = prebuild_tables(p, dtype, o.order);
         if (rc != ADASUM_OK) return rc;
     }
@@ -1033,7 +1138,7 @@ struct Carver {
 // the layer table goes to the device in kernel arguments, the tables are built there, and the
 // scheduler then runs on a plan that only borrows that memory.
 int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_offsets, int n_layers, int dtype,
-                        void* out, const adasum_options* opts, void* stream) {
+                        void* out, const adasum_options* opts, void* stream, bool resident = true) {
     Opts o;
     int64_t N = 0;
     int rc = check_reduce_args(grads, K, layer_offsets, n_layers, dtype, out, opts, o, N);
@@ -1058,6 +1163,7 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
     Carver carve;
     size_t off_offsets = 0, off_gram_tiles = 0, off_gram_begin = 0, off_small = 0, off_ws = 0;
     size_t off_span_tiles = 0, off_span_begin = 0, off_span_parts = 0;
+    size_t off_unit_tiles = 0, off_unit_begin = 0, off_units = 0;
     int gcap = 0;
     int64_t n_gram = 0;
     try {
@@ -1091,16 +1197,26 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
                                : plan.feed ? next_entries_bound(Kv, layer_offsets, L, plan.radices, node_type)
                                            : 0,
                                static_cast<int64_t>(plan.wide_spans.tiles.size()));
+        if (resident && !o.separate) {
+            rc = take_resident(&plan, dtype, o.delta_start != nullptr, layer_offsets, L);
+            if (rc != ADASUM_OK) return rc;
+        }
         // the combine tables this reduction reads: one per distinct tile capacity
         std::vector<int> caps;
         if (K == 1) caps.push_back(combine_tile_capacity(dtype, 1));
-        for (size_t lv = 0; lv < plan.radices.size(); ++lv) {
+        for (size_t lv = 0; lv < plan.radices.size() && plan.resident.form == 0; ++lv) {
             const bool leaves = lv == 0 || o.order == ADASUM_ORDER_LINEAR;
             caps.push_back(table_capacity(plan.feed != 0, plan.radices, lv, leaves ? dtype : node_type));
         }
         off_offsets = carve.take(sizeof(int64_t) * (static_cast<size_t>(L) + 1));
-        off_gram_tiles = carve.take(sizeof(adasum_tile) * static_cast<size_t>(n_gram));
-        off_gram_begin = carve.take(sizeof(int32_t) * (static_cast<size_t>(L) + 1));
+        if (plan.resident.form > 0) {
+            off_unit_tiles = carve.take(sizeof(adasum_tile) * static_cast<size_t>(plan.resident.n_units));
+            off_unit_begin = carve.take(sizeof(int32_t) * (static_cast<size_t>(L) + 1));
+            off_units = carve.take(sizeof(ResidentUnit) * static_cast<size_t>(plan.resident.n_units));
+        } else {
+            off_gram_tiles = carve.take(sizeof(adasum_tile) * static_cast<size_t>(n_gram));
+            off_gram_begin = carve.take(sizeof(int32_t) * (static_cast<size_t>(L) + 1));
+        }
         for (int cap : caps) {
             bool seen = false;
             for (const CombTable& c : combs) seen = seen || c.cap == cap;
@@ -1124,7 +1240,11 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
     } catch (const std::bad_alloc&) {
         return ADASUM_ERR_OUT_OF_MEMORY;
     }
-    if (carve.off > ADASUM_NOALLOC_SCRATCH_BYTES) return ADASUM_ERR_TOO_LARGE;
+    if (carve.off > ADASUM_NOALLOC_SCRATCH_BYTES) {
+        // (the other passes share less between workgroups and may fit still)
+        if (plan.resident.form > 0) return reduce_noalloc_impl(grads, K, layer_offsets, n_layers, dtype, out, opts, stream, false);
+        return ADASUM_ERR_TOO_LARGE;
+    }
 
     char* base = nullptr;
     size_t have = 0;
@@ -1134,12 +1254,22 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
 
     int64_t* d_offsets = reinterpret_cast<int64_t*>(base + off_offsets);
     ADASUM_LAUNCH(launch_put_offsets(layer_offsets, L, d_offsets, stream));
-    plan.gram_tiles.capacity = gcap;
-    plan.gram_tiles.n_borrowed = n_gram;
-    plan.gram_tiles.d_tiles = reinterpret_cast<adasum_tile*>(base + off_gram_tiles);
-    plan.gram_tiles.d_layer_begin = reinterpret_cast<int32_t*>(base + off_gram_begin);
-    ADASUM_LAUNCH(launch_build_tiles(d_offsets, L, gcap, n_gram, plan.gram_tiles.d_tiles,
-                                     plan.gram_tiles.d_layer_begin, stream));
+    if (plan.resident.form > 0) {
+        TileTable& u = plan.unit_tiles;
+        u.n_borrowed = plan.resident.n_units;
+        u.d_tiles = reinterpret_cast<adasum_tile*>(base + off_unit_tiles);
+        u.d_layer_begin = reinterpret_cast<int32_t*>(base + off_unit_begin);
+        plan.d_units = reinterpret_cast<ResidentUnit*>(base + off_units);
+        ADASUM_LAUNCH(launch_build_tiles(d_offsets, L, u.capacity, u.n_borrowed, u.d_tiles, u.d_layer_begin, stream));
+        ADASUM_LAUNCH(launch_resident_units(u.view(), plan.d_units, stream));
+    } else {
+        plan.gram_tiles.capacity = gcap;
+        plan.gram_tiles.n_borrowed = n_gram;
+        plan.gram_tiles.d_tiles = reinterpret_cast<adasum_tile*>(base + off_gram_tiles);
+        plan.gram_tiles.d_layer_begin = reinterpret_cast<int32_t*>(base + off_gram_begin);
+        ADASUM_LAUNCH(launch_build_tiles(d_offsets, L, gcap, n_gram, plan.gram_tiles.d_tiles,
+                                         plan.gram_tiles.d_layer_begin, stream));
+    }
     try {
         for (const CombTable& c : combs) {
             TileTable t;
@@ -1235,13 +1365,15 @@ int adasum_plan_create(int K, const int64_t* layer_offsets, int n_layers, int dt
     h->opts.radix = o.radix == 0 ? default_radix(o) : o.radix;
     h->opts.delta_start = nullptr;
     if (layer_offsets[n_layers] > 0) {
-        rc = make_plan(K, h->opts.radix, o.order, node_dtype(dtype), o.fuse != 0, h->for_delta || o.separate != 0,
-                       layer_offsets, n_layers, h->plan);
+        rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, h->for_delta || o.separate != 0,
+                       o.separate == 0, layer_offsets, n_layers, h->plan);
         if (rc != ADASUM_OK) return rc;
         if (o.workspace != nullptr && o.workspace_bytes < h->plan->lay.total) return ADASUM_ERR_WORKSPACE;
         // everything execute needs exists from here on: it allocates nothing
-        rc = prebuild_tables(h->plan.get(), dtype, o.order);
-        if (rc != ADASUM_OK) return rc;
+        if (h->plan->resident.form == 0) {
+            rc = prebuild_tables(h->plan.get(), dtype, o.order);
+            if (rc != ADASUM_OK) return rc;
+        }
         char* ws = nullptr;
         rc = plan_workspace(h->plan.get(), h->opts, &ws);
         if (rc != ADASUM_OK) return rc;
@@ -1315,7 +1447,7 @@ int adasum_workspace_bytes(int K, const int64_t* layer_offsets, int n_layers, in
         const int Kv = o.order == ADASUM_ORDER_LINEAR ? K : virtual_leaves(radices);
         std::vector<SmallLayer> small;
         const int64_t small_elems = K > 1 ? find_small_layers(layer_offsets, n_layers, small) : 0;
-        const Layout lay = make_layout(Kv, layer_offsets[n_layers], n_layers,
+        Layout lay = make_layout(Kv, layer_offsets[n_layers], n_layers,
                                        count_tiles(layer_offsets, n_layers, gram_tile_capacity(layer_offsets, n_layers)),
                                        norm_entries_bound(Kv, layer_offsets, n_layers, radices, node_dtype(dtype)),
                                        radices, o.order, K + 1, small_elems, node_dtype(dtype),
@@ -1326,6 +1458,10 @@ int adasum_workspace_bytes(int K, const int64_t* layer_offsets, int n_layers, in
                                        !radices.empty() && wide_radix(radices[0])
                                            ? count_spans(layer_offsets, n_layers, wide_part_count(layer_offsets[n_layers]))
                                            : 0);
+        if (!o.separate) {
+            const ResidentPlan r = plan_resident(K, radices, dtype, o.delta_start != nullptr, layer_offsets, n_layers);
+            if (r.form > 0) add_resident(lay, r);
+        }
         *bytes = lay.total;
     } catch (const std::bad_alloc&) {
         return ADASUM_ERR_OUT_OF_MEMORY;

@@ -201,6 +201,10 @@ struct Layout {
     size_t  off_dotparts = 0; // doubles [sibling pair][combine tile]: dot product of the two nodes a
                               // sibling-fused combine wrote (only with fuse_siblings)
     int64_t dot_entries = 0;
+    size_t  base_total = 0;   // bytes of everything above
+    size_t  off_resident = 0; // a resident pass: int32 [1 + units], then the tagged words (see ResidentState)
+    size_t  off_words = 0;
+    int64_t partial_words = 0;
     size_t  total = 0;
 };
 // `norm_entries`: doubles needed for the squared norms the combines leave
@@ -257,6 +261,93 @@ struct TileSet {
     const int32_t* part_begin = nullptr;
     int n_parts = 0;
 };
+
+// ---- the resident pass (adasum_resident.hip) ----------------------------------
+//
+// How much a workgroup keeps (16-byte granules per lane and operand, in registers and in LDS) and how many workgroups
+// a compute unit holds.  Form 1: one granule, for problems that the chip holds at once in such pieces (latency counts).
+// Form 2: three workgroups per compute unit; form 3: two, which keep more.  Smaller units overlap better (K = 2 bf16,
+// ResNet-50 sizes: 40 us in form 2, 62 in form 3; K = 6 binary16: 115 and 121), but a layer that takes most of the chip
+// stalls it (K = 8 fp32, whose largest layers have 75 of 84 MB: 260 us in form 2, 217 in form 3): form 2 while the
+// largest layer takes at most half of its workgroups.  Groups of more than 8 operands have forms 1 and 3 (one step of
+// 16 operands is 64 KB).
+constexpr int kResidentRadix = 8;        // operands at most
+constexpr int kResidentCus = 256;        // compute units the figures are for; not used on fewer
+constexpr int kDirectUnits = 16;         // units of a layer up to which every workgroup reads all partial sums
+constexpr int resident_slots(int form) { return form == 3 ? 2 * kResidentCus : 3 * kResidentCus; }
+// units of a layer at most: its workgroups must be on the chip together
+constexpr int resident_most(int form) { return form == 3 ? resident_slots(3) - 12 : resident_slots(form) / 2; }
+constexpr int resident_register_steps(int dtype, int R, bool delta, int form) {
+    const int rows = form == 2 ? 24 : (dtype == ADASUM_F64 || R > 8 ? 32 : 40);
+    const int steps = rows / (R + (delta ? 1 : 0));
+    return steps < 16 ? (steps < 1 ? 1 : steps) : 16;
+}
+constexpr int resident_lds_steps(int R, bool delta, int form) {
+    const int steps = (form == 2 ? 12 : 18) / (R + (delta ? 1 : 0));
+    return steps < 8 ? steps : 8;
+}
+constexpr int resident_capacity(int dtype, int R, bool delta, int form) {
+    const int steps = form == 1 ? 1 : resident_register_steps(dtype, R, delta, form) + resident_lds_steps(R, delta, form);
+    return kThreads * steps * (dtype == ADASUM_F64 ? 2 : dtype == ADASUM_F32 ? 4 : 8);
+}
+// Operands a resident kernel is instantiated for that holds a group of `leaves`.
+constexpr int resident_operands(int leaves) { return leaves <= 8 ? leaves : (leaves + 1) / 2 * 2; }
+
+struct ResidentPlan {
+    int form = 0;        // 0: the reduction is taken in the other passes
+    int R = 0, capacity = 0;
+    int64_t n_units = 0;
+};
+// A reduction in one pass (of either order) as a resident pass, where its layer table suits one.
+ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bool delta, const int64_t* layer_offsets,
+                           int n_layers);
+// Adds its section to a layout.
+void add_resident(Layout& lay, const ResidentPlan& p);
+
+// A unit: consecutive elements of one layer, all operands, that one workgroup keeps.
+struct ResidentUnit {
+    int64_t start;
+    int32_t len, layer;
+    int32_t unit;                      // its place among the units in element order
+    int32_t layer_first, layer_end;    // its layer's units
+    int32_t pad;
+};
+// The units in launch order, from the tile table of the plan's capacity.
+void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int form,
+                 std::vector<ResidentUnit>& units);
+
+// What the workgroups of a resident pass share.  All zero before the first pass; every call has a tag of its own.
+struct ResidentState {
+    int32_t* epoch;                 // calls so far
+    int32_t* skipped;               // [unit in launch order]: gave up waiting, done by the second launch
+    unsigned long long* partials;   // [unit][entry][2]
+    unsigned long long* sums;       // [layer][entry][2]
+};
+struct ResidentCall {
+    int out_dtype, R, leaves, form, n_units;
+    Operands ops;
+    void* out;
+    const ResidentUnit* units;
+    ResidentState state;
+    double* gram;            // or null: [layer][R][R]
+    double* normparts;       // or null: [unit]
+    const void* start;       // or null: the after-optimizer form
+    int order;
+};
+int launch_resident_f32(const ResidentCall& c, void* stream);
+int launch_resident_bf16(const ResidentCall& c, void* stream);
+int launch_resident_f16(const ResidentCall& c, void* stream);
+int launch_resident_f64(const ResidentCall& c, void* stream);
+int launch_resident_wide_f32(const ResidentCall& c, void* stream);
+int launch_resident_wide_bf16(const ResidentCall& c, void* stream);
+int launch_resident_wide_f16(const ResidentCall& c, void* stream);
+// n 32-bit words to zero (no hipMemset: callers may capture).
+int launch_zero_words(int32_t* p, int64_t n, void* stream);
+// The units in element order from their tile table (where nothing may be copied from the host).
+int launch_resident_units(const TileSet& t, ResidentUnit* units, void* stream);
+// stats[layer] = squared norm of the result (its units' sums), sum of the leaves' (the trace of the Gram matrix).
+int launch_resident_stats(const double* normparts, const TileSet& t, const double* gram, int R, int leaves, int n_layers,
+                          double* stats, void* stream);
 
 // All launchers return a hipError_t as int (0 = success) and enqueue on `stream`.
 // partials[(group * gt.n_tiles + tile) * entries + entry]

@@ -30,17 +30,11 @@
 #include <type_traits>
 
 #include "adasum_host.h"
+#include "adasum_device.h"
 
-// Tuning knobs (compile-time): 16-byte loads a lane issues before consuming any,
-// and whether streaming loads / stores carry the non-temporal hint.
+// Tuning knob (compile-time): 16-byte loads a lane issues before consuming any.
 #ifndef ADASUM_INFLIGHT
 #define ADASUM_INFLIGHT 8
-#endif
-#ifndef ADASUM_NT_LOAD
-#define ADASUM_NT_LOAD 1
-#endif
-#ifndef ADASUM_NT_STORE
-#define ADASUM_NT_STORE 1
 #endif
 // bf16 Gram entries through v_dot2c_f32_bf16: 0 = never (unpack + fp32 FMA), 1 = only at
 // radix 16, where 136 entries per lane would otherwise be bound by the vector ALUs
@@ -64,256 +58,6 @@ static __device__ __align__(256) unsigned char scratch[ADASUM_NOALLOC_SCRATCH_BY
 
 namespace adasum {
 namespace {
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-
-struct bf16_t { unsigned short v; };
-struct f16_t { unsigned short v; };   // IEEE binary16
-typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
-
-// VEC: elements per 16-byte granule; acc_t: the type lanes compute in (fp64 storage is
-// reduced in fp64 throughout, everything else in fp32 lanes with fp64 above the wave)
-template <typename T> struct Traits;
-template <> struct Traits<float>  { static constexpr int VEC = 4; typedef float acc_t; };
-template <> struct Traits<bf16_t> { static constexpr int VEC = 8; typedef float acc_t; };
-template <> struct Traits<f16_t>  { static constexpr int VEC = 8; typedef float acc_t; };
-template <> struct Traits<double> { static constexpr int VEC = 2; typedef double acc_t; };
-
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// round to nearest even; NaN stays NaN (quiet), overflow rounds to infinity
-__device__ __forceinline__ unsigned int f32_to_bf16_rne(float f) {
-    unsigned int u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x0040u;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-
-// G consecutive elements of T held as raw 32-bit words (8, 16 or 32 bytes)
-template <typename T, int G>
-struct Granule {
-    static constexpr int NW = G * (int)sizeof(T) / 4;
-    static_assert(NW == 2 || NW == 4 || NW == 8, "granule must be 8, 16 or 32 bytes");
-    unsigned int w[NW];
-};
-
-template <typename V>
-__device__ __forceinline__ V stream_load(const V* p) {
-#if ADASUM_NT_LOAD
-    return __builtin_nontemporal_load(p);
-#else
-    return *p;
-#endif
-}
-
-template <bool NT, typename V>
-__device__ __forceinline__ void stream_store(V v, V* p) {
-    if constexpr (NT && ADASUM_NT_STORE) {
-        __builtin_nontemporal_store(v, p);
-    } else {
-        *p = v;
-    }
-}
-
-// p must be aligned to the granule size (to 16 bytes for a 32-byte granule)
-template <typename T, int G>
-__device__ __forceinline__ void load_raw(Granule<T, G>& r, const T* p) {
-    constexpr int NW = Granule<T, G>::NW;
-    if constexpr (NW == 2) {
-        const u32x2 q = stream_load(reinterpret_cast<const u32x2*>(p));
-        r.w[0] = q.x;
-        r.w[1] = q.y;
-    } else {
-#pragma unroll
-        for (int i = 0; i < NW / 4; ++i) {
-            const u32x4 q = stream_load(reinterpret_cast<const u32x4*>(p) + i);
-            r.w[4 * i + 0] = q.x;
-            r.w[4 * i + 1] = q.y;
-            r.w[4 * i + 2] = q.z;
-            r.w[4 * i + 3] = q.w;
-        }
-    }
-}
-
-template <int G>
-__device__ __forceinline__ void unpack(const Granule<float, G>& r, float (&v)[G]) {
-#pragma unroll
-    for (int i = 0; i < G; ++i) v[i] = __uint_as_float(r.w[i]);
-}
-
-template <int G>
-__device__ __forceinline__ void unpack(const Granule<bf16_t, G>& r, float (&v)[G]) {
-#pragma unroll
-    for (int i = 0; i < G / 2; ++i) {
-        v[2 * i + 0] = __uint_as_float(r.w[i] << 16);
-        v[2 * i + 1] = __uint_as_float(r.w[i] & 0xffff0000u);
-    }
-}
-
-template <int G>
-__device__ __forceinline__ void unpack(const Granule<f16_t, G>& r, float (&v)[G]) {
-#pragma unroll
-    for (int i = 0; i < G / 2; ++i) {
-        const f16x2_t h = __builtin_bit_cast(f16x2_t, r.w[i]);
-        v[2 * i + 0] = static_cast<float>(h.x);
-        v[2 * i + 1] = static_cast<float>(h.y);
-    }
-}
-
-template <int G>
-__device__ __forceinline__ void unpack(const Granule<double, G>& r, double (&v)[G]) {
-#pragma unroll
-    for (int i = 0; i < G; ++i)
-        v[i] = __longlong_as_double((static_cast<long long>(r.w[2 * i + 1]) << 32) |
-                                    static_cast<long long>(r.w[2 * i]));
-}
-
-// fp32 -> binary16, round to nearest even (the conversion instruction's default mode)
-__device__ __forceinline__ unsigned int f32_to_f16_bits(float f) {
-    const _Float16 h = static_cast<_Float16>(f);
-    return static_cast<unsigned int>(__builtin_bit_cast(unsigned short, h));
-}
-
-template <bool NT, int NW>
-__device__ __forceinline__ void store_words(void* p, const unsigned int (&w)[NW]) {
-    if constexpr (NW == 2) {
-        u32x2 q;
-        q.x = w[0];
-        q.y = w[1];
-        stream_store<NT>(q, reinterpret_cast<u32x2*>(p));
-    } else {
-#pragma unroll
-        for (int i = 0; i < NW / 4; ++i) {
-            u32x4 q;
-            q.x = w[4 * i + 0];
-            q.y = w[4 * i + 1];
-            q.z = w[4 * i + 2];
-            q.w = w[4 * i + 3];
-            stream_store<NT>(q, reinterpret_cast<u32x4*>(p) + i);
-        }
-    }
-}
-
-template <bool NT, int G>
-__device__ __forceinline__ void store_granule(float* p, const float (&v)[G]) {
-    unsigned int w[G];
-#pragma unroll
-    for (int i = 0; i < G; ++i) w[i] = __float_as_uint(v[i]);
-    store_words<NT>(p, w);
-}
-
-template <bool NT, int G>
-__device__ __forceinline__ void store_granule(bf16_t* p, const float (&v)[G]) {
-    unsigned int w[G / 2];
-#pragma unroll
-    for (int i = 0; i < G / 2; ++i) w[i] = f32_to_bf16_rne(v[2 * i]) | (f32_to_bf16_rne(v[2 * i + 1]) << 16);
-    store_words<NT>(p, w);
-}
-
-template <bool NT, int G>
-__device__ __forceinline__ void store_granule(f16_t* p, const float (&v)[G]) {
-    unsigned int w[G / 2];
-#pragma unroll
-    for (int i = 0; i < G / 2; ++i) w[i] = f32_to_f16_bits(v[2 * i]) | (f32_to_f16_bits(v[2 * i + 1]) << 16);
-    store_words<NT>(p, w);
-}
-
-template <bool NT, int G>
-__device__ __forceinline__ void store_granule(double* p, const double (&v)[G]) {
-    unsigned int w[2 * G];
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-        const long long b = __double_as_longlong(v[i]);
-        w[2 * i] = static_cast<unsigned int>(b);
-        w[2 * i + 1] = static_cast<unsigned int>(b >> 32);
-    }
-    store_words<NT>(p, w);
-}
-
-__device__ __forceinline__ double load_elem(const double* p) { return *p; }
-__device__ __forceinline__ void store_elem(double* p, double v) { *p = v; }
-__device__ __forceinline__ float load_elem(const float* p) { return *p; }
-__device__ __forceinline__ float load_elem(const f16_t* p) {
-    return static_cast<float>(__builtin_bit_cast(_Float16, p->v));
-}
-__device__ __forceinline__ void store_elem(f16_t* p, float v) {
-    p->v = static_cast<unsigned short>(f32_to_f16_bits(v));
-}
-__device__ __forceinline__ float load_elem(const bf16_t* p) {
-    return __uint_as_float(static_cast<unsigned int>(p->v) << 16);
-}
-__device__ __forceinline__ void store_elem(float* p, float v) { *p = v; }
-__device__ __forceinline__ void store_elem(bf16_t* p, float v) {
-    p->v = static_cast<unsigned short>(f32_to_bf16_rne(v));
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
-}
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
-}
-
-// Sums every one of N per-lane values over the 64 lanes of a wave with N + N/2 + ... shuffles
-// instead of 6 N: at the step with mask m a lane whose bit m is clear keeps the even-indexed
-// values and hands the odd-indexed ones to its partner (and the other way round), so each step
-// halves the number of values a lane carries.  On return lane l holds in v[i] the complete sum
-// of value number l + 64 i (values past N are padding).  Fixed order: bit-identical reruns.
-template <typename A, int N>
-__device__ __forceinline__ void wave_sum_scatter(A (&v)[N], int lane) {
-    static_assert(N >= 1, "");
-    int n = N;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const bool upper = (lane & m) != 0;
-        const int half = (n + 1) / 2;
-#pragma unroll
-        for (int i = 0; i < (N + 1) / 2; ++i) {
-            if (i < half) {
-                const A a = v[2 * i];
-                const A b = (2 * i + 1 < n) ? v[2 * i + 1] : static_cast<A>(0);
-                const A keep = upper ? b : a, send = upper ? a : b;
-                v[i] = keep + __shfl_xor(send, m, 64);
-            }
-        }
-        n = half;
-    }
-}
-
-template <int R>
-__device__ __forceinline__ const void* operand_ptr(const Operands& ops, int g, int r) {
-    return ops.pack[g * R + r];
-}
-
-// The tile split every kernel uses: [start, hs) scalar head, [bs, be) whole
-// granules aligned to G elements of the global index, [ts, end) scalar tail.
-struct Split {
-    long long start, end, bs, hs, ts;
-    int ng, nh, nt;
-};
-
-template <int G>
-__device__ __forceinline__ Split split_tile(const adasum_tile& t) {
-    Split s;
-    s.start = t.start;
-    s.end = t.start + t.len;
-    s.bs = (s.start + (G - 1)) / G * G;
-    const long long be = s.end / G * G;
-    s.hs = s.bs < s.end ? s.bs : s.end;
-    s.ts = be > s.hs ? be : s.hs;
-    s.ng = be > s.bs ? static_cast<int>((be - s.bs) / G) : 0;
-    s.nh = static_cast<int>(s.hs - s.start);
-    s.nt = static_cast<int>(s.end - s.ts);
-    return s;
-}
 
 // ---------------------------------------------------------------------------
 // Step 1: per-tile partial Gram entries of R operands.
@@ -553,69 +297,6 @@ norm_coarsen_kernel(const double* __restrict__ fine, int n_fine_tiles,
     if (threadIdx.x == 0) coarse[static_cast<long long>(node) * n_gram_tiles + t] = v;
 }
 
-// Entry e of the Gram kernel's order -> (i, j).
-template <int R, bool DIAG>
-__device__ __forceinline__ void entry_to_ij(int e, int& i, int& j) {
-    i = 0;
-    int rowlen = DIAG ? R : R - 1;
-    while (e >= rowlen) {
-        e -= rowlen;
-        ++i;
-        --rowlen;
-    }
-    j = (DIAG ? i : i + 1) + e;
-}
-
-// The tree's weights from one Gram matrix, computed by one wave (64 lanes): every node of
-// the tree is a combination of its leaves, node = sum_p w_p x_p; for two sibling nodes A and
-// B the operator of Section 3 needs d = A.B = sum_{p in A, q in B} w_p w_q G_pq, n1 = |A|^2,
-// n2 = |B|^2 (quadratic forms whose terms are spread over the lanes and summed in a fixed
-// order) and scales A's weights by 1 - d/(2 n1), B's by 1 - d/(2 n2); a zero squared norm
-// gives coefficient 1.  G and w live in LDS; r leaves are real, the rest get weight 0.
-template <int R>
-__device__ __forceinline__ double wave_quadratic(const double* G, const double* w, int a0, int a1, int b0, int b1,
-                                                 int lane) {
-    const int nb = b1 - b0, n = (a1 - a0) * nb;
-    double v = 0.0;
-    for (int i = lane; i < n; i += 64) {
-        const int p = a0 + i / nb, q = b0 + i % nb;
-        v += w[p] * w[q] * G[p * R + q];
-    }
-    return wave_sum(v);
-}
-
-template <int R>
-__device__ __forceinline__ void wave_merge(const double* G, double* w, int a0, int a1, int b0, int b1, int lane) {
-    const double n1 = wave_quadratic<R>(G, w, a0, a1, a0, a1, lane);
-    const double n2 = wave_quadratic<R>(G, w, b0, b1, b0, b1, lane);
-    const double d = wave_quadratic<R>(G, w, a0, a1, b0, b1, lane);
-    const double ca = n1 > 0.0 ? 1.0 - d / (2.0 * n1) : 1.0;
-    const double cb = n2 > 0.0 ? 1.0 - d / (2.0 * n2) : 1.0;
-    if (lane >= a0 && lane < a1) w[lane] *= ca;
-    if (lane >= b0 && lane < b1) w[lane] *= cb;
-}
-
-template <int R>
-__device__ __forceinline__ void wave_tree_weights(const double* G, double* w, int r, int order, int lane) {
-    if (lane < R) w[lane] = lane < r ? 1.0 : 0.0;
-    if (order == ADASUM_ORDER_LINEAR) {
-        for (int k = 1; k < r; ++k) wave_merge<R>(G, w, 0, k, k, k + 1, lane);
-        return;
-    }
-    // the halving tree over r leaves, deepest nodes first: children before parents
-    int levels = 0;
-    while ((1 << levels) < r) ++levels;
-    for (int d = levels - 1; d >= 0; --d) {
-        for (int j = 0; j < (1 << d); ++j) {
-            int lo, hi;
-            leaf_range(r, d, j, lo, hi);
-            if (hi - lo >= 2) {
-                const int mid = lo + (hi - lo) / 2;
-                wave_merge<R>(G, w, lo, mid, mid, hi, lane);
-            }
-        }
-    }
-}
 
 // The same walk by a whole workgroup of NW waves (the wide first pass: 63 merges of up to 32 x 32 terms
 // are slow one after the other): the nodes of one depth are independent, so their 3 quadratic forms
@@ -2453,6 +2134,70 @@ int static_scratch(char** base, size_t* bytes) {
     *base = ptrs[dev];
     *bytes = sizeof(scratch);
     return 0;
+}
+
+__global__ void __launch_bounds__(kThreads) zero_words_kernel(int32_t* __restrict__ p, long long n) {
+    for (long long i = static_cast<long long>(blockIdx.x) * kThreads + threadIdx.x; i < n;
+         i += static_cast<long long>(gridDim.x) * kThreads)
+        p[i] = 0;
+}
+
+int launch_zero_words(int32_t* p, int64_t n, void* stream) {
+    if (n <= 0) return 0;
+    const long long blocks = std::min<long long>((n + kThreads - 1) / kThreads, 1024);
+    hipLaunchKernelGGL(zero_words_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0,
+                       static_cast<hipStream_t>(stream), p, static_cast<long long>(n));
+    return check_launch();
+}
+
+__global__ void __launch_bounds__(kThreads)
+resident_units_kernel(const adasum_tile* __restrict__ tiles, int n, const int32_t* __restrict__ layer_begin,
+                      ResidentUnit* __restrict__ units) {
+    const int i = static_cast<int>(blockIdx.x) * kThreads + static_cast<int>(threadIdx.x);
+    if (i >= n) return;
+    const adasum_tile t = tiles[i];
+    ResidentUnit u;
+    u.start = t.start;
+    u.len = t.len;
+    u.layer = t.layer;
+    u.unit = i;
+    u.layer_first = layer_begin[t.layer];
+    u.layer_end = layer_begin[t.layer + 1];
+    u.pad = 0;
+    units[i] = u;
+}
+
+int launch_resident_units(const TileSet& t, ResidentUnit* units, void* stream) {
+    const int n = static_cast<int>(t.n_tiles);
+    if (n < 1) return 0;
+    hipLaunchKernelGGL(resident_units_kernel, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0,
+                       static_cast<hipStream_t>(stream), t.tiles, n, t.layer_begin, units);
+    return check_launch();
+}
+
+// (an empty layer has no units and no Gram matrix: zeros)
+__global__ void __launch_bounds__(64)
+resident_stats_kernel(const double* __restrict__ normparts, const int32_t* __restrict__ layer_begin,
+                      const double* __restrict__ gram, int R, int leaves, double* __restrict__ stats) {
+    const int l = blockIdx.x, lane = threadIdx.x;
+    const int tb = layer_begin[l], te = layer_begin[l + 1];
+    double v = 0.0;
+    for (int t = tb + lane; t < te; t += 64) v += normparts[t];
+    v = wave_sum(v);
+    double d = te > tb && lane < leaves ? gram[static_cast<long long>(l) * R * R + lane * (R + 1)] : 0.0;
+    d = wave_sum(d);
+    if (lane == 0) {
+        stats[2 * l] = v;
+        stats[2 * l + 1] = d;
+    }
+}
+
+int launch_resident_stats(const double* normparts, const TileSet& t, const double* gram, int R, int leaves, int n_layers,
+                          double* stats, void* stream) {
+    if (n_layers == 0) return 0;
+    hipLaunchKernelGGL(resident_stats_kernel, dim3(n_layers), dim3(64), 0, static_cast<hipStream_t>(stream), normparts,
+                       t.layer_begin, gram, R, leaves, stats);
+    return check_launch();
 }
 
 int launch_put_words(const int64_t* words, size_t n_words, int64_t* d_words, void* stream) {

@@ -1,0 +1,564 @@
+// The resident pass (gfx950): a pass whose layers fit on the chip reads its operands ONCE.  A workgroup loads a unit
+// (a run of consecutive elements of one layer, all operands), keeps it in registers and LDS, sends its
+// partial Gram entries to the other workgroups of the layer, gets the layer's whole Gram matrix back, walks the tree's
+// scalars and combines from what it kept.  One launch takes the place of gram_kernel, gram_finish_kernel and
+// combine_kernel, and operands that those read twice cross the fabric between the memory and the compute dies once.
+//
+// What bounds it.  Re-reading is what the three kernels lose: the Infinity Cache gives a compute die no more bandwidth
+// than memory does (7.1 TB/s, measured on 64 .. 256 MB re-read in a loop against 7.0 TB/s fresh), so bytes have to stay
+// in registers and LDS to be saved.  The chip holds some 110 MB there, about 15 us of memory traffic; a unit lives
+// through its loads (5 .. 12 us), the exchange (5 .. 10 us: two trips through memory under load, and waiting for the
+// layer's slowest unit), the scalars (1 us) and its stores.  So the pass is bound by how much is kept over how long:
+// hence as much as the register file takes per unit, LDS filled straight from memory beside it, an exchange without
+// atomics, flags or fences (a fence of agent scope cost 1.4 x the whole pass), and launch order (order_units).
+// Measured against the three kernels, us per reduction: ResNet-50 sizes, K = 8 fp32 298 -> 217, K = 2 bf16 51 -> 40,
+// K = 6 binary16 152 -> 115.
+#include <hip/hip_runtime.h>
+
+#include "adasum_host.h"
+#include "adasum_device.h"
+
+namespace adasum {
+namespace {
+
+template <typename T> struct DtypeOf;
+template <> struct DtypeOf<float> { enum { value = ADASUM_F32 }; };
+template <> struct DtypeOf<bf16_t> { enum { value = ADASUM_BF16 }; };
+template <> struct DtypeOf<f16_t> { enum { value = ADASUM_F16 }; };
+template <> struct DtypeOf<double> { enum { value = ADASUM_F64 }; };
+
+// element k of some 32-bit words of T, widened to the type lanes compute in
+template <typename T> __device__ __forceinline__ typename Traits<T>::acc_t element(const unsigned int* w, int k) {
+    if constexpr (std::is_same<T, float>::value) return __uint_as_float(w[k]);
+    else if constexpr (std::is_same<T, bf16_t>::value)
+        return __uint_as_float((k & 1) ? (w[k / 2] & 0xffff0000u) : (w[k / 2] << 16));
+    else if constexpr (std::is_same<T, f16_t>::value) {
+        const f16x2_t h = __builtin_bit_cast(f16x2_t, w[k / 2]);
+        return static_cast<float>((k & 1) ? h.y : h.x);
+    } else {
+        return __longlong_as_double((static_cast<long long>(w[2 * k + 1]) << 32) | static_cast<long long>(w[2 * k]));
+    }
+}
+
+// The rows and columns of the Gram entries (i <= j), row by row.
+template <int R>
+struct Entries {
+    int row[R * (R + 1) / 2], col[R * (R + 1) / 2];
+    constexpr Entries() : row(), col() {
+        int e = 0;
+        for (int i = 0; i < R; ++i)
+            for (int j = i; j < R; ++j) {
+                row[e] = i;
+                col[e] = j;
+                ++e;
+            }
+    }
+};
+template <int R> constexpr Entries<R> kEntries{};
+
+// ---- values that one workgroup of a launch writes and others read ----
+// A double travels as two 8-byte words, each with half of its bits and the call's tag: a reader knows from the word
+// itself whether it was written in this call, so there are no flags, no counters and nothing to wait for between a
+// value and its announcement.  Accesses are relaxed and of agent scope (they go past the compute dies' own caches).
+__device__ __forceinline__ void send(unsigned long long* p, double v, unsigned tag) {
+    const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(v));
+    const unsigned long long t = static_cast<unsigned long long>(tag) << 32;
+    __hip_atomic_store(p, t | (b & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+struct Words {
+    unsigned long long lo, hi;
+};
+__device__ __forceinline__ Words peek(const unsigned long long* p) {
+    Words w;
+    w.lo = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    w.hi = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return w;
+}
+__device__ __forceinline__ double value(const Words& w) {
+    return __longlong_as_double(static_cast<long long>((w.hi << 32) | (w.lo & 0xffffffffull)));
+}
+// Looks again until the value is there, or the time is up (false).
+__device__ __forceinline__ bool await(const unsigned long long* p, Words& w, unsigned tag, long long deadline) {
+    while (static_cast<unsigned>(w.lo >> 32) != tag || static_cast<unsigned>(w.hi >> 32) != tag) {
+        if (static_cast<long long>(wall_clock64()) > deadline) return false;
+        __builtin_amdgcn_s_sleep(2);
+        w = peek(p);
+    }
+    return true;
+}
+
+constexpr int kSkipScan = 32;            // units a workgroup of the second launch looks at
+#ifndef ADASUM_WAIT_TICKS
+#define ADASUM_WAIT_TICKS 10000
+#endif
+constexpr long long kWaitTicks = ADASUM_WAIT_TICKS;   // of the 100 MHz clock: 100 us
+
+// 16 bytes per lane straight from memory into LDS (lane l's at dst + 16 l): no registers are held meanwhile.
+__device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 2 /* non-temporal */);
+}
+
+// One workgroup per unit.  SV steps of 256 granules (16 bytes) of every operand stay in registers, SL in LDS; WPS
+// waves per SIMD are resident, i.e. WPS workgroups per compute unit.
+//
+// A layer of W units gets its Gram matrix in one trip when W is small (every workgroup reads the W partial matrices)
+// and in two otherwise (wave w of the q-th workgroup sums entry q + W w over the units; everybody reads the sums).
+// The order of the sums depends on W alone: identical inputs give bit-identical outputs.
+//
+// Waiting is bounded, because nothing promises that a layer's workgroups run side by side (another stream's kernels
+// may hold part of the chip): after 100 us a workgroup marks its unit and ends.  The second launch (`second`) does the
+// marked units from memory, with the same arithmetic -- by then every partial sum is there -- and moves the tag on.
+// DELTA: operands are x - start, the result is start + z (the single pass of the after-optimizer form).
+template <typename TI, typename TO, int R, bool DELTA, int SV, int SL, int WPS>
+__global__ void __launch_bounds__(kThreads, WPS)
+resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ units, int n_units, const ResidentState st,
+                int second, double* __restrict__ gram, double* __restrict__ normparts, const TI* start, int order, int leaves) {
+    constexpr int G = Traits<TI>::VEC;
+    constexpr int NP = R * (R + 1) / 2;
+    constexpr int NW = kThreads / 64;
+    constexpr int ROWS = kThreads / NP;
+    constexpr int kEdge = 2 * (G - 1);
+    constexpr int RL = R + (DELTA ? 1 : 0);   // rows kept: the operands, and `start`
+    // entries accumulated side by side: more than some 60 do not fit beside what is kept, and take more sweeps over it
+    constexpr int SWEEPS = (NP + 59) / 60;
+    constexpr int NA = (NP + SWEEPS - 1) / SWEEPS;
+    // 16-bit products through the packed dot instruction, as gram_kernel: only where the vector units would bind
+    constexpr bool DOT2 = sizeof(TI) == 2 && R > 8;
+    typedef typename Traits<TI>::acc_t acc_t;
+    typedef typename Traits<TO>::acc_t out_acc_t;
+    constexpr bool NTS = !(sizeof(TI) == 2 && sizeof(TO) == 4 && R <= 2);   // as combine_kernel
+    static_assert(ROWS >= 1 && SV >= 1 && R <= 16, "");
+
+    __shared__ double shP[NW * NP];
+    __shared__ double shR[ROWS * NP];
+    __shared__ double shEdge[R][kEdge > 0 ? kEdge : 1];
+    __shared__ double shG[R * R];
+    __shared__ double shW[R];
+    __shared__ double shQ[4 * R];
+    __shared__ double shNorm[NW];
+    __shared__ int shSkip;
+    __shared__ __align__(16) unsigned char shKeep[SL > 0 ? SL * RL * kThreads * 16 : 16];
+
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned tag = static_cast<unsigned>(*st.epoch) + 1u;
+
+    int at = static_cast<int>(blockIdx.x);
+    unsigned long long todo = 0;
+    if (second) {
+        const int u0 = static_cast<int>(blockIdx.x) * kSkipScan;
+        int mine = 0;
+        if (lane < kSkipScan && u0 + lane < n_units) mine = st.skipped[u0 + lane];
+        todo = __ballot(mine != 0);
+        __syncthreads();
+        if (mine != 0 && wave == 0) st.skipped[u0 + lane] = 0;
+        if (blockIdx.x == 0 && tid == 0) *st.epoch = static_cast<int32_t>(tag);
+        if (todo == 0) return;
+    }
+    do {
+    // (opaque to the compiler: what follows from the thread's number is not held in registers across the loop, where
+    // the operands need them; without this the pass spills 40 registers and more)
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    if (second) {
+        const int b = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        at = static_cast<int>(blockIdx.x) * kSkipScan + b;
+    }
+    const ResidentUnit t = units[at];
+    const int W = t.layer_end - t.layer_first;
+    adasum_tile tile;
+    tile.start = t.start;
+    tile.len = t.len;
+    tile.layer = t.layer;
+    const Split s = split_tile<G>(tile);
+    auto operand = [&](int r) { return static_cast<const TI*>(ops.pack[r]); };
+
+    // every load of the unit is issued before anything is consumed
+    // (a lane past the last granule re-reads that one: no divergent branch around a load)
+    auto granule_at = [&](int i) {
+        const int j = i * kThreads + tid;
+        return s.bs + static_cast<long long>(j < s.ng ? j : s.ng - 1) * G;
+    };
+    Granule<TI, G> raw[SV][RL];
+#pragma unroll
+    for (int i = 0; i < SV; ++i) {
+        if (i * kThreads < s.ng) {
+            const long long idx = granule_at(i);
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_raw(raw[i][r], operand(r) + idx);
+            if constexpr (DELTA) load_raw(raw[i][R], start + idx);
+        }
+    }
+    // step SV + i, row r: this wave's 1 KB
+    auto keep = [&](int i, int r) { return shKeep + ((i * RL + r) * NW + wave) * 1024; };
+    if constexpr (SL > 0) {
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            if ((SV + i) * kThreads < s.ng) {
+                const long long idx = granule_at(SV + i);
+#pragma unroll
+                for (int r = 0; r < R; ++r) load_to_lds(operand(r) + idx, keep(i, r));
+                if constexpr (DELTA) load_to_lds(start + idx, keep(i, R));
+            }
+        }
+    }
+    const int nedge = s.nh + s.nt;
+    const long long eidx = lane < s.nh ? s.start + lane : s.ts + (lane - s.nh);
+    __builtin_amdgcn_sched_barrier(0);
+
+    if (!second) {
+        if (tid == 0) shSkip = 0;
+        // the ragged head and tail are multiplied and summed in fp64
+        if (wave == 0 && lane < nedge) {
+            double sd = 0.0;
+            if constexpr (DELTA) sd = static_cast<double>(load_elem(start + eidx));
+#pragma unroll
+            for (int r = 0; r < R; ++r) shEdge[r][lane] = static_cast<double>(load_elem(operand(r) + eidx)) - sd;
+        }
+#pragma unroll
+        for (int sweep = 0; sweep < SWEEPS; ++sweep) {
+            acc_t acc[NA];
+#pragma unroll
+            for (int e = 0; e < NA; ++e) acc[e] = 0;
+            // eight bytes of every row
+            auto multiply = [&](const unsigned int (&q)[RL][2], bool live) {
+                if constexpr (DOT2) {
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        unsigned int x[R];
+#pragma unroll
+                        for (int r = 0; r < R; ++r) x[r] = live ? q[r][k] : 0u;
+#pragma unroll
+                        for (int e = 0; e < NA; ++e)
+                            if (sweep * NA + e < NP) {
+                                const int a = kEntries<R>.row[sweep * NA + e], b = kEntries<R>.col[sweep * NA + e];
+                                if constexpr (std::is_same<TI, bf16_t>::value)
+                                    acc[e] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, x[a]),
+                                                                             __builtin_bit_cast(bf16x2_t, x[b]), acc[e], false);
+                                else
+                                    acc[e] = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, x[a]),
+                                                                    __builtin_bit_cast(f16x2_t, x[b]), acc[e], false);
+                            }
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < G / 2; ++k) {
+                        acc_t v[R];
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            v[r] = element<TI>(q[r], k);
+                            if constexpr (DELTA) v[r] -= element<TI>(q[R], k);
+                            v[r] = live ? v[r] : static_cast<acc_t>(0);
+                        }
+#pragma unroll
+                        for (int e = 0; e < NA; ++e)
+                            if (sweep * NA + e < NP) {
+                                const int a = kEntries<R>.row[sweep * NA + e], b = kEntries<R>.col[sweep * NA + e];
+                                acc[e] = fma_t(v[a], v[b], acc[e]);
+                            }
+                    }
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < SV; ++i)
+                if (i * kThreads < s.ng) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        unsigned int q[RL][2];
+#pragma unroll
+                        for (int r = 0; r < RL; ++r) {
+                            q[r][0] = raw[i][r].w[2 * h];
+                            q[r][1] = raw[i][r].w[2 * h + 1];
+                        }
+                        multiply(q, i * kThreads + tid < s.ng);
+                    }
+                }
+            if constexpr (SL > 0) {
+                // what this wave sent to LDS is there (a lane reads only what it loaded itself)
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int i = 0; i < SL; ++i)
+                    if ((SV + i) * kThreads < s.ng) {
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            unsigned int q[RL][2];
+#pragma unroll
+                            for (int r = 0; r < RL; ++r) {
+                                const u32x2 v = *reinterpret_cast<const u32x2*>(keep(i, r) + lane * 16 + 8 * h);
+                                q[r][0] = v.x;
+                                q[r][1] = v.y;
+                            }
+                            multiply(q, (SV + i) * kThreads + tid < s.ng);
+                        }
+                    }
+            }
+            wave_sum_scatter(acc, lane);
+#pragma unroll
+            for (int i = 0; i < (NA + 63) / 64; ++i) {
+                const int e = lane + 64 * i;
+                if (e < NA && sweep * NA + e < NP) shP[wave * NP + sweep * NA + e] = static_cast<double>(acc[i]);
+            }
+        }
+        __syncthreads();
+        if (tid < NP) {
+            double tot = shP[tid];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) tot += shP[w * NP + tid];
+            int a, b;
+            entry_to_ij<R, true>(tid, a, b);
+            for (int k = 0; k < nedge; ++k) tot += shEdge[a][k] * shEdge[b][k];
+            if (W > 1) send(st.partials + (static_cast<long long>(t.unit) * NP + tid) * 2, tot, tag);
+            else shG[a * R + b] = shG[b * R + a] = tot;
+        }
+    } else {
+        if constexpr (SL > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+
+    if (W > 1) {
+        const long long deadline = static_cast<long long>(wall_clock64()) + kWaitTicks;
+        const int tb = t.layer_first, te = t.layer_end;
+        bool ok = true;
+        // the sum of entry e over the units u0, u0 + step, ... of the layer, a few loads in flight
+        auto sum_units = [&](int e, int u0, int step) {
+            constexpr int kAhead = 4;
+            double v = 0.0;
+            for (; u0 < te; u0 += step * kAhead) {
+                Words x[kAhead];
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) {
+                    const int u = u0 + step * k;
+                    x[k] = peek(st.partials + (static_cast<long long>(u < te ? u : te - 1) * NP + e) * 2);
+                }
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) {
+                    const int u = u0 + step * k;
+                    if (u < te) {
+                        // (in the second launch every sum is there, and the tag may have moved on already)
+                        if (!second) ok = await(st.partials + (static_cast<long long>(u) * NP + e) * 2, x[k], tag, deadline) && ok;
+                        v += value(x[k]);
+                    }
+                }
+            }
+            return v;
+        };
+        if (W <= kDirectUnits) {
+            const int row = tid / NP, e = tid % NP;
+            if (row < ROWS) shR[row * NP + e] = sum_units(e, tb + row, ROWS);
+            __syncthreads();
+            if (tid < NP) {
+                double tot = shR[tid];
+#pragma unroll
+                for (int k = 1; k < ROWS; ++k) tot += shR[k * NP + tid];
+                int a, b;
+                entry_to_ij<R, true>(tid, a, b);
+                shG[a * R + b] = shG[b * R + a] = tot;
+            }
+        } else {
+            unsigned long long* sums = st.sums + static_cast<long long>(t.layer) * (NP * 2);
+            const int e0 = second ? wave : (t.unit - tb) + W * wave, estep = second ? NW : W * NW;
+            for (int e = e0; e < NP; e += estep) {
+                const double v = wave_sum(sum_units(e, tb + lane, 64));
+                if (second) {
+                    int a, b;
+                    entry_to_ij<R, true>(e, a, b);
+                    if (lane == 0) shG[a * R + b] = shG[b * R + a] = v;
+                } else if (__ballot(!ok) == 0) {
+                    if (lane == 0) send(sums + 2 * e, v, tag);
+                }
+            }
+            if (!second && tid < NP) {
+                Words x = peek(sums + 2 * tid);
+                ok = await(sums + 2 * tid, x, tag, deadline) && ok;
+                int a, b;
+                entry_to_ij<R, true>(tid, a, b);
+                shG[a * R + b] = shG[b * R + a] = value(x);
+            }
+        }
+        if (!ok) shSkip = 1;
+    }
+    __syncthreads();
+    if (!second && shSkip) {
+        if (tid == 0) st.skipped[at] = 1;
+        return;
+    }
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);   // (the workgroup waits for these few instructions)
+        if (order == ADASUM_ORDER_LINEAR) wave_tree_weights<R>(shG, shW, leaves, order, lane);
+        else if ((R & (R - 1)) == 0 && leaves == R) wave_balanced_weights<R>(shG, shW, shQ, lane);
+        else wave_level_weights<R>(shG, shW, shQ, leaves, lane);
+        __builtin_amdgcn_s_setprio(0);
+    }
+    if (gram != nullptr && t.unit == t.layer_first)   // (for the statistics)
+        for (int i = tid; i < R * R; i += kThreads) gram[static_cast<long long>(t.layer) * (R * R) + i] = shG[i];
+    __syncthreads();
+
+    acc_t w[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) w[r] = static_cast<acc_t>(shW[r]);
+    acc_t nacc = 0;
+    auto combine = [&](const Granule<TI, G> (&q)[RL], int i) {
+        const int j = i * kThreads + tid;
+        if (j < s.ng) {
+            const long long idx = s.bs + static_cast<long long>(j) * G;
+            acc_t z[G];
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                acc_t sv = 0;
+                if constexpr (DELTA) sv = element<TI>(q[R].w, k);
+                z[k] = w[0] * (DELTA ? element<TI>(q[0].w, k) - sv : element<TI>(q[0].w, k));
+#pragma unroll
+                for (int r = 1; r < R; ++r)
+                    z[k] = fma_t(w[r], DELTA ? element<TI>(q[r].w, k) - sv : element<TI>(q[r].w, k), z[k]);
+                nacc = fma_t(z[k], z[k], nacc);
+                if constexpr (DELTA) z[k] += sv;
+            }
+            store_granule<NTS>(out + idx, z);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < SV; ++i)
+        if (i * kThreads < s.ng) combine(raw[i], i);
+    if constexpr (SL > 0) {
+#pragma unroll
+        for (int i = 0; i < SL; ++i)
+            if ((SV + i) * kThreads < s.ng) {
+                Granule<TI, G> q[RL];
+#pragma unroll
+                for (int r = 0; r < RL; ++r) {
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(keep(i, r) + lane * 16);
+                    q[r].w[0] = v.x;
+                    q[r].w[1] = v.y;
+                    q[r].w[2] = v.z;
+                    q[r].w[3] = v.w;
+                }
+                combine(q, SV + i);
+            }
+    }
+    // ragged head/tail elements: fp64 arithmetic, one rounding at the store
+    double enorm = 0.0;
+    if (nedge > 0 && wave == 0) {
+        if (lane < nedge) {
+            double sd = 0.0;
+            if constexpr (DELTA) sd = static_cast<double>(load_elem(start + eidx));
+            double z = shW[0] * (static_cast<double>(load_elem(operand(0) + eidx)) - sd);
+#pragma unroll
+            for (int r = 1; r < R; ++r)
+                z = __builtin_fma(shW[r], static_cast<double>(load_elem(operand(r) + eidx)) - sd, z);
+            const out_acc_t zs = static_cast<out_acc_t>(z);
+            enorm = static_cast<double>(zs) * static_cast<double>(zs);
+            if constexpr (DELTA) z += sd;
+            store_elem(out + eidx, static_cast<out_acc_t>(z));
+        }
+        if (normparts != nullptr) enorm = wave_sum(enorm);
+    }
+    if (normparts != nullptr) {
+        const acc_t ws = wave_sum(nacc);
+        if (lane == 0) shNorm[wave] = static_cast<double>(ws);
+        __syncthreads();
+        if (tid == 0) {
+            double tot = shNorm[0];
+#pragma unroll
+            for (int k = 1; k < NW; ++k) tot += shNorm[k];
+            if (nedge > 0) tot += enorm;
+            normparts[t.unit] = tot;
+        }
+    }
+    if (second) __syncthreads();
+    } while (second && todo != 0);
+}
+
+template <typename TI, typename TO, int R, bool DELTA, int SV, int SL, int WPS>
+int launch_s(const ResidentCall& c, hipStream_t stream) {
+    for (int second = 0; second < 2; ++second) {
+        const int blocks = second ? (c.n_units + kSkipScan - 1) / kSkipScan : c.n_units;
+        hipLaunchKernelGGL((resident_kernel<TI, TO, R, DELTA, SV, SL, WPS>), dim3(static_cast<unsigned>(blocks)),
+                           dim3(kThreads), 0, stream, c.ops, static_cast<TO*>(c.out), c.units, c.n_units, c.state, second,
+                           c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return static_cast<int>(e);
+    }
+    return 0;
+}
+
+template <typename TI, typename TO, int R, bool DELTA>
+int launch_r(const ResidentCall& c, hipStream_t stream) {
+    constexpr int D = DtypeOf<TI>::value;
+    switch (c.form) {
+        case 1: return launch_s<TI, TO, R, DELTA, 1, 0, 2>(c, stream);
+        case 2:
+            if constexpr (R > 8) return static_cast<int>(hipErrorInvalidValue);
+            else return launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 2), resident_lds_steps(R, DELTA, 2), 3>(c, stream);
+        case 3: return launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 3), resident_lds_steps(R, DELTA, 3), 2>(c, stream);
+        default: return static_cast<int>(hipErrorInvalidValue);
+    }
+}
+
+template <typename TI, typename TO, bool DELTA>
+int launch_t(const ResidentCall& c, hipStream_t stream) {
+#define ADASUM_RESIDENT(RR) \
+    case RR: return launch_r<TI, TO, RR, DELTA>(c, stream)
+    switch (c.R) {
+#if ADASUM_WIDE_GROUPS
+        ADASUM_RESIDENT(10);
+        ADASUM_RESIDENT(12);
+        ADASUM_RESIDENT(14);
+        ADASUM_RESIDENT(16);
+#else
+        ADASUM_RESIDENT(2);
+        ADASUM_RESIDENT(3);
+        ADASUM_RESIDENT(4);
+        ADASUM_RESIDENT(5);
+        ADASUM_RESIDENT(6);
+        ADASUM_RESIDENT(7);
+        ADASUM_RESIDENT(8);
+#endif
+        default: return static_cast<int>(hipErrorInvalidValue);
+    }
+#undef ADASUM_RESIDENT
+}
+
+}  // namespace
+
+// This file is compiled once per storage type of the operands (ADASUM_LEAF_TYPE) and range of group sizes
+// (ADASUM_WIDE_GROUPS: 10 .. 16 operands, else 2 .. 8).
+#if ADASUM_LEAF_TYPE == 0
+typedef float leaf_t;
+#define ADASUM_ENTRY_NAME(x) x##_f32
+#elif ADASUM_LEAF_TYPE == 1
+typedef bf16_t leaf_t;
+#define ADASUM_ENTRY_NAME(x) x##_bf16
+#elif ADASUM_LEAF_TYPE == 2
+typedef f16_t leaf_t;
+#define ADASUM_ENTRY_NAME(x) x##_f16
+#else
+typedef double leaf_t;
+#define ADASUM_ENTRY_NAME(x) x##_f64
+#endif
+#if ADASUM_WIDE_GROUPS
+int ADASUM_ENTRY_NAME(launch_resident_wide)(const ResidentCall& c, void* stream) {
+#else
+int ADASUM_ENTRY_NAME(launch_resident)(const ResidentCall& c, void* stream) {
+#endif
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    constexpr int D = DtypeOf<leaf_t>::value;
+    if (c.n_units < 1) return static_cast<int>(hipErrorInvalidConfiguration);
+#if !ADASUM_WIDE_GROUPS
+    if (c.start != nullptr) return c.out_dtype == D ? launch_t<leaf_t, leaf_t, true>(c, s) : static_cast<int>(hipErrorInvalidValue);
+#else
+    if (c.start != nullptr) return static_cast<int>(hipErrorInvalidValue);
+#endif
+    if (c.out_dtype == D) return launch_t<leaf_t, leaf_t, false>(c, s);
+#if ADASUM_LEAF_TYPE == 1 || ADASUM_LEAF_TYPE == 2
+    if (c.out_dtype == ADASUM_F32) return launch_t<leaf_t, float, false>(c, s);
+#elif ADASUM_LEAF_TYPE == 0
+    if (c.out_dtype == ADASUM_BF16) return launch_t<float, bf16_t, false>(c, s);
+    if (c.out_dtype == ADASUM_F16) return launch_t<float, f16_t, false>(c, s);
+#endif
+    return static_cast<int>(hipErrorInvalidValue);
+}
+
+}  // namespace adasum
