@@ -20,8 +20,9 @@ LIB_PATH = os.path.join(HERE, "libadasum.so")
 # a measuring tool (the memory system's ceiling for the combine pass's access pattern)
 CEILING_PATH = os.path.join(HERE, "pattern_ceiling")
 
-# (source, defines): the resident kernels are compiled once per storage type of the gradients
-SOURCES = [("adasum_resident.hip", [f"-DADASUM_LEAF_TYPE={t}"]) for t in (0, 1, 2, 3)] + [
+# (source, defines): the resident kernels are compiled once per storage type of the gradients and range of worker counts
+SOURCES = [("adasum_resident.hip", [f"-DADASUM_LEAF_TYPE={t}", f"-DADASUM_WIDE_GROUPS={w}"])
+           for t, w in ((0, 0), (1, 0), (2, 0), (3, 0), (0, 1), (1, 1), (2, 1))] + [
     ("adasum_kernels.hip", []), ("adasum_api.cpp", []), ("adasum_plan.cpp", [])]
 
 # -packed-fp32-ops off: the compiler must not form packed fp32 instructions.

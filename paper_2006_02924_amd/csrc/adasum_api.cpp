@@ -616,9 +616,10 @@ int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* o
     char namebuf[48];
     kernel_name("resident", dtype, o.out_dtype, c.R, false, namebuf, sizeof(namebuf));
     const double bytes = static_cast<double>(lay.N) * ((K + (o.delta_start ? 1 : 0)) * elem_bytes(dtype) + elem_bytes(o.out_dtype));
-    auto* launch = dtype == ADASUM_F32    ? launch_resident_f32
-                   : dtype == ADASUM_BF16 ? launch_resident_bf16
-                   : dtype == ADASUM_F16  ? launch_resident_f16
+    const bool wide = c.R > 8;
+    auto* launch = dtype == ADASUM_F32    ? (wide ? launch_resident_wide_f32 : launch_resident_f32)
+                   : dtype == ADASUM_BF16 ? (wide ? launch_resident_wide_bf16 : launch_resident_bf16)
+                   : dtype == ADASUM_F16  ? (wide ? launch_resident_wide_f16 : launch_resident_f16)
                                           : launch_resident_f64;
     ADASUM_TIMED(namebuf, bytes, stream, launch(c, stream));
     if (o.layer_stats != nullptr)

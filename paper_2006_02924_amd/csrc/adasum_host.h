@@ -269,25 +269,28 @@ struct TileSet {
 // Form 2: three workgroups per compute unit; form 3: two, which keep more.  Smaller units overlap better (K = 2 bf16,
 // ResNet-50 sizes: 40 us in form 2, 62 in form 3; K = 6 binary16: 115 and 121), but a layer that takes most of the chip
 // stalls it (K = 8 fp32, whose largest layers have 75 of 84 MB: 260 us in form 2, 217 in form 3): form 2 while the
-// largest layer takes at most half of its workgroups.  Groups of more than 8 operands have forms 1 and 3 (one step of
-// 16 operands is 64 KB).
-constexpr int kResidentRadix = 8;        // operands at most
+// largest layer takes at most half of its workgroups.  More than 8 operands have forms 1 and 3 only (one step of 16
+// operands is 64 KB), and an even number: an odd one repeats an operand with weight 0.
+constexpr int kResidentRadix = 16;       // operands at most
 constexpr int kResidentCus = 256;        // compute units the figures are for; not used on fewer
 constexpr int kDirectUnits = 16;         // units of a layer up to which every workgroup reads all partial sums
 constexpr int resident_slots(int form) { return form == 3 ? 2 * kResidentCus : 3 * kResidentCus; }
 // units of a layer at most: its workgroups must be on the chip together
 constexpr int resident_most(int form) { return form == 3 ? resident_slots(3) - 12 : resident_slots(form) / 2; }
 constexpr int resident_register_steps(int dtype, int R, bool delta, int form) {
-    const int rows = form == 2 ? 24 : (dtype == ADASUM_F64 || R > 8 ? 32 : 40);
+    // (16-bit operands, more than 8: the Gram matrix takes few registers and the LDS)
+    const bool matrix = R > 8 && (dtype == ADASUM_BF16 || dtype == ADASUM_F16);
+    const int rows = form == 2 ? 24 : matrix ? 48 : dtype == ADASUM_F64 || R > 8 ? 32 : 40;
     const int steps = rows / (R + (delta ? 1 : 0));
     return steps < 16 ? (steps < 1 ? 1 : steps) : 16;
 }
-constexpr int resident_lds_steps(int R, bool delta, int form) {
+constexpr int resident_lds_steps(int dtype, int R, bool delta, int form) {
+    if (R > 8 && (dtype == ADASUM_BF16 || dtype == ADASUM_F16)) return 0;
     const int steps = (form == 2 ? 12 : 18) / (R + (delta ? 1 : 0));
     return steps < 8 ? steps : 8;
 }
 constexpr int resident_capacity(int dtype, int R, bool delta, int form) {
-    const int steps = form == 1 ? 1 : resident_register_steps(dtype, R, delta, form) + resident_lds_steps(R, delta, form);
+    const int steps = form == 1 ? 1 : resident_register_steps(dtype, R, delta, form) + resident_lds_steps(dtype, R, delta, form);
     return kThreads * steps * (dtype == ADASUM_F64 ? 2 : dtype == ADASUM_F32 ? 4 : 8);
 }
 // Operands a resident kernel is instantiated for that holds a group of `leaves`.

@@ -253,6 +253,7 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
     ResidentPlan p;
     if (radices.size() != 1 || K < 2 || K > kResidentRadix || layer_offsets[n_layers] == 0) return p;
     p.R = resident_operands(K);
+    if (p.R > 8 && (delta || dtype == ADASUM_F64)) return p;
     auto fits = [&](int form) {
         const int64_t cap = resident_capacity(dtype, p.R, delta, form);
         int64_t most = 0, all = 0;
@@ -268,7 +269,7 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
         p.n_units = all;
         return true;
     };
-    if (!fits(1) && !fits(2)) fits(3);
+    if (!fits(1) && !(p.R <= 8 && fits(2))) fits(3);
     return p;
 }
 

@@ -11,8 +11,8 @@
 // layer's slowest unit), the scalars (1 us) and its stores.  So the pass is bound by how much is kept over how long:
 // hence as much as the register file takes per unit, LDS filled straight from memory beside it, an exchange without
 // atomics, flags or fences (a fence of agent scope cost 1.4 x the whole pass), and launch order (order_units).
-// Measured against the three kernels, us per reduction: ResNet-50 sizes, K = 8 fp32 298 -> 217, K = 2 bf16 51 -> 40,
-// K = 6 binary16 152 -> 115.
+// Measured against the three kernels, us per reduction: ResNet-50 sizes, K = 8 fp32 298 -> 215, K = 2 bf16 51 -> 36,
+// K = 6 binary16 152 -> 109, K = 16 bf16 with statistics 316 -> 276; 400 odd tensors, K = 12 bf16, 182 -> 102.
 #include <hip/hip_runtime.h>
 
 #include "adasum_host.h"
@@ -55,6 +55,21 @@ struct Entries {
     }
 };
 template <int R> constexpr Entries<R> kEntries{};
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+// X X^T of 16 rows of 32 elements, added to c
+template <typename T>
+__device__ __forceinline__ f32x4_t mfma_square(const u32x4& x, const f32x4_t& c) {
+    if constexpr (std::is_same<T, bf16_t>::value) {
+        const bf16x8_t v = __builtin_bit_cast(bf16x8_t, x);
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, v, c, 0, 0, 0);
+    } else {
+        const f16x8_t v = __builtin_bit_cast(f16x8_t, x);
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(v, v, c, 0, 0, 0);
+    }
+}
 
 // ---- values that one workgroup of a launch writes and others read ----
 // A double travels as two 8-byte words, each with half of its bits and the call's tag: a reader knows from the word
@@ -124,14 +139,14 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     // entries accumulated side by side: more than some 60 do not fit beside what is kept, and take more sweeps over it
     constexpr int SWEEPS = (NP + 59) / 60;
     constexpr int NA = (NP + SWEEPS - 1) / SWEEPS;
-    // 16-bit products through the packed dot instruction, as gram_kernel: only where the vector units would bind
-    constexpr bool DOT2 = sizeof(TI) == 2 && R > 8;
+    // more than 8 operands of a 16-bit type: the Gram matrix on the matrix cores (gram_step below)
+    constexpr bool MFMA = sizeof(TI) == 2 && R > 8;
     typedef typename Traits<TI>::acc_t acc_t;
     typedef typename Traits<TO>::acc_t out_acc_t;
     constexpr bool NTS = !(sizeof(TI) == 2 && sizeof(TO) == 4 && R <= 2);   // as combine_kernel
-    static_assert(ROWS >= 1 && SV >= 1 && R <= 16, "");
+    static_assert(ROWS >= 1 && SV >= 1 && R <= 16 && !(MFMA && SL > 0), "");
 
-    __shared__ double shP[NW * NP];
+    __shared__ double shP[NW * (MFMA ? 256 : NP)];
     __shared__ double shR[ROWS * NP];
     __shared__ double shEdge[R][kEdge > 0 ? kEdge : 1];
     __shared__ double shG[R * R];
@@ -139,6 +154,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     __shared__ double shQ[4 * R];
     __shared__ double shNorm[NW];
     __shared__ int shSkip;
+    __shared__ __align__(16) unsigned char shStage[MFMA ? NW * 16 * 1024 : 16];
     __shared__ __align__(16) unsigned char shKeep[SL > 0 ? SL * RL * kThreads * 16 : 16];
 
     int tid = threadIdx.x, lane = tid & 63;
@@ -218,32 +234,58 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
 #pragma unroll
             for (int r = 0; r < R; ++r) shEdge[r][lane] = static_cast<double>(load_elem(operand(r) + eidx)) - sd;
         }
+        if constexpr (MFMA) {
+            // G = X X^T with v_mfma_f32_16x16x32: per lane, eight consecutive elements (a granule) of row lane % 16, for
+            // either operand.  What is kept has a row's granules along the lanes, so a step goes through LDS (a wave's own
+            // 16 KB, no barrier): granule c of row r lies at place c ^ r, conflict-free both ways.  Four accumulators
+            // where the vector units would need R (R + 1) / 2: 136 of them took three sweeps over what is kept (K = 16 bf16
+            // on a sixteenth of ResNet-50: 82 us with spills, 30 this way).  The products are exact; four instructions in a row accumulate 128 of them, the rest are ordinary fp32 additions.
+            unsigned char* stage = shStage + wave * (16 * 1024);
+            const int m = lane & 15, kg = lane >> 4;
+            float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = R; r < 16; ++r) *reinterpret_cast<u32x4*>(stage + r * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int i = 0; i < SV; ++i)
+                if (i * kThreads < s.ng) {
+                    const bool live = i * kThreads + tid < s.ng;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        u32x4 v;
+                        v.x = live ? raw[i][r].w[0] : 0u;
+                        v.y = live ? raw[i][r].w[1] : 0u;
+                        v.z = live ? raw[i][r].w[2] : 0u;
+                        v.w = live ? raw[i][r].w[3] : 0u;
+                        *reinterpret_cast<u32x4*>(stage + r * 1024 + (lane ^ r) * 16) = v;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int b0 = 0; b0 < 16; b0 += 4) {
+                        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int b = b0; b < b0 + 4; ++b) {
+                            const u32x4 x = *reinterpret_cast<const u32x4*>(stage + m * 1024 + ((4 * b + kg) ^ m) * 16);
+                            acc = mfma_square<TI>(x, acc);
+                        }
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sum[v] += acc[v];
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
+            // (accumulator v of a lane: row 4 (lane / 16) + v, column lane % 16)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) shP[wave * 256 + (4 * kg + v) * 16 + m] = static_cast<double>(sum[v]);
+        } else {
 #pragma unroll
         for (int sweep = 0; sweep < SWEEPS; ++sweep) {
+            // (opaque: what a sweep derives from the kept operands is derived again by the next, not held in registers)
+            int n_live = s.ng;
+            asm volatile("" : "+s"(n_live)::"memory");
             acc_t acc[NA];
 #pragma unroll
             for (int e = 0; e < NA; ++e) acc[e] = 0;
             // eight bytes of every row
             auto multiply = [&](const unsigned int (&q)[RL][2], bool live) {
-                if constexpr (DOT2) {
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        unsigned int x[R];
-#pragma unroll
-                        for (int r = 0; r < R; ++r) x[r] = live ? q[r][k] : 0u;
-#pragma unroll
-                        for (int e = 0; e < NA; ++e)
-                            if (sweep * NA + e < NP) {
-                                const int a = kEntries<R>.row[sweep * NA + e], b = kEntries<R>.col[sweep * NA + e];
-                                if constexpr (std::is_same<TI, bf16_t>::value)
-                                    acc[e] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, x[a]),
-                                                                             __builtin_bit_cast(bf16x2_t, x[b]), acc[e], false);
-                                else
-                                    acc[e] = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, x[a]),
-                                                                    __builtin_bit_cast(f16x2_t, x[b]), acc[e], false);
-                            }
-                    }
-                } else {
 #pragma unroll
                     for (int k = 0; k < G / 2; ++k) {
                         acc_t v[R];
@@ -260,7 +302,6 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
                                 acc[e] = fma_t(v[a], v[b], acc[e]);
                             }
                     }
-                }
             };
 #pragma unroll
             for (int i = 0; i < SV; ++i)
@@ -273,7 +314,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
                             q[r][0] = raw[i][r].w[2 * h];
                             q[r][1] = raw[i][r].w[2 * h + 1];
                         }
-                        multiply(q, i * kThreads + tid < s.ng);
+                        multiply(q, i * kThreads + tid < n_live);
                     }
                 }
             if constexpr (SL > 0) {
@@ -291,7 +332,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
                                 q[r][0] = v.x;
                                 q[r][1] = v.y;
                             }
-                            multiply(q, (SV + i) * kThreads + tid < s.ng);
+                            multiply(q, (SV + i) * kThreads + tid < n_live);
                         }
                     }
             }
@@ -302,13 +343,15 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
                 if (e < NA && sweep * NA + e < NP) shP[wave * NP + sweep * NA + e] = static_cast<double>(acc[i]);
             }
         }
+        }
         __syncthreads();
         if (tid < NP) {
-            double tot = shP[tid];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) tot += shP[w * NP + tid];
             int a, b;
             entry_to_ij<R, true>(tid, a, b);
+            const int cell = MFMA ? a * 16 + b : tid;
+            double tot = shP[cell];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) tot += shP[w * (MFMA ? 256 : NP) + cell];
             for (int k = 0; k < nedge; ++k) tot += shEdge[a][k] * shEdge[b][k];
             if (W > 1) send(st.partials + (static_cast<long long>(t.unit) * NP + tid) * 2, tot, tag);
             else shG[a * R + b] = shG[b * R + a] = tot;
@@ -324,7 +367,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
         bool ok = true;
         // the sum of entry e over the units u0, u0 + step, ... of the layer, a few loads in flight
         auto sum_units = [&](int e, int u0, int step) {
-            constexpr int kAhead = 4;
+            constexpr int kAhead = R > 8 ? 8 : 4;
             double v = 0.0;
             for (; u0 < te; u0 += step * kAhead) {
                 Words x[kAhead];
@@ -491,8 +534,8 @@ int launch_r(const ResidentCall& c, hipStream_t stream) {
         case 1: return launch_s<TI, TO, R, DELTA, 1, 0, 2>(c, stream);
         case 2:
             if constexpr (R > 8) return static_cast<int>(hipErrorInvalidValue);
-            else return launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 2), resident_lds_steps(R, DELTA, 2), 3>(c, stream);
-        case 3: return launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 3), resident_lds_steps(R, DELTA, 3), 2>(c, stream);
+            else return launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 2), resident_lds_steps(D, R, DELTA, 2), 3>(c, stream);
+        case 3: return launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 3), resident_lds_steps(D, R, DELTA, 3), 2>(c, stream);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }

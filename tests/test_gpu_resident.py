@@ -19,8 +19,11 @@ def unit_elements(K, dtype, form, delta=False):
     rows = K + (1 if delta else 0)
     if form == 1:
         return LANES * vec
-    registers = {2: 24, 3: 32 if dtype == torch.float64 else 40}[form]
-    steps = max(1, min(16, registers // rows)) + min(8, {2: 12, 3: 18}[form] // rows)
+    if K > 8:
+        rows = (K + 1) // 2 * 2
+    matrix = K > 8 and vec == 8
+    registers = {2: 24, 3: 48 if matrix else 32 if dtype == torch.float64 or K > 8 else 40}[form]
+    steps = max(1, min(16, registers // rows)) + (0 if matrix else min(8, {2: 12, 3: 18}[form] // rows))
     return LANES * vec * steps
 
 
@@ -40,7 +43,11 @@ def edges(u, vec):
 
 CASES = [(K, dtype, form) for form in (1, 2, 3) for K, dtype in (
     (2, torch.bfloat16), (3, torch.float32), (4, torch.float64), (5, torch.float16), (6, torch.bfloat16),
-    (7, torch.float32), (8, torch.float32), (8, torch.bfloat16), (8, torch.float64))]
+    (7, torch.float32), (8, torch.float32), (8, torch.bfloat16), (8, torch.float64))] + [
+    # more than 8 operands have no form 2; 16-bit ones on the matrix cores, odd counts filled up
+    (K, dtype, form) for form in (1, 3) for K, dtype in (
+        (9, torch.bfloat16), (12, torch.bfloat16), (14, torch.float16), (16, torch.bfloat16), (11, torch.float32),
+        (16, torch.float32))]
 
 
 @pytest.mark.parametrize("K,dtype,form", CASES)
@@ -50,8 +57,10 @@ def test_unit_edges_against_the_oracle(K, dtype, form):
     sizes = edges(u, vec)
     if form == 2:      # more units of one step than the chip holds at once
         sizes.append(max(0, 769 * unit_elements(K, dtype, 1) - sum(sizes)) + 7)
-    elif form == 3:    # a layer of more than half the units of form 2
+    elif form == 3 and K <= 8:    # a layer of more than half the units of form 2
         sizes.append(385 * unit_elements(K, dtype, 2) + 3)
+    elif form == 3:
+        sizes.append(max(0, 769 * unit_elements(K, dtype, 1) - sum(sizes)) + 7)
     print(f"resident K={K} {dtype} form {form}: unit {u}, N={sum(sizes)}", flush=True)
     w = workload(sizes, K, dtype, 40 + K)
     wide = torch.float64 if dtype == torch.float64 else torch.float32
