@@ -14,6 +14,11 @@
  *     head/tail elements of a layer) is summed in fp64; the operator's scalars
  *     are computed in fp64 (Section 4.4.1 asks for double accumulation).  fp64
  *     inputs are reduced in fp64 throughout;
+ *   - up to 16 workers whose layers fit on the chip are reduced in one resident pass:
+ *     a piece of a layer stays in a workgroup's registers and LDS while the layer's
+ *     scalars are worked out, so every input is read once.  Workgroups of a layer wait
+ *     for each other, at most 100 us; what that leaves undone (when other kernels hold
+ *     much of the chip) a second launch does from memory, with the same result;
  *   - layers of at most 16 elements are reduced by the definition itself, pair by
  *     pair in fp64 over all K workers with nothing stored in between: vectors that
  *     short can nearly cancel at a tree node, where stored fp32 nodes lose digits.
@@ -23,8 +28,7 @@
  * Supported magnitudes.  Products of two stored values are formed and summed in fp32
  * lanes (fp64 for fp64 storage), so for fp32 and bf16 storage a layer's values must
  * keep their squares inside the fp32 range: root-mean-square magnitude of a layer
- * between about 1e-17 and 1e+17 (checked against the oracle at 1e-15 and 1e+15; a first
- * pass of radix 32 or 64 sums up to 2^18 products in fp32 before it widens them: 1e+16).
+ * between about 1e-17 and 1e+17 (checked against the oracle at 1e-15 and 1e+15).
  * fp16 storage cannot leave that range; fp64 storage has fp64's (1e-150 .. 1e+150).
  * Outside it the result of THAT layer is not the operator's: squares that underflow
  * to zero put the layer on (or near) the zero-norm convention, a plain sum of the
@@ -50,7 +54,7 @@
  *     No ordering is inserted on a stream that is being captured into a graph:
  *     what a caller captures, it orders.
  *   - results are deterministic: identical inputs give bit-identical outputs
- *     (no atomics anywhere on the path).
+ *     (sums in fixed orders, no atomic additions).
  */
 #ifndef ADASUM_H
 #define ADASUM_H
@@ -109,7 +113,10 @@ typedef struct adasum_options {
                                   matrix cores (exact 16-bit products, summed in fp32 within a
                                   workgroup's span of a layer, fp64 above); K = 64 is then a single
                                   pass.  Later passes, over fp32 nodes, stay at 16 or less;
-                                  0 = library default (16; 8 for fp64 and the delta form).
+                                  0 = library default: 16; 8 for fp64 and the delta form; for bf16
+                                  and fp16 inputs of more than 16 workers in the tree order 32 or,
+                                  from 33 workers and 4 million elements on, 64 (16 still where
+                                  only that fits ADASUM_NOALLOC_SCRATCH_BYTES).
                                   The result is the same binary tree. */
     int32_t  order;            /* ADASUM_ORDER_TREE (default) | ADASUM_ORDER_LINEAR */
     int32_t  use_graph;        /* 1 = replay the level ladder as one hipGraph launch: captured
@@ -239,7 +246,8 @@ ADASUM_API int adasum_plan_destroy(adasum_plan* plan);
  *   opts   as for adasum_reduce_ex, except workspace must be NULL and use_graph 0
  *          (ADASUM_ERR_INVALID_ARG otherwise); NULL = all defaults
  * Limit: tables + workspace of the problem (about adasum_workspace_bytes() plus 16 bytes per
- * 256 to 512 elements) must fit the array, else ADASUM_ERR_TOO_LARGE and nothing is enqueued.  That
+ * 256 to 512 elements; with radix 0 those of the radix-16 schedule, also where a wider one is
+ * the default) must fit the array, else ADASUM_ERR_TOO_LARGE and nothing is enqueued.  That
  * holds for e.g. ResNet-50 (25.6 M elements) at K <= 16, or 3 M elements at K = 64 -- and, since a
  * single pass keeps no intermediate nodes, for BERT-Large (335 M elements) at K <= 64 with radix 64.
  * Every call on one GPU uses the same array and finds the previous call's contents there:

@@ -113,11 +113,97 @@ int read_opts(const adasum_options* o, int dtype, Opts& r) {
     return ADASUM_OK;
 }
 
-// The delta form's Gram pass subtracts before it multiplies and so cannot use the packed
-// dot instructions; with 16 operands it runs out of registers, 8 is its fastest radix.
-// fp64 accumulators are twice as wide: 8 as well.
-int default_radix(const Opts& o) {
-    return (o.delta_start != nullptr || o.dtype == ADASUM_F64) ? 8 : kDefaultRadix;
+// Capacity of the combine tile table pass lv uses, reading operands of type `dtype`: a pass that feeds
+// the next one works with one wave per group whatever its radix.
+int table_capacity(bool feed, const std::vector<int>& radices, size_t lv, int dtype) {
+    return feed && pass_feeds_next(radices, lv) ? feed_tile_capacity(dtype, radices[lv])
+                                                : combine_tile_capacity(dtype, radices[lv]);
+}
+
+// Workspace layout of a problem with a radix (spans: of a wide first pass).
+Layout problem_layout(int K, const std::vector<int>& radices, int order, int dtype, bool delta, bool fuse, bool separate,
+                      const int64_t* offsets, int L) {
+    const int node_type = node_dtype(dtype);
+    const int Kv = order == ADASUM_ORDER_LINEAR ? K : virtual_leaves(radices);
+    int64_t small_elems = 0;
+    for (int l = 0; l < L && K > 1; ++l) {
+        const int64_t len = offsets[l + 1] - offsets[l];
+        if (len >= 1 && len <= kSmallLayer) small_elems += len;
+    }
+    return make_layout(Kv, offsets[L], L, count_tiles(offsets, L, gram_tile_capacity(offsets, L)),
+                       norm_entries_bound(Kv, offsets, L, radices, node_type), radices, order, K + 1, small_elems, node_type,
+                       fuse ? dot_entries_bound(Kv, offsets, L, radices, node_type)
+                       : (order == ADASUM_ORDER_TREE && !separate && !delta) ? next_entries_bound(Kv, offsets, L, radices, node_type)
+                                                                             : 0,
+                       !radices.empty() && wide_radix(radices[0]) ? count_spans(offsets, L, wide_part_count(offsets[L])) : 0);
+}
+
+// What adasum_reduce_noalloc takes of its scratch for a tree schedule: tables and workspace (the pieces in its order).
+size_t scratch_bytes(int K, const std::vector<int>& radices, int dtype, bool separate, const Layout& lay,
+                     const int64_t* offsets, int L) {
+    size_t off = 0;
+    auto take = [&](size_t bytes) { off = align_up(off, 256) + bytes; };
+    const size_t per_layer = sizeof(int32_t) * (static_cast<size_t>(L) + 1);
+    const int gcap = gram_tile_capacity(offsets, L);
+    const int64_t n_gram = count_tiles(offsets, L, gcap);
+    take(2 * per_layer);
+    take(sizeof(adasum_tile) * static_cast<size_t>(n_gram));
+    take(per_layer);
+    std::vector<int> caps;
+    for (size_t lv = 0; lv < radices.size(); ++lv) {
+        const int cap = table_capacity(!separate, radices, lv, lv == 0 ? dtype : node_dtype(dtype));
+        if (std::find(caps.begin(), caps.end(), cap) != caps.end()) continue;
+        caps.push_back(cap);
+        take(sizeof(adasum_tile) * static_cast<size_t>(count_tiles(offsets, L, cap)));
+        take(per_layer);
+        take(sizeof(int32_t) * (static_cast<size_t>(n_gram) + 1));
+    }
+    int64_t n_small = 0;
+    for (int l = 0; l < L; ++l) {
+        const int64_t len = offsets[l + 1] - offsets[l];
+        n_small += len >= 1 && len <= kSmallLayer;
+    }
+    take(sizeof(SmallLayer) * static_cast<size_t>(n_small));
+    if (wide_radix(radices[0])) {
+        const int parts = wide_part_count(offsets[L]);
+        take(sizeof(adasum_tile) * static_cast<size_t>(count_spans(offsets, L, parts)));
+        take(sizeof(int64_t) * ((static_cast<size_t>(L) + 2) / 2));
+        take(sizeof(int64_t) * ((static_cast<size_t>(parts) + 2) / 2));
+    }
+    take(lay.base_total);
+    return off;
+}
+
+// The radix of a problem that names none.
+//  - The delta form's Gram pass subtracts before it multiplies and so cannot use the packed dot instructions; with 16
+//    operands it runs out of registers, 8 is its fastest radix.  fp64 accumulators are twice as wide: 8 as well.
+//  - 16-bit gradients of more than 16 workers in tree order: a wide first pass, which stores no or fewer nodes and has its
+//    Gram matrix from the matrix cores.  Measured against [16, ...], us: BERT-Large sizes K = 64 16070 -> 13900, a quarter
+//    of them K = 32 2080 -> 1756, ResNet-50 sizes K = 24 537 -> 435, a 64th of them K = 32 138 -> 111.  Beyond 32 workers
+//    one pass of 64 (with 64 rows and a 64 x 64 walk for every layer) pays from some 4 million elements on: K = 64,
+//    5.2 M elements 391 -> 370 with [64] for [32, 2], 1.6 M 225 -> 246.
+//  - adasum_reduce_noalloc takes what the radix-16 schedule's tables and workspace fit its scratch for, no more and no
+//    less, and gives the bits that the other entry points give: where that schedule fits and the wide one does not,
+//    it is the default of all of them.
+struct Replaced {
+    size_t workspace = 0, scratch = 0;   // what the radix-16 schedule needs where a wide pass takes its place
+};
+int default_radix(int K, int order, int dtype, bool delta, bool separate, const int64_t* offsets, int L, Replaced* by_wide) {
+    *by_wide = Replaced();
+    if (delta || dtype == ADASUM_F64) return 8;
+    if (K <= kMaxRadix || order != ADASUM_ORDER_TREE || (dtype != ADASUM_BF16 && dtype != ADASUM_F16)) return kDefaultRadix;
+    const int wide = K > 32 && offsets[L] >= kWideElements ? 64 : 32;
+    std::vector<int> r16, rw;
+    if (build_levels(K, kDefaultRadix, r16) != ADASUM_OK || build_levels(K, wide, rw) != ADASUM_OK) return kDefaultRadix;
+    const Layout l16 = problem_layout(K, r16, order, dtype, delta, false, separate, offsets, L);
+    const size_t s16 = scratch_bytes(K, r16, dtype, separate, l16, offsets, L);
+    if (s16 <= ADASUM_NOALLOC_SCRATCH_BYTES &&
+        scratch_bytes(K, rw, dtype, separate, problem_layout(K, rw, order, dtype, delta, false, separate, offsets, L), offsets, L) >
+            ADASUM_NOALLOC_SCRATCH_BYTES)
+        return kDefaultRadix;
+    by_wide->workspace = l16.base_total;
+    by_wide->scratch = s16;
+    return wide;
 }
 
 // ---- plans -------------------------------------------------------------------
@@ -286,13 +372,6 @@ std::mutex g_mutex;
 std::vector<std::unique_ptr<Plan>> g_plans;   // least recently used first
 constexpr size_t kMaxPlans = 64;
 
-// Capacity of the combine tile table pass lv uses, reading operands of type `dtype`: a pass that feeds
-// the next one works with one wave per group whatever its radix.
-int table_capacity(bool feed, const std::vector<int>& radices, size_t lv, int dtype) {
-    return feed && pass_feeds_next(radices, lv) ? feed_tile_capacity(dtype, radices[lv])
-                                                : combine_tile_capacity(dtype, radices[lv]);
-}
-
 // Takes the reduction as a resident pass, and lays out its section of the workspace, where the layer table suits one
 // and the device is one it is made for (the section is there all the same: adasum_workspace_bytes asks no device).
 int take_resident(Plan* p, int dtype, bool delta, const int64_t* offsets, int n_layers) {
@@ -309,9 +388,8 @@ int take_resident(Plan* p, int dtype, bool delta, const int64_t* offsets, int n_
 }
 
 // Builds a plan (host tables, their device copies; no workspace yet) on the current device.
-// `no_feed`: the delta form, the step plans and separate_passes: no pass feeds the next.
-// `whole`: the plan is for whole reductions that may be taken as a resident pass (not a step, not separate_passes).
-int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, bool no_feed, bool whole,
+// `radix` 0: the default's.  `whole`: the plan is for whole reductions, not for the steps of one.
+int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, bool separate, bool whole,
               const int64_t* offsets, int n_layers, std::unique_ptr<Plan>& out) {
     const int node_type = node_dtype(dtype);
     int device = 0;
@@ -322,10 +400,12 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
         p->device = device;
         p->K = K;
         p->radix = radix;
+        Replaced replaced;
+        if (radix == 0) radix = default_radix(K, order, dtype, delta, separate, offsets, n_layers, &replaced);
         p->order = order;
         p->node_type = node_type;
         p->fuse = fuse ? 1 : 0;
-        p->feed = (order == ADASUM_ORDER_TREE && !fuse && !no_feed) ? 1 : 0;
+        p->feed = (order == ADASUM_ORDER_TREE && !fuse && !delta && !separate && whole) ? 1 : 0;
         p->offsets.assign(offsets, offsets + n_layers + 1);
         p->gram_tiles.capacity = gram_tile_capacity(offsets, n_layers);
         build_tiles(offsets, n_layers, p->gram_tiles.capacity, p->gram_tiles.tiles, p->gram_tiles.layer_begin);
@@ -347,7 +427,9 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
                              : p->feed ? next_entries_bound(Kv, offsets, n_layers, p->radices, node_type)
                                        : 0,
                              static_cast<int64_t>(p->wide_spans.tiles.size()));
-        if (whole) {
+        p->lay.need = p->lay.total;
+        p->lay.total = std::max(p->lay.total, replaced.workspace);
+        if (whole && !separate) {
             const int rc = take_resident(p.get(), dtype, delta, offsets, n_layers);
             if (rc != ADASUM_OK) return rc;
             if (p->resident.form > 0)
@@ -411,8 +493,7 @@ int find_or_make_plan(int K, int radix, int order, int in_dtype, int out_dtype, 
     while (g_plans.size() >= kMaxPlans) g_plans.erase(g_plans.begin());
     std::unique_ptr<Plan> p;
     const int rc = make_plan(K, radix, order == kStepPlans ? ADASUM_ORDER_TREE : order, in_dtype, delta, fuse,
-                             delta || separate || order == kStepPlans, !separate && order != kStepPlans, offsets,
-                             n_layers, p);
+                             separate, order != kStepPlans, offsets, n_layers, p);
     if (rc != ADASUM_OK) return rc;
     p->order = order;
     p->in_dtype = in_dtype;
@@ -430,9 +511,9 @@ int plan_workspace(Plan* p, const Opts& o, char** ws) {
         *ws = static_cast<char*>(o.workspace);
         return ADASUM_OK;
     }
-    if (p->d_ws == nullptr && p->lay.total > 0) {
+    if (p->d_ws == nullptr && p->lay.need > 0) {
         char* mem = nullptr;
-        ADASUM_HIP(hipMalloc(reinterpret_cast<void**>(&mem), p->lay.total));
+        ADASUM_HIP(hipMalloc(reinterpret_cast<void**>(&mem), p->lay.need));
         if (p->resident.form > 0) {
             // the resident pass's section starts at zero; what a call leaves there carries that call's tag
             hipError_t e = hipErrorOutOfMemory;
@@ -1116,7 +1197,7 @@ int reduce_impl(const void* const* grads, int K, const int64_t* layer_offsets, i
 
     std::lock_guard<std::mutex> lock(g_mutex);
     Plan* p = nullptr;
-    rc = find_or_make_plan(K, o.radix == 0 ? default_radix(o) : o.radix, o.order, dtype, o.out_dtype,
+    rc = find_or_make_plan(K, o.radix, o.order, dtype, o.out_dtype,
                            o.delta_start != nullptr, o.fuse != 0, o.separate != 0, layer_offsets, n_layers, &p);
     if (rc != ADASUM_OK) return rc;
     return execute_plan(p, grads, dtype, out, o, stream);
@@ -1152,7 +1233,13 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
     Plan plan;   // host-side description only; its device pointers point into the static array
     plan.borrowed = true;
     plan.K = K;
-    plan.radix = o.radix == 0 ? default_radix(o) : o.radix;
+    Replaced replaced;
+    try {
+        plan.radix = o.radix != 0 ? o.radix
+                                  : default_radix(K, o.order, dtype, o.delta_start != nullptr, o.separate != 0, layer_offsets, L, &replaced);
+    } catch (const std::bad_alloc&) {
+        return ADASUM_ERR_OUT_OF_MEMORY;
+    }
     plan.order = o.order;
     plan.node_type = node_type;
     struct CombTable {
@@ -1241,6 +1328,7 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
     } catch (const std::bad_alloc&) {
         return ADASUM_ERR_OUT_OF_MEMORY;
     }
+    if (replaced.scratch > ADASUM_NOALLOC_SCRATCH_BYTES) return ADASUM_ERR_TOO_LARGE;
     if (carve.off > ADASUM_NOALLOC_SCRATCH_BYTES) {
         // (the other passes share less between workgroups and may fit still)
         if (plan.resident.form > 0) return reduce_noalloc_impl(grads, K, layer_offsets, n_layers, dtype, out, opts, stream, false);
@@ -1363,11 +1451,10 @@ int adasum_plan_create(int K, const int64_t* layer_offsets, int n_layers, int dt
     h->dtype = dtype;
     h->for_delta = o.delta_start != nullptr;
     h->opts = o;
-    h->opts.radix = o.radix == 0 ? default_radix(o) : o.radix;
     h->opts.delta_start = nullptr;
     if (layer_offsets[n_layers] > 0) {
-        rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, h->for_delta || o.separate != 0,
-                       o.separate == 0, layer_offsets, n_layers, h->plan);
+        rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, o.separate != 0, true,
+                       layer_offsets, n_layers, h->plan);
         if (rc != ADASUM_OK) return rc;
         if (o.workspace != nullptr && o.workspace_bytes < h->plan->lay.total) return ADASUM_ERR_WORKSPACE;
         // everything execute needs exists from here on: it allocates nothing
@@ -1441,26 +1528,16 @@ int adasum_workspace_bytes(int K, const int64_t* layer_offsets, int n_layers, in
     if (rc != ADASUM_OK && rc != ADASUM_ERR_WORKSPACE) return rc;
     try {
         std::vector<int> radices;
-        const int radix = o.radix == 0 ? default_radix(o) : o.radix;
+        const bool delta = o.delta_start != nullptr;
+        Replaced replaced;
+        const int radix = o.radix != 0 ? o.radix : default_radix(K, o.order, dtype, delta, o.separate != 0, layer_offsets, n_layers, &replaced);
         rc = o.order == ADASUM_ORDER_LINEAR ? build_linear_passes(K, radix, radices)
                                             : build_levels(K, radix, radices);
         if (rc != ADASUM_OK) return rc;
-        const int Kv = o.order == ADASUM_ORDER_LINEAR ? K : virtual_leaves(radices);
-        std::vector<SmallLayer> small;
-        const int64_t small_elems = K > 1 ? find_small_layers(layer_offsets, n_layers, small) : 0;
-        Layout lay = make_layout(Kv, layer_offsets[n_layers], n_layers,
-                                       count_tiles(layer_offsets, n_layers, gram_tile_capacity(layer_offsets, n_layers)),
-                                       norm_entries_bound(Kv, layer_offsets, n_layers, radices, node_dtype(dtype)),
-                                       radices, o.order, K + 1, small_elems, node_dtype(dtype),
-                                       o.fuse ? dot_entries_bound(Kv, layer_offsets, n_layers, radices, node_dtype(dtype))
-                                       : (o.order == ADASUM_ORDER_TREE && !o.separate && o.delta_start == nullptr)
-                                           ? next_entries_bound(Kv, layer_offsets, n_layers, radices, node_dtype(dtype))
-                                           : 0,
-                                       !radices.empty() && wide_radix(radices[0])
-                                           ? count_spans(layer_offsets, n_layers, wide_part_count(layer_offsets[n_layers]))
-                                           : 0);
+        Layout lay = problem_layout(K, radices, o.order, dtype, delta, o.fuse != 0, o.separate != 0, layer_offsets, n_layers);
+        lay.total = std::max(lay.total, replaced.workspace);
         if (!o.separate) {
-            const ResidentPlan r = plan_resident(K, radices, dtype, o.delta_start != nullptr, layer_offsets, n_layers);
+            const ResidentPlan r = plan_resident(K, radices, dtype, delta, layer_offsets, n_layers);
             if (r.form > 0) add_resident(lay, r);
         }
         *bytes = lay.total;

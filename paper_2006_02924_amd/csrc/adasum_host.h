@@ -52,8 +52,10 @@ constexpr int kMaxWideRadix = 64;
 inline bool wide_radix(int R) { return R > kMaxRadix; }
 // 32 x 32 blocks a wide Gram pass keeps per tile: the three distinct ones of a 64 x 64 matrix, or one.
 constexpr int wide_blocks(int R) { return R == 64 ? 3 : 1; }
-// Radix used when the caller asks for 0: the widest pass moves the fewest bytes.
+// Radix used when the caller asks for 0 (the widest pass of the vector-unit kernels moves the fewest bytes), unless a wide
+// first pass takes its place: default_radix in adasum_api.cpp.
 constexpr int kDefaultRadix = 16;
+constexpr int64_t kWideElements = 4000000;   // from here on more than 32 workers are taken in one pass of 64
 
 inline bool known_dtype(int dtype) { return dtype == ADASUM_F32 || dtype == ADASUM_BF16 || dtype == ADASUM_F16 || dtype == ADASUM_F64; }
 // Storage type of the intermediate tree nodes for an input type.
@@ -205,7 +207,9 @@ struct Layout {
     size_t  off_resident = 0; // a resident pass: int32 [1 + units], then the tagged words (see ResidentState)
     size_t  off_words = 0;
     int64_t partial_words = 0;
-    size_t  total = 0;
+    size_t  need = 0;         // what the plan's own workspace holds
+    size_t  total = 0;        // what a caller's must hold: no less than the radix-16 schedule needs where a wide first
+                              // pass is the default in its place
 };
 // `norm_entries`: doubles needed for the squared norms the combines leave
 // (max over passes of nodes written x combine tiles of that pass).

@@ -20,7 +20,7 @@
 // 16-operand combine of 16-bit inputs: 512 bytes of each of two operands);
 // partial sums go lane (fp32; fp64 for
 // fp64 storage) -> wave (shuffles) -> workgroup (fp64 via LDS) -> per-tile fp64
-// partial in memory, summed later in a fixed order; no atomics anywhere.
+// partial in memory, summed later in a fixed order.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1097,7 +1097,9 @@ gram_wide_kernel(const Operands ops, const adasum_tile* __restrict__ spans, cons
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                sum[b][v] += acc[b][v];
+                // (scaled by a power of two, exactly: a span of 2^18 products per accumulator then stays in the fp32 range
+                // for as large values as the other passes take)
+                sum[b][v] = fma_t(acc[b][v], 0x1p-8f, sum[b][v]);
                 acc[b][v] = 0.f;
             }
     };
@@ -1200,8 +1202,8 @@ gram_wide_kernel(const Operands ops, const adasum_tile* __restrict__ spans, cons
             for (int v = 0; v < 16; ++v) red[wave * NPW + (b * 16 + v) * 64 + lane] = sum[b][v];
         __syncthreads();
         for (int e = tid; e < NPW; e += kThreads)
-            out[e] = ((static_cast<double>(red[e]) + static_cast<double>(red[NPW + e])) +
-                      static_cast<double>(red[2 * NPW + e])) + static_cast<double>(red[3 * NPW + e]);
+            out[e] = 0x1p8 * (((static_cast<double>(red[e]) + static_cast<double>(red[NPW + e])) +
+                               static_cast<double>(red[2 * NPW + e])) + static_cast<double>(red[3 * NPW + e]));
         __syncthreads();   // (the next span stages into the same memory)
     }
 }

@@ -244,7 +244,7 @@ Layout make_layout(int K, int64_t N, int n_layers, int64_t n_tiles, int64_t norm
     lay.dot_entries = dot_entries;
     off = align_up(off + static_cast<size_t>(dot_entries) * sizeof(double), 256);
     lay.base_total = off;
-    lay.total = off;
+    lay.need = lay.total = off;
     return lay;
 }
 
@@ -281,7 +281,7 @@ void add_resident(Layout& lay, const ResidentPlan& p) {
     lay.off_words = off;
     lay.partial_words = static_cast<int64_t>(p.n_units * words);
     off = align_up(off + (static_cast<size_t>(p.n_units) + static_cast<size_t>(lay.n_layers)) * words * sizeof(int64_t), 256);
-    lay.total = off;
+    lay.need = lay.total = off;
 }
 
 void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int form,

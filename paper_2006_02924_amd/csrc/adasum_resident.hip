@@ -110,7 +110,7 @@ constexpr int kSkipScan = 32;            // units a workgroup of the second laun
 constexpr long long kWaitTicks = ADASUM_WAIT_TICKS;   // of the 100 MHz clock: 100 us
 
 // 16 bytes per lane straight from memory into LDS (lane l's at dst + 16 l): no registers are held meanwhile.
-__device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
+[[maybe_unused]] __device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                      (__attribute__((address_space(3))) void*)dst, 16, 0, 2 /* non-temporal */);
 }
