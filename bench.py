@@ -295,7 +295,7 @@ def run_other(B, name, *, radix=0, steps=10, warmup=2, w=None, fuse=False, separ
                     "dominant_kernel_GBps": roof["achieved"], "dominant_kernel_frac": roof["frac"],
                     "ms_per_step_with_events": dtp / steps * 1e3})
         eff = effective_radix(w, radix, order, delta)
-        t = measured_traffic((name if eff in (8, 16) and not radix else f"{name}_radix{eff}") + ("_fused" if fuse else "")
+        t = measured_traffic((name if eff == 16 or (eff == 8 and not radix) else f"{name}_radix{eff}") + ("_fused" if fuse else "")
                              + ("_separate" if separate else ""), roof["kernel"]) if (order == "tree" and not delta) else None
         row["dominant_kernel_traffic"] = t["bytes"] if t else None
     if w.K & (w.K - 1) == 0 and w.K > 1 and order == "tree" and not delta:
@@ -396,7 +396,7 @@ def main():
 
     roofline = kernel_summary(prof, args.steps, ms_per_step, args.workload, verbose_tag="")
     if roofline is not None:
-        key = (args.workload if eff in (8, 16) and not args.radix else f"{args.workload}_radix{eff}") + \
+        key = (args.workload if eff == 16 or (eff == 8 and not args.radix) else f"{args.workload}_radix{eff}") + \
               ("_fused" if args.fuse_siblings else "") + ("_separate" if args.separate_passes else "")
         t = measured_traffic(key, roofline["kernel"]) if (args.order == "tree" and not args.delta) else None
         if t is not None:
