@@ -195,7 +195,9 @@ ADASUM_API int adasum_reduce_ex(const void* const* grads, int K,
 /* Bytes of DEVICE workspace adasum_reduce_ex needs for this problem (intermediate
  * tree nodes, per-tile partial sums, coefficient tables, the compact copy of the
  * small layers).  Depends on dtype, radix, order, fuse_siblings, separate_passes and on
- * whether delta_start is set (any non-NULL value).  Host-only. */
+ * whether delta_start is set (any non-NULL value).  Host-only.  A smaller workspace that
+ * holds the sections of the passes without the resident pass and without a wide default is
+ * taken too: the reduction then takes those passes. */
 ADASUM_API int adasum_workspace_bytes(int K, const int64_t* layer_offsets, int n_layers,
                            int dtype, const adasum_options* opts, size_t* bytes);
 

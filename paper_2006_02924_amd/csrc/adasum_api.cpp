@@ -289,6 +289,7 @@ struct Plan {
     int in_dtype = -1, out_dtype = -1, delta = 0;
     int fuse = 0;                         // laid out for the sibling-fused radix-2 schedule
     int separate = 0;                     // cache key: made with separate_passes
+    int lean = 0;                         // cache key: without what makes the workspace larger (make_plan)
     int feed = 0;                         // passes leave the next pass's Gram entries where they can
                                           // (pass_feeds_next): tree order, no delta form, no fuse
     std::vector<int64_t> offsets;
@@ -388,8 +389,9 @@ int take_resident(Plan* p, int dtype, bool delta, const int64_t* offsets, int n_
 }
 
 // Builds a plan (host tables, their device copies; no workspace yet) on the current device.
-// `radix` 0: the default's.  `whole`: the plan is for whole reductions, not for the steps of one.
-int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, bool separate, bool whole,
+// `radix` 0: the default's.  `whole`: the plan is for whole reductions, not for the steps of one.  `lean`: neither the
+// resident pass nor a wide default, so that a caller's workspace that holds the other passes' sections is enough.
+int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, bool separate, bool whole, bool lean,
               const int64_t* offsets, int n_layers, std::unique_ptr<Plan>& out) {
     const int node_type = node_dtype(dtype);
     int device = 0;
@@ -401,7 +403,10 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
         p->K = K;
         p->radix = radix;
         Replaced replaced;
-        if (radix == 0) radix = default_radix(K, order, dtype, delta, separate, offsets, n_layers, &replaced);
+        p->lean = lean ? 1 : 0;
+        if (radix == 0)
+            radix = lean ? (delta || dtype == ADASUM_F64 ? 8 : kDefaultRadix)
+                         : default_radix(K, order, dtype, delta, separate, offsets, n_layers, &replaced);
         p->order = order;
         p->node_type = node_type;
         p->fuse = fuse ? 1 : 0;
@@ -429,7 +434,7 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
                              static_cast<int64_t>(p->wide_spans.tiles.size()));
         p->lay.need = p->lay.total;
         p->lay.total = std::max(p->lay.total, replaced.workspace);
-        if (whole && !separate) {
+        if (whole && !separate && !lean) {
             const int rc = take_resident(p.get(), dtype, delta, offsets, n_layers);
             if (rc != ADASUM_OK) return rc;
             if (p->resident.form > 0)
@@ -472,7 +477,7 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
 // `order` is a tree order or kStepPlans (the step entry points keep plans of their own).
 constexpr int kStepPlans = 100;
 int find_or_make_plan(int K, int radix, int order, int in_dtype, int out_dtype, bool delta, bool fuse, bool separate,
-                      const int64_t* offsets, int n_layers, Plan** out) {
+                      const int64_t* offsets, int n_layers, Plan** out, bool lean = false) {
     const int node_type = node_dtype(in_dtype);
     int device = 0;
     ADASUM_HIP(hipGetDevice(&device));
@@ -480,7 +485,7 @@ int find_or_make_plan(int K, int radix, int order, int in_dtype, int out_dtype, 
         Plan* p = g_plans[i].get();
         if (p->device == device && p->K == K && p->radix == radix && p->order == order && p->node_type == node_type &&
             p->in_dtype == in_dtype && p->out_dtype == out_dtype && p->delta == (delta ? 1 : 0) &&
-            p->fuse == (fuse ? 1 : 0) && p->separate == (separate ? 1 : 0) &&
+            p->fuse == (fuse ? 1 : 0) && p->separate == (separate ? 1 : 0) && p->lean == (lean ? 1 : 0) &&
             static_cast<int>(p->offsets.size()) == n_layers + 1 &&
             std::memcmp(p->offsets.data(), offsets, sizeof(int64_t) * (n_layers + 1)) == 0) {
             // most recently used last
@@ -493,7 +498,7 @@ int find_or_make_plan(int K, int radix, int order, int in_dtype, int out_dtype, 
     while (g_plans.size() >= kMaxPlans) g_plans.erase(g_plans.begin());
     std::unique_ptr<Plan> p;
     const int rc = make_plan(K, radix, order == kStepPlans ? ADASUM_ORDER_TREE : order, in_dtype, delta, fuse,
-                             separate, order != kStepPlans, offsets, n_layers, p);
+                             separate, order != kStepPlans, lean, offsets, n_layers, p);
     if (rc != ADASUM_OK) return rc;
     p->order = order;
     p->in_dtype = in_dtype;
@@ -1200,6 +1205,12 @@ int reduce_impl(const void* const* grads, int K, const int64_t* layer_offsets, i
     rc = find_or_make_plan(K, o.radix, o.order, dtype, o.out_dtype,
                            o.delta_start != nullptr, o.fuse != 0, o.separate != 0, layer_offsets, n_layers, &p);
     if (rc != ADASUM_OK) return rc;
+    if (o.workspace != nullptr && o.workspace_bytes < p->lay.total) {
+        // a workspace that holds the other passes' sections only is enough for those
+        rc = find_or_make_plan(K, o.radix, o.order, dtype, o.out_dtype, o.delta_start != nullptr, o.fuse != 0,
+                               o.separate != 0, layer_offsets, n_layers, &p, true);
+        if (rc != ADASUM_OK) return rc;
+    }
     return execute_plan(p, grads, dtype, out, o, stream);
 }
 
@@ -1453,9 +1464,14 @@ int adasum_plan_create(int K, const int64_t* layer_offsets, int n_layers, int dt
     h->opts = o;
     h->opts.delta_start = nullptr;
     if (layer_offsets[n_layers] > 0) {
-        rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, o.separate != 0, true,
+        rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, o.separate != 0, true, false,
                        layer_offsets, n_layers, h->plan);
         if (rc != ADASUM_OK) return rc;
+        if (o.workspace != nullptr && o.workspace_bytes < h->plan->lay.total) {
+            rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, o.separate != 0, true, true,
+                           layer_offsets, n_layers, h->plan);
+            if (rc != ADASUM_OK) return rc;
+        }
         if (o.workspace != nullptr && o.workspace_bytes < h->plan->lay.total) return ADASUM_ERR_WORKSPACE;
         // everything execute needs exists from here on: it allocates nothing
         if (h->plan->resident.form == 0) {

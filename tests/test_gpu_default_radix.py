@@ -6,6 +6,7 @@ import torch
 
 from paper_2006_02924_amd import binding as B
 from paper_2006_02924_amd import workloads as W
+from tests.gpu_util import oracle_reduce
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -25,6 +26,37 @@ def test_default_is_the_named_schedule(K, N, radix, dtype):
         out = torch.empty_like(got)
         B.adasum_reduce(w.grads, w.layer_offsets, out, noalloc=True)
         assert torch.equal(got, out)
+
+
+@pytest.mark.parametrize("K,dtype,code,enough", [(16, torch.float32, B.F32, 24_320), (8, torch.float64, B.F64, 9_216),
+                                                 (33, torch.bfloat16, B.BF16, 1_318_912)])
+def test_a_workspace_without_room_for_the_faster_passes(K, dtype, code, enough):
+    """`enough` is what the passes without the resident one and without a wide default take: refused below it, and
+    from it on the result of those passes (within rounding: separate passes sum the same products in other orders)."""
+    print(f"lean workspace K={K} {dtype}", flush=True)
+    offs = W.offsets_from_sizes([1, 17, 5_003, 33, 70_001])
+    assert B.adasum_workspace_bytes(K, offs, code) > enough
+    wide = torch.float32 if dtype == torch.float64 else dtype
+    w = W.correlated_gaussian([1, 17, 5_003, 33, 70_001], K, dtype=wide, device=DEV, seed=9)
+    grads = [g.to(dtype) for g in w.grads]
+    out_dtype = torch.float64 if dtype == torch.float64 else torch.float32
+    ws = torch.empty(enough, dtype=torch.uint8, device=DEV)
+    got = B.adasum_reduce(grads, offs, out_dtype=out_dtype, workspace=ws)
+    ref = oracle_reduce(grads, offs)
+    own = B.adasum_reduce(grads, offs, out_dtype=out_dtype)
+    # both are within half an fp32 epsilon times a small factor of the exact result per layer
+    tol = 1e-13 if dtype == torch.float64 else 2e-6
+    for lo, hi in zip(offs[:-1], offs[1:]):
+        assert torch.linalg.vector_norm((got - own)[lo:hi].double()) <= tol * torch.linalg.vector_norm(own[lo:hi].double())
+        if not np.isnan(ref[lo:hi]).any():               # (a layer whose result is ill-posed has no reference)
+            d = got[lo:hi].cpu().double().numpy() - ref[lo:hi]
+            assert np.linalg.norm(d) <= tol * np.linalg.norm(ref[lo:hi])
+    plan = B.Plan(K, offs, dtype, out_dtype=out_dtype, workspace=ws)
+    out = torch.empty_like(got)
+    plan.execute(grads, out)
+    assert torch.equal(out, got)
+    with pytest.raises(Exception):
+        B.adasum_reduce(grads, offs, out_dtype=out_dtype, workspace=ws[: enough - 256])
 
 
 @pytest.mark.parametrize("K", [24, 40])
