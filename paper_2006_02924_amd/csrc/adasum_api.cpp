@@ -174,6 +174,42 @@ size_t scratch_bytes(int K, const std::vector<int>& radices, int dtype, bool sep
     return off;
 }
 
+// The same for a resident pass (`lay` with its section).
+size_t resident_scratch_bytes(const ResidentPlan& r, const Layout& lay, const int64_t* offsets, int L) {
+    size_t off = 0;
+    auto take = [&](size_t bytes) { off = align_up(off, 256) + bytes; };
+    take(sizeof(int64_t) * (static_cast<size_t>(L) + 1));
+    take(sizeof(adasum_tile) * static_cast<size_t>(r.n_units));
+    take(sizeof(int32_t) * (static_cast<size_t>(L) + 1));
+    take(sizeof(ResidentUnit) * static_cast<size_t>(r.n_units));
+    int64_t n_small = 0;
+    for (int l = 0; l < L; ++l) {
+        const int64_t len = offsets[l + 1] - offsets[l];
+        n_small += len >= 1 && len <= kSmallLayer;
+    }
+    take(sizeof(SmallLayer) * static_cast<size_t>(n_small));
+    take(lay.total);
+    return off;
+}
+
+// Whether a reduction in one pass is taken as a resident pass (form 0: not), from the layer table alone, and with `lay`
+// (of the other passes) its section added.  adasum_reduce_noalloc takes what the other passes' tables and workspace fit
+// its scratch for and gives the bits that the other entry points give, so where those fit it and the resident pass does
+// not (tens of thousands of units), no entry point takes the resident pass.
+ResidentPlan route_resident(int K, const std::vector<int>& radices, int dtype, bool delta, bool separate,
+                            const int64_t* offsets, int L, Layout& lay) {
+    if (separate) return ResidentPlan();
+    const ResidentPlan r = plan_resident(K, radices, dtype, delta, offsets, L);
+    if (r.form == 0) return r;
+    Layout with = lay;
+    add_resident(with, r);
+    if (resident_scratch_bytes(r, with, offsets, L) > ADASUM_NOALLOC_SCRATCH_BYTES &&
+        scratch_bytes(K, radices, dtype, separate, lay, offsets, L) <= ADASUM_NOALLOC_SCRATCH_BYTES)
+        return ResidentPlan();
+    lay = with;
+    return r;
+}
+
 // The radix of a problem that names none.
 //  - The delta form's Gram pass subtracts before it multiplies and so cannot use the packed dot instructions; with 16
 //    operands it runs out of registers, 8 is its fastest radix.  fp64 accumulators are twice as wide: 8 as well.
@@ -373,18 +409,18 @@ std::mutex g_mutex;
 std::vector<std::unique_ptr<Plan>> g_plans;   // least recently used first
 constexpr size_t kMaxPlans = 64;
 
-// Takes the reduction as a resident pass, and lays out its section of the workspace, where the layer table suits one
-// and the device is one it is made for (the section is there all the same: adasum_workspace_bytes asks no device).
-int take_resident(Plan* p, int dtype, bool delta, const int64_t* offsets, int n_layers) {
-    const ResidentPlan r = plan_resident(p->K, p->radices, dtype, delta, offsets, n_layers);
+// Takes the reduction as the resident pass `r` (with its section in the layout `with`) where the device is one it is
+// made for.  (A plan's own or a caller's workspace has the section all the same: adasum_workspace_bytes asks no device.)
+int take_resident(Plan* p, const ResidentPlan& r, const Layout& with) {
     if (r.form == 0) return ADASUM_OK;
     int device = 0, cus = 0;
     ADASUM_HIP(hipGetDevice(&device));
     ADASUM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
-    add_resident(p->lay, r);
-    if (cus < kResidentCus) return ADASUM_OK;
-    p->resident = r;
-    p->unit_tiles.capacity = r.capacity;
+    if (cus >= kResidentCus) {
+        p->resident = r;
+        p->unit_tiles.capacity = r.capacity;
+    }
+    if (p->resident.form > 0 || !p->borrowed) p->lay = with;
     return ADASUM_OK;
 }
 
@@ -434,8 +470,10 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
                              static_cast<int64_t>(p->wide_spans.tiles.size()));
         p->lay.need = p->lay.total;
         p->lay.total = std::max(p->lay.total, replaced.workspace);
-        if (whole && !separate && !lean) {
-            const int rc = take_resident(p.get(), dtype, delta, offsets, n_layers);
+        if (whole && !lean) {
+            Layout with = p->lay;
+            const ResidentPlan r = route_resident(K, p->radices, dtype, delta, separate, offsets, n_layers, with);
+            const int rc = take_resident(p.get(), r, with);
             if (rc != ADASUM_OK) return rc;
             if (p->resident.form > 0)
                 build_tiles(offsets, n_layers, p->resident.capacity, p->unit_tiles.tiles, p->unit_tiles.layer_begin);
@@ -1231,7 +1269,7 @@ struct Carver {
 // the layer table goes to the device in kernel arguments, the tables are built there, and the
 // scheduler then runs on a plan that only borrows that memory.
 int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_offsets, int n_layers, int dtype,
-                        void* out, const adasum_options* opts, void* stream, bool resident = true) {
+                        void* out, const adasum_options* opts, void* stream) {
     Opts o;
     int64_t N = 0;
     int rc = check_reduce_args(grads, K, layer_offsets, n_layers, dtype, out, opts, o, N);
@@ -1296,10 +1334,13 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
                                : plan.feed ? next_entries_bound(Kv, layer_offsets, L, plan.radices, node_type)
                                            : 0,
                                static_cast<int64_t>(plan.wide_spans.tiles.size()));
-        if (resident && !o.separate) {
-            rc = take_resident(&plan, dtype, o.delta_start != nullptr, layer_offsets, L);
-            if (rc != ADASUM_OK) return rc;
-        }
+        Layout with = plan.lay;
+        const ResidentPlan r = route_resident(K, plan.radices, dtype, o.delta_start != nullptr, o.separate != 0, layer_offsets, L, with);
+        // (what fits does not depend on the route)
+        if (r.form > 0 && scratch_bytes(K, plan.radices, dtype, false, plan.lay, layer_offsets, L) > ADASUM_NOALLOC_SCRATCH_BYTES)
+            return ADASUM_ERR_TOO_LARGE;
+        rc = take_resident(&plan, r, with);
+        if (rc != ADASUM_OK) return rc;
         // the combine tables this reduction reads: one per distinct tile capacity
         std::vector<int> caps;
         if (K == 1) caps.push_back(combine_tile_capacity(dtype, 1));
@@ -1340,11 +1381,7 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
         return ADASUM_ERR_OUT_OF_MEMORY;
     }
     if (replaced.scratch > ADASUM_NOALLOC_SCRATCH_BYTES) return ADASUM_ERR_TOO_LARGE;
-    if (carve.off > ADASUM_NOALLOC_SCRATCH_BYTES) {
-        // (the other passes share less between workgroups and may fit still)
-        if (plan.resident.form > 0) return reduce_noalloc_impl(grads, K, layer_offsets, n_layers, dtype, out, opts, stream, false);
-        return ADASUM_ERR_TOO_LARGE;
-    }
+    if (carve.off > ADASUM_NOALLOC_SCRATCH_BYTES) return ADASUM_ERR_TOO_LARGE;
 
     char* base = nullptr;
     size_t have = 0;
@@ -1552,10 +1589,7 @@ int adasum_workspace_bytes(int K, const int64_t* layer_offsets, int n_layers, in
         if (rc != ADASUM_OK) return rc;
         Layout lay = problem_layout(K, radices, o.order, dtype, delta, o.fuse != 0, o.separate != 0, layer_offsets, n_layers);
         lay.total = std::max(lay.total, replaced.workspace);
-        if (!o.separate) {
-            const ResidentPlan r = plan_resident(K, radices, dtype, delta, layer_offsets, n_layers);
-            if (r.form > 0) add_resident(lay, r);
-        }
+        (void)route_resident(K, radices, dtype, delta, o.separate != 0, layer_offsets, n_layers, lay);
         *bytes = lay.total;
     } catch (const std::bad_alloc&) {
         return ADASUM_ERR_OUT_OF_MEMORY;
