@@ -1011,8 +1011,11 @@ parts_coarsen_kernel(const double* __restrict__ fine, int n_fine_tiles, const in
 // wave w loads rows w, w + 4, ... of the block, 512 bytes or 1 KB of a row per load instruction,
 // one block ahead of the multiplies.  The block goes through LDS (two buffers, one barrier per
 // block) to reach the operand layout; every wave then multiplies its quarter of the block's columns
-// for all rows.  The products are exact; the matrix cores add the 64 of a wave's quarter in fp32,
-// the blocks' sums are added with ordinary fp32 additions (round to nearest), fp64 above the wave.
+// for all rows.  The products are exact; the matrix cores add the 64 of a wave's quarter (128 columns at
+// R = 32 in two such runs) in fp32, everything above is added in fp64.  (Kept in fp32 over a span, up to 2^18
+// products, the sums of a constant layer were off by 1e-5 and more, where every addition in a binade
+// rounds the same way; in fp64 they take 96 registers, which fit beside the loads because a block of the
+// matrix is accumulated and widened before the next is begun.)
 // partials[(group * n_spans + span) * NPW + (block * 16 + v) * 64 + lane], NPW = blocks * 1024:
 // accumulator v of a lane is row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32 of the block.
 // ---------------------------------------------------------------------------
@@ -1030,6 +1033,13 @@ __device__ __forceinline__ u32x4 stream_load_global(const void* p) {
 #else
     return *(global_u32x4_ptr)p;
 #endif
+}
+
+template <typename T>
+__device__ __forceinline__ float load_elem_global(const T* p) {
+    T x;
+    x.v = *(const unsigned short __attribute__((address_space(1)))*)p;
+    return load_elem(&x);
 }
 
 template <typename T>
@@ -1059,10 +1069,11 @@ gram_wide_kernel(const Operands ops, const adasum_tile* __restrict__ spans, cons
     constexpr int PITCH = CH * 16 + 16;           // bytes per row in LDS (padded: conflict-free operand reads)
     constexpr int BUF = R * PITCH;
     constexpr int NPW = NB * 1024;
-    static_assert(NLD == 8 && 2 * BUF >= 4 * NPW * (int)sizeof(float), "LDS is reused for the waves' sums");
+    static_assert(NLD == 8 && KW % 4 == 0 && 2 * BUF >= 4 * 1024 * (int)sizeof(double), "LDS is reused for the waves' sums");
 
     __shared__ __align__(16) unsigned char lds[2 * BUF];
     __shared__ const T* rowptr[R];
+    __shared__ float edge[2 * (G - 1)][R];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1083,33 +1094,14 @@ gram_wide_kernel(const Operands ops, const adasum_tile* __restrict__ spans, cons
     const int rdP = m * PITCH + (2 * KW * wave + h) * 16;
     const int rdQ = rdP + 32 * PITCH;
 
-    float sum[NB][16];
-
-    auto multiply_add = [&](const u32x4& p, const u32x4& q, f32x16_t (&acc)[NB]) {
-        acc[0] = mfma_rows<T>(p, p, acc[0]);
-        if constexpr (NB == 3) {
-            acc[1] = mfma_rows<T>(p, q, acc[1]);
-            acc[2] = mfma_rows<T>(q, q, acc[2]);
-        }
-    };
-    auto flush = [&](f32x16_t (&acc)[NB]) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                // (scaled by a power of two, exactly: a span of 2^18 products per accumulator then stays in the fp32 range
-                // for as large values as the other passes take)
-                sum[b][v] = fma_t(acc[b][v], 0x1p-8f, sum[b][v]);
-                acc[b][v] = 0.f;
-            }
-    };
+    double sum[NB][16];
 
     for (int sp = part_begin[part]; sp < part_begin[part + 1]; ++sp) {   // (uniform: the barriers below match)
         const Split s = split_tile<G>(spans[sp]);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sum[b][v] = 0.f;
+            for (int v = 0; v < 16; ++v) sum[b][v] = 0.0;
         // Blocks start at multiples of the block length in the fused buffer, so that a lane group's
         // 512 bytes or 1 KB of a row are whole 128-byte lines whatever the layer's offset: the span's
         // granules are numbers g0 .. g0 + ng - 1 of that grid.
@@ -1140,11 +1132,10 @@ gram_wide_kernel(const Operands ops, const adasum_tile* __restrict__ spans, cons
                 *reinterpret_cast<u32x4*>(buf + wr + i * (RPI * 4 * PITCH)) = v;
             }
         };
-        f32x16_t acc[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+        // the at most 2 * 7 elements of a ragged head and tail: element tid / R + i * (kThreads / R) of row tid % R
+        const int nedge = s.nh + s.nt;
+        for (int e = tid / R; e < nedge; e += kThreads / R)
+            edge[e][tid % R] = load_elem_global(rowptr[tid % R] + (e < s.nh ? s.start + e : s.ts + (e - s.nh)));
 
         if (nsteps > 0) {
 #pragma unroll
@@ -1159,51 +1150,62 @@ gram_wide_kernel(const Operands ops, const adasum_tile* __restrict__ spans, cons
                 store_block(buf, stage[a % AHEAD], step0 + a);
                 fetch(stage[a % AHEAD], step0 + a + AHEAD);
                 __syncthreads();
+                // one block of the matrix after the other: 16 accumulators live beside the sums, not 48
 #pragma unroll
-                for (int j = 0; j < KW; ++j) {
-                    const u32x4 p = *reinterpret_cast<const u32x4*>(buf + rdP + j * 32);
-                    u32x4 q = p;
-                    if constexpr (NB == 3) q = *reinterpret_cast<const u32x4*>(buf + rdQ + j * 32);
-                    multiply_add(p, q, acc);
-                }
-                flush(acc);
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int j0 = 0; j0 < KW; j0 += 4) {
+                        f32x16_t acc;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+                        for (int j = j0; j < j0 + 4; ++j) {
+                            const u32x4 x = *reinterpret_cast<const u32x4*>(buf + (b == 2 ? rdQ : rdP) + j * 32);
+                            const u32x4 y = b == 1 ? *reinterpret_cast<const u32x4*>(buf + rdQ + j * 32) : x;
+                            acc = mfma_rows<T>(x, y, acc);
+                        }
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) sum[b][v] += static_cast<double>(acc[v]);
+                    }
             }
         }
 
-        // the at most 2 * 7 elements of a ragged head and tail: one more multiply step by wave 0, the
-        // elements fetched one by one straight into the operand layout (k = 8 h .. 8 h + 7)
-        const int nedge = s.nh + s.nt;
-        if (nedge > 0 && wave == 0) {
-            unsigned int pw[4] = {0u, 0u, 0u, 0u}, qw[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int e = 8 * h + k;
-                if (e < nedge) {
-                    const long long idx = e < s.nh ? s.start + e : s.ts + (e - s.nh);
-                    pw[k / 2] |= static_cast<unsigned int>(rowptr[m][idx].v) << (16 * (k & 1));
-                    if constexpr (NB == 3) qw[k / 2] |= static_cast<unsigned int>(rowptr[32 + m][idx].v) << (16 * (k & 1));
-                }
-            }
-            u32x4 p, q;
-            p.x = pw[0]; p.y = pw[1]; p.z = pw[2]; p.w = pw[3];
-            q.x = qw[0]; q.y = qw[1]; q.z = qw[2]; q.w = qw[3];
-            multiply_add(p, q, acc);
-            flush(acc);
-        }
-
-        // the four waves' sums go through LDS (the staging area, now free) and are added in a fixed
-        // order, in fp64, by all lanes: entry e of wave w sits at w * NPW + e
-        float* red = reinterpret_cast<float*>(lds);
+        // the four waves' sums go through LDS (the staging area, now free), a block of the matrix at a time, and are
+        // added in a fixed order: entry e of wave w sits at w * 1024 + e.  The ragged elements are multiplied and
+        // summed in fp64, as in the other passes: lane m of half h has column m (and 32 + m) of rows 8 k + 4 h + wave.
+        double* red = reinterpret_cast<double*>(lds);
         double* out = partials + (static_cast<long long>(g) * n_spans + sp) * NPW;
         __syncthreads();
+        double ragged[NB][4];
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) red[wave * NPW + (b * 16 + v) * 64 + lane] = sum[b][v];
-        __syncthreads();
-        for (int e = tid; e < NPW; e += kThreads)
-            out[e] = 0x1p8 * (((static_cast<double>(red[e]) + static_cast<double>(red[NPW + e])) +
-                               static_cast<double>(red[2 * NPW + e])) + static_cast<double>(red[3 * NPW + e]));
+            for (int k = 0; k < 4; ++k) ragged[b][k] = 0.0;
+        for (int n = 0; n < nedge; ++n) {
+            const double colP = edge[n][m], colQ = NB == 3 ? edge[n][R - 32 + m] : 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double rowP = edge[n][8 * k + 4 * h + wave];
+                ragged[0][k] = __builtin_fma(rowP, colP, ragged[0][k]);
+                if constexpr (NB == 3) {
+                    const double rowQ = edge[n][32 + 8 * k + 4 * h + wave];
+                    ragged[1][k] = __builtin_fma(rowP, colQ, ragged[1][k]);
+                    ragged[2][k] = __builtin_fma(rowQ, colQ, ragged[2][k]);
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (b > 0) __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 16; ++v) red[wave * 1024 + v * 64 + lane] = sum[b][v];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int e = tid + k * kThreads;
+                out[b * 1024 + e] = ((red[e] + red[1024 + e]) + (red[2048 + e] + red[3072 + e])) + ragged[b][k];
+            }
+        }
         __syncthreads();   // (the next span stages into the same memory)
     }
 }
