@@ -1278,13 +1278,16 @@ gram_finish_wide_kernel(const double* __restrict__ partials, const int32_t* __re
 
 // Step 3 after a wide first pass: out = sum_r w_r x_r over R = 32 or 64 16-bit operands, sixteen at a
 // time (as many loads in flight per lane as the radix-16 combine has), one 16-byte granule per lane, one
-// wave per tile.  normparts[group * n_tiles + tile] (or null).
+// wave per tile.  Runs of 8 products (4 at R = 32, which may have another pass above it) are summed in fp32, the
+// runs in fp64: one fp32 chain over all operands put 1.2e-7 of relative error on an fp32 result where the radix-16
+// passes put 5.3e-8 (K = 64, one layer of 20 million elements); this way it is 3.2e-8, at the same speed (every
+// product in fp64: 2.6e-8, 1 % slower).  normparts[group * n_tiles + tile] (or null).
 template <typename TI, typename TO, int R>
 __global__ void __launch_bounds__(64)
 combine_wide_kernel(const Operands ops, const Outputs outs, const adasum_tile* __restrict__ tiles, int n_tiles,
                     int n_layers, const double* __restrict__ weights, double* __restrict__ normparts) {
     static_assert(sizeof(TI) == 2 && (R == 32 || R == 64), "16-bit leaves, 32 or 64 operands");
-    constexpr int G = 8, C = 16;
+    constexpr int G = 8, C = 16, RUN = R == 32 ? 4 : 8;
     typedef typename Traits<TO>::acc_t out_acc_t;
     const int lane = threadIdx.x;
     const int tile_id = static_cast<int>(blockIdx.x);   // grid: (tile, group)
@@ -1297,9 +1300,10 @@ combine_wide_kernel(const Operands ops, const Outputs outs, const adasum_tile* _
 
     float nacc = 0.f;
     if (lane < s.ng) {
-        float z[G];
+        float part[G];
+        double sum[G];
 #pragma unroll
-        for (int k = 0; k < G; ++k) z[k] = 0.f;
+        for (int k = 0; k < G; ++k) sum[k] = 0.0;
 #pragma unroll 1
         for (int c = 0; c < R / C; ++c) {
             Granule<TI, G> raw[C];
@@ -1307,13 +1311,24 @@ combine_wide_kernel(const Operands ops, const Outputs outs, const adasum_tile* _
             for (int r = 0; r < C; ++r) load_raw(raw[r], static_cast<const TI*>(ops.pack[g * R + c * C + r]) + idx);
 #pragma unroll
             for (int r = 0; r < C; ++r) {
+                if (r % RUN == 0) {
+#pragma unroll
+                    for (int k = 0; k < G; ++k) part[k] = 0.f;
+                }
                 const float w = static_cast<float>(wl[c * C + r]);
                 float v[G];
                 unpack(raw[r], v);
 #pragma unroll
-                for (int k = 0; k < G; ++k) z[k] = fma_t(w, v[k], z[k]);
+                for (int k = 0; k < G; ++k) part[k] = fma_t(w, v[k], part[k]);
+                if (r % RUN == RUN - 1) {
+#pragma unroll
+                    for (int k = 0; k < G; ++k) sum[k] += static_cast<double>(part[k]);
+                }
             }
         }
+        float z[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) z[k] = static_cast<float>(sum[k]);
 #pragma unroll
         for (int k = 0; k < G; ++k) nacc = fma_t(z[k], z[k], nacc);
         store_granule<true>(out + idx, z);
