@@ -256,6 +256,7 @@ struct TileTable {
     int32_t* d_first_in_gram = nullptr;
     int32_t* d_part_begin = nullptr;
     int n_parts = 0;
+    int longest = 0;                      // span tables only: spans of the layer that has most
     // >= 0: the device tables are borrowed (built on the device inside someone else's memory,
     // no host copy, never freed here) and hold this many tiles
     int64_t n_borrowed = -1;
@@ -269,7 +270,13 @@ struct TileTable {
         t.capacity = capacity;
         t.part_begin = d_part_begin;
         t.n_parts = n_parts;
+        t.longest = longest;
         return t;
+    }
+    void make_spans(const int64_t* offsets, int n_layers) {
+        n_parts = wide_part_count(offsets[n_layers]);
+        build_spans(offsets, n_layers, n_parts, tiles, part_begin, layer_begin);
+        for (int l = 0; l < n_layers; ++l) longest = std::max(longest, layer_begin[l + 1] - layer_begin[l]);
     }
     // Both tables are sorted by start and a combine tile never straddles a Gram tile.
     void index_against(const std::vector<adasum_tile>& gram_tiles) {
@@ -457,9 +464,7 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
         const int Kv = order == ADASUM_ORDER_LINEAR ? K : virtual_leaves(p->radices);
         const int64_t small_elems = K > 1 ? find_small_layers(offsets, n_layers, p->small) : 0;
         if (!p->radices.empty() && wide_radix(p->radices[0])) {
-            p->wide_spans.n_parts = wide_part_count(offsets[n_layers]);
-            build_spans(offsets, n_layers, p->wide_spans.n_parts, p->wide_spans.tiles, p->wide_spans.part_begin,
-                        p->wide_spans.layer_begin);
+            p->wide_spans.make_spans(offsets, n_layers);
         }
         p->lay = make_layout(Kv, offsets[n_layers], n_layers, static_cast<int64_t>(p->gram_tiles.tiles.size()),
                              norm_entries_bound(Kv, offsets, n_layers, p->radices, node_type), p->radices, order,
@@ -1324,9 +1329,7 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
         plan.feed = (o.order == ADASUM_ORDER_TREE && !o.fuse && !o.separate && o.delta_start == nullptr) ? 1 : 0;
         // the span table of a wide first pass is small (a few hundred entries): built here, on the host
         if (!plan.radices.empty() && wide_radix(plan.radices[0])) {
-            plan.wide_spans.n_parts = wide_part_count(N);
-            build_spans(layer_offsets, L, plan.wide_spans.n_parts, plan.wide_spans.tiles, plan.wide_spans.part_begin,
-                        plan.wide_spans.layer_begin);
+            plan.wide_spans.make_spans(layer_offsets, L);
         }
         plan.lay = make_layout(Kv, N, L, n_gram, norm_entries_bound(Kv, layer_offsets, L, plan.radices, node_type),
                                plan.radices, o.order, K + 1, small_elems, node_type,

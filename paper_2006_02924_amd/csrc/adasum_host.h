@@ -264,6 +264,7 @@ struct TileSet {
     // span tables (wide first pass) only: device, n_parts + 1
     const int32_t* part_begin = nullptr;
     int n_parts = 0;
+    int longest = 0;        // spans of the layer that has most
 };
 
 // ---- the resident pass (adasum_resident.hip) ----------------------------------
@@ -369,9 +370,10 @@ int launch_norm_coarsen(const double* fine, int n_nodes, const TileSet& ct, cons
                         void* stream);
 // Sums the per-tile partials (and, when !diag, the coarsened squared norms
 // normparts[(group * R + i) * gt.n_tiles + tile] of the operand nodes) into full
-// R x R Gram matrices gram[group][layer][R*R].
+// R x R Gram matrices gram[group][layer][R*R].  (A wide pass's partials of layers of many spans are
+// folded in place first.)
 int launch_gram_finish(bool diag, const TileSet& gt, int n_layers, int n_groups, int R,
-                       const double* partials, const double* normparts, double* gram,
+                       double* partials, const double* normparts, double* gram,
                        double* weights /* or null: step 2b is not done here */, int order, int K_leaves, int depth,
                        void* stream);
 // Gram matrices -> per-layer weights of the binary (or linear) tree over R leaves.

@@ -1210,6 +1210,37 @@ gram_wide_kernel(const Operands ops, const adasum_tile* __restrict__ spans, cons
     }
 }
 
+// A layer of very many spans (one of 8 million elements at K = 33 has 512 of 24 KB) is slow to sum by its one workgroup
+// of the finish: 117 of 381 us.  FIXME
+constexpr int kWideFold = 16;
+__device__ __forceinline__ bool wide_folded(int n_spans_of_layer) { return n_spans_of_layer > 2 * kWideFold; }
+
+template <int NB>
+__global__ void __launch_bounds__(kThreads)
+wide_fold_kernel(double* __restrict__ partials, const adasum_tile* __restrict__ spans,
+                 const int32_t* __restrict__ layer_begin, int n_spans) {
+    constexpr int NPW = NB * 1024;
+    const int sp = static_cast<int>(blockIdx.x);
+    const int l = spans[sp].layer;
+    const int tb = layer_begin[l], te = layer_begin[l + 1];
+    if (!wide_folded(te - tb) || (sp - tb) % kWideFold != 0) return;
+    const int n = te - sp < kWideFold ? te - sp : kWideFold;
+    // block row y: entries of block y % NB of group y / NB (a run is read by the workgroup that writes its first span)
+    double* row = partials + (static_cast<long long>(blockIdx.y / NB) * n_spans + sp) * NPW + blockIdx.y % NB * 1024 + threadIdx.x;
+    double x[4][kWideFold];
+#pragma unroll
+    for (int u = 0; u < kWideFold; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k][u] = row[static_cast<long long>(u < n ? u : n - 1) * NPW + k * kThreads];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        double tot = x[k][0];
+#pragma unroll
+        for (int u = 1; u < kWideFold; ++u) tot += u < n ? x[k][u] : 0.0;
+        row[k * kThreads] = tot;
+    }
+}
+
 // Step 2 after a wide first pass: sums the per-tile blocks of a (group, layer) in a fixed order,
 // spreads them into the full R x R matrix and walks the tree (wave_tree_weights).
 template <int R>
@@ -1231,23 +1262,25 @@ gram_finish_wide_kernel(const double* __restrict__ partials, const int32_t* __re
     // thread tid owns accumulator v = tid / 64 of lane tid % 64 in every block; one workgroup sums all
     // tiles of a layer, so it keeps many loads in flight (branch-free: a tile past the end re-reads the
     // layer's last tile and its value is dropped)
+    // (of a folded layer, the first spans of its runs)
+    const int step = wide_folded(te - tb) ? kWideFold : 1, last = tb + (te - tb - 1) / step * step;
     const double* base = partials + static_cast<long long>(g) * n_tiles * NPW + tid;
     double tots[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) tots[b] = 0.0;
-    for (int t0 = tb; t0 < te; t0 += kAhead) {
+    for (int t0 = tb; t0 < te; t0 += kAhead * step) {
         double x[NB][kAhead];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
-            const int t = t0 + u;
-            const double* row = base + static_cast<long long>(t < te ? t : te - 1) * NPW;
+            const int t = t0 + u * step;
+            const double* row = base + static_cast<long long>(t < te ? t : last) * NPW;
 #pragma unroll
             for (int b = 0; b < NB; ++b) x[b][u] = row[b * 1024];
         }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) tots[b] += (t0 + u < te) ? x[b][u] : 0.0;
+            for (int b = 0; b < NB; ++b) tots[b] += (t0 + u * step < te) ? x[b][u] : 0.0;
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -1975,7 +2008,7 @@ int launch_norm_coarsen(const double* fine, int n_nodes, const TileSet& ct, cons
 }
 
 int launch_gram_finish(bool diag, const TileSet& gt, int n_layers, int n_groups, int R,
-                       const double* partials, const double* normparts, double* gram, double* weights, int order,
+                       double* partials, const double* normparts, double* gram, double* weights, int order,
                        int K_leaves, int depth, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     const long long blocks = static_cast<long long>(n_groups) * n_layers;
@@ -1985,6 +2018,14 @@ int launch_gram_finish(bool diag, const TileSet& gt, int n_layers, int n_groups,
     if (wide_radix(R)) {
         if (!diag) return static_cast<int>(hipErrorInvalidValue);
         const dim3 wgrid(static_cast<unsigned>(blocks)), wblock(1024);
+        if (gt.longest > 2 * kWideFold) {
+            const dim3 fgrid(static_cast<unsigned>(ngt), static_cast<unsigned>(n_groups * wide_blocks(R))), fblock(kThreads);
+            if (fgrid.y > 65535u || R < 32) return static_cast<int>(hipErrorInvalidConfiguration);
+            if (R == 64) hipLaunchKernelGGL((wide_fold_kernel<wide_blocks(64)>), fgrid, fblock, 0, st, partials, gt.tiles, gt.layer_begin, ngt);
+            else hipLaunchKernelGGL((wide_fold_kernel<wide_blocks(32)>), fgrid, fblock, 0, st, partials, gt.tiles, gt.layer_begin, ngt);
+            const int rc = check_launch();
+            if (rc != 0) return rc;
+        }
         if (R == 64)
             hipLaunchKernelGGL((gram_finish_wide_kernel<64>), wgrid, wblock, 0, st, partials, gt.layer_begin, ngt, n_layers,
                                gram, weights, order, K_leaves, depth);

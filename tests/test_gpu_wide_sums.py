@@ -43,3 +43,16 @@ def test_ragged_elements_are_summed_in_64_bits(R, dtype):
         whole = max(0, hi // 8 * 8 - (lo + 7) // 8 * 8)
         eps = 2.0 ** -48 if whole == 0 else 63 * 2.0 ** -24
         assert np.all(np.abs(gram[l] - part @ part.T) <= eps * bound), l
+
+
+@pytest.mark.parametrize("R", [32, 64])
+def test_layers_of_many_spans(R):
+    """Around the number of spans (of 2048 elements here) from which a layer's are folded in runs of 16 first."""
+    print(f"many spans R={R}", flush=True)
+    offs = np.cumsum([0, 5, 32 * 2048 - 5, 33 * 2048, 48 * 2048 + 9, 2048 * 3 - 9, 65 * 2048, 17 * 2048]).tolist()
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    x = (torch.randn(R, offs[-1], device=DEV, generator=gen) + 0.25).to(torch.bfloat16)
+    gram = B.adasum_group_gram([row.clone() for row in x], offs)
+    for l, (lo, hi) in enumerate(zip(offs, offs[1:])):
+        part = x[:, lo:hi].double()
+        assert torch.all((gram[l] - part @ part.T).abs() <= 63 * 2.0 ** -24 * (part.abs() @ part.abs().T)), l
