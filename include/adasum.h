@@ -115,8 +115,10 @@ typedef struct adasum_options {
                                   pass.  Later passes, over fp32 nodes, stay at 16 or less;
                                   0 = library default: 16; 8 for fp64 and the delta form; for bf16
                                   and fp16 inputs of more than 16 workers in the tree order 32 or,
-                                  from 33 workers and 4 million elements on, 64 (16 still where
-                                  only that fits ADASUM_NOALLOC_SCRATCH_BYTES).
+                                  from 33 workers and 4 million elements on (8 million beyond 64
+                                  workers), 64 -- 16 still where only that fits
+                                  ADASUM_NOALLOC_SCRATCH_BYTES, and for 33 to 48 workers with a few
+                                  layers of 0.7 to 3 million elements together.
                                   The result is the same binary tree. */
     int32_t  order;            /* ADASUM_ORDER_TREE (default) | ADASUM_ORDER_LINEAR */
     int32_t  use_graph;        /* 1 = replay the level ladder as one hipGraph launch: captured

@@ -214,10 +214,15 @@ ResidentPlan route_resident(int K, const std::vector<int>& radices, int dtype, b
 //  - The delta form's Gram pass subtracts before it multiplies and so cannot use the packed dot instructions; with 16
 //    operands it runs out of registers, 8 is its fastest radix.  fp64 accumulators are twice as wide: 8 as well.
 //  - 16-bit gradients of more than 16 workers in tree order: a wide first pass, which stores no or fewer nodes and has its
-//    Gram matrix from the matrix cores.  Measured against [16, ...], us: BERT-Large sizes K = 64 16070 -> 13900, a quarter
-//    of them K = 32 2080 -> 1756, ResNet-50 sizes K = 24 537 -> 435, a 64th of them K = 32 138 -> 111.  Beyond 32 workers
-//    one pass of 64 (with 64 rows and a 64 x 64 walk for every layer) pays from some 4 million elements on: K = 64,
-//    5.2 M elements 391 -> 370 with [64] for [32, 2], 1.6 M 225 -> 246.
+//    Gram matrix from the matrix cores.  Measured against [16, ...], us: BERT-Large sizes K = 64 16200 -> 13600, a quarter
+//    of them K = 32 2060 -> 1700, ResNet-50 sizes K = 24 524 -> 434, a 64th of them K = 32 135 -> 105.
+//  - Beyond 32 workers one pass of 64 (with 64 rows and a 64 x 64 walk for every layer) instead of [32, ...] pays from
+//    some 4 million elements on: K = 64, 5.2 M elements in 391 layers 398 -> 364, 3.2 M in 161 layers 287 -> 301.  Beyond
+//    64, where another pass follows either way, from 8 million on: K = 96, 6.4 M in 161 layers 653 -> 683, 8 M in one
+//    660 -> 647.
+//  - With 33 to 48 workers the second pass of [32, 2] costs more than the first saves where neither the bytes nor the
+//    layers are many: K = 33, one layer of 1 M elements 80 us against 71 for [16, 4], four of 500 000 108 against 98; but
+//    57 against 63 at 500 000, 107 against 109 in forty layers of 50 000, 164 against 164 at 3.9 M.
 //  - adasum_reduce_noalloc takes what the radix-16 schedule's tables and workspace fit its scratch for, no more and no
 //    less, and gives the bits that the other entry points give: where that schedule fits and the wide one does not,
 //    it is the default of all of them.
@@ -228,7 +233,9 @@ int default_radix(int K, int order, int dtype, bool delta, bool separate, const 
     *by_wide = Replaced();
     if (delta || dtype == ADASUM_F64) return 8;
     if (K <= kMaxRadix || order != ADASUM_ORDER_TREE || (dtype != ADASUM_BF16 && dtype != ADASUM_F16)) return kDefaultRadix;
-    const int wide = K > 32 && offsets[L] >= kWideElements ? 64 : 32;
+    const int64_t N = offsets[L];
+    if (K > 32 && K <= 48 && N >= 700000 && N < 3000000 && N >= static_cast<int64_t>(L) * 60000) return kDefaultRadix;
+    const int wide = K > 32 && N >= (K > 64 ? 2 * kWideElements : kWideElements) ? 64 : 32;
     std::vector<int> r16, rw;
     if (build_levels(K, kDefaultRadix, r16) != ADASUM_OK || build_levels(K, wide, rw) != ADASUM_OK) return kDefaultRadix;
     const Layout l16 = problem_layout(K, r16, order, dtype, delta, false, separate, offsets, L);

@@ -55,7 +55,8 @@ constexpr int wide_blocks(int R) { return R == 64 ? 3 : 1; }
 // Radix used when the caller asks for 0 (the widest pass of the vector-unit kernels moves the fewest bytes), unless a wide
 // first pass takes its place: default_radix in adasum_api.cpp.
 constexpr int kDefaultRadix = 16;
-constexpr int64_t kWideElements = 4000000;   // from here on more than 32 workers are taken in one pass of 64
+// From here on more than 32 workers are taken in one pass of 64 (from twice as many on, more than 64 in passes of 64).
+constexpr int64_t kWideElements = 4000000;
 
 inline bool known_dtype(int dtype) { return dtype == ADASUM_F32 || dtype == ADASUM_BF16 || dtype == ADASUM_F16 || dtype == ADASUM_F64; }
 // Storage type of the intermediate tree nodes for an input type.

@@ -18,3 +18,25 @@ def test_noalloc_gives_the_same_bits_where_the_resident_pass_does_not_fit_its_sc
     assert torch.equal(out, B.adasum_reduce(w.grads, w.layer_offsets))
     plan = B.Plan(K, w.layer_offsets, dtype)
     assert torch.equal(out, plan.execute(w.grads))
+
+
+@pytest.mark.parametrize("K,sizes,radix", [
+    # few layers of some million elements: [16, 4] is faster than [32, 2] up to 48 workers
+    (33, [1_000_000], 16), (48, [700_000], 16), (48, [699_999], 32), (33, [2_999_999], 16), (33, [3_000_000], 32),
+    (49, [1_000_000], 32), (32, [1_000_000], 32), (40, [60_000] * 20, 16), (40, [60_000] * 19 + [59_999], 32),
+    # beyond 64 workers passes of 64 pay later
+    (65, [7_999_999], 32), (65, [8_000_000], 64), (64, [7_999_999], 64)])
+def test_the_default_where_radices_change_places(K, sizes, radix):
+    """The default is the named schedule bit for bit, and not the other ones."""
+    print(f"default radix K={K} {len(sizes)} layers of {sizes[0]}", flush=True)
+    offs = W.offsets_from_sizes(sizes)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    base = torch.randn(offs[-1], device=DEV, generator=gen)
+    grads = [(base + 0.7 * torch.randn(offs[-1], device=DEV, generator=gen)).to(torch.bfloat16) for _ in range(K)]
+    got = B.adasum_reduce(grads, offs, out_dtype=torch.float32)
+    same = {r: torch.equal(got, B.adasum_reduce(grads, offs, out_dtype=torch.float32, radix=r)) for r in (16, 32, 64)}
+    assert same[radix] and not all(same.values()), same
+    if K <= 32:
+        assert same[64]        # (64 is 32 up to 32 workers)
+    else:
+        assert sum(same.values()) == 1, same
