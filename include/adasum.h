@@ -159,6 +159,12 @@ typedef struct adasum_options {
                                   measurements; the result is the same up to rounding).  A struct_bytes
                                   that ends before this field reads as 0. */
     int32_t  reserved1;        /* must be 0 */
+    int32_t  resident_wait_us; /* microseconds that the workgroups of a layer wait for each other in the resident pass before
+                                  they leave their pieces to its second launch: 0 = 100; 1 .. 10000; -1 = none at all, for
+                                  programs whose other kernels always hold much of the chip, and for tests of that launch.
+                                  The result is the same bit for bit.  A struct_bytes that ends before this field reads
+                                  as 0. */
+    int32_t  reserved2;        /* must be 0 */
 } adasum_options;
 
 /*

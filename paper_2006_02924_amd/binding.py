@@ -55,6 +55,8 @@ class Options(C.Structure):
         ("delta_start", C.c_void_p),
         ("separate_passes", C.c_int32),
         ("reserved1", C.c_int32),
+        ("resident_wait_us", C.c_int32),
+        ("reserved2", C.c_int32),
     ]
 
 
@@ -177,7 +179,7 @@ def _check_inputs(tensors, N):
 def adasum_reduce(grads: Sequence, layer_offsets: Sequence[int], out=None, *, out_dtype=None,
                   radix: int = 0, order: int = ORDER_TREE, layer_stats=None, workspace=None,
                   use_graph: bool = False, delta_start=None, stream=None, noalloc: bool = False,
-                  fuse_siblings: bool = False, separate_passes: bool = False):
+                  fuse_siblings: bool = False, separate_passes: bool = False, resident_wait_us: int = 0):
     """Per-layer Adasum tree of ``grads`` (K device tensors of N elements).
     Returns ``out`` (allocated here when None).  With ``delta_start`` (a tensor
     like one of ``grads``) the tensors in ``grads`` are parameters after a local
@@ -202,7 +204,7 @@ def adasum_reduce(grads: Sequence, layer_offsets: Sequence[int], out=None, *, ou
     ptrs = _ptr_array(grads)
     plain = (out_code == in_code and radix == 0 and order == ORDER_TREE and layer_stats is None
              and workspace is None and not use_graph and delta_start is None and not noalloc
-             and not fuse_siblings and not separate_passes)
+             and not fuse_siblings and not separate_passes and resident_wait_us == 0)
     if plain:
         check(lib.adasum_reduce(ptrs, len(grads), offs, L, in_code, C.c_void_p(out.data_ptr()), _stream(stream)))
         return out
@@ -214,6 +216,7 @@ def adasum_reduce(grads: Sequence, layer_offsets: Sequence[int], out=None, *, ou
     o.use_graph = 1 if use_graph else 0
     o.fuse_siblings = 1 if fuse_siblings else 0
     o.separate_passes = 1 if separate_passes else 0
+    o.resident_wait_us = resident_wait_us
     if workspace is not None:
         o.workspace = workspace.data_ptr()
         o.workspace_bytes = workspace.numel() * workspace.element_size()
@@ -238,7 +241,7 @@ class Plan:
 
     def __init__(self, K: int, layer_offsets: Sequence[int], dtype, *, out_dtype=None, radix: int = 0,
                  order: int = ORDER_TREE, use_graph: bool = False, workspace=None, delta: bool = False,
-                 fuse_siblings: bool = False, separate_passes: bool = False):
+                 fuse_siblings: bool = False, separate_passes: bool = False, resident_wait_us: int = 0):
         lib = load()
         offs, L = _offsets(layer_offsets)
         self.K, self.N, self.n_layers = K, int(layer_offsets[-1]), L
@@ -254,6 +257,7 @@ class Plan:
         o.use_graph = 1 if use_graph else 0
         o.fuse_siblings = 1 if fuse_siblings else 0
         o.separate_passes = 1 if separate_passes else 0
+        o.resident_wait_us = resident_wait_us
         if workspace is not None:
             o.workspace = workspace.data_ptr()
             o.workspace_bytes = workspace.numel() * workspace.element_size()

@@ -59,11 +59,13 @@ struct Opts {
     size_t workspace_bytes;
     double* layer_stats;
     const void* delta_start;
+    int wait_us;     // as given (0: the default)
 };
 
-// adasum_options as it was before delta_start, and before separate_passes, were appended: still accepted.
+// adasum_options as it was before delta_start, separate_passes and resident_wait_us were appended: still accepted.
 constexpr uint32_t kOptionsBytesV1 = offsetof(adasum_options, delta_start);
 constexpr uint32_t kOptionsBytesV2 = offsetof(adasum_options, separate_passes);
+constexpr uint32_t kOptionsBytesV3 = offsetof(adasum_options, resident_wait_us);
 
 int read_opts(const adasum_options* o, int dtype, Opts& r) {
     r.dtype = dtype;
@@ -77,12 +79,17 @@ int read_opts(const adasum_options* o, int dtype, Opts& r) {
     r.workspace_bytes = 0;
     r.layer_stats = nullptr;
     r.delta_start = nullptr;
+    r.wait_us = 0;
     if (o != nullptr) {
         if (o->struct_bytes < kOptionsBytesV1) return ADASUM_ERR_INVALID_ARG;
         if (o->struct_bytes >= kOptionsBytesV2) r.delta_start = o->delta_start;
-        if (o->struct_bytes >= sizeof(adasum_options)) {
+        if (o->struct_bytes >= kOptionsBytesV3) {
             if (o->reserved1 != 0) return ADASUM_ERR_INVALID_ARG;
             r.separate = o->separate_passes != 0;
+        }
+        if (o->struct_bytes >= sizeof(adasum_options)) {
+            if (o->reserved2 != 0 || o->resident_wait_us < -1 || o->resident_wait_us > 10000) return ADASUM_ERR_INVALID_ARG;
+            r.wait_us = o->resident_wait_us;
         }
         if (o->out_dtype >= 0) r.out_dtype = o->out_dtype;
         r.radix = o->radix;
@@ -745,6 +752,7 @@ int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* o
     c.normparts = o.layer_stats ? reinterpret_cast<double*>(ws + lay.off_normparts) : nullptr;
     c.start = o.delta_start;
     c.order = o.order;
+    c.wait_us = o.wait_us == 0 ? kResidentWaitUs : o.wait_us;
     if (o.workspace != nullptr || p->borrowed) {
         // memory that is not the plan's own holds anything
         ADASUM_LAUNCH(launch_zero_words(c.state.epoch, static_cast<int64_t>((lay.total - lay.off_resident) / sizeof(int32_t)), stream));
@@ -1102,7 +1110,7 @@ constexpr size_t kMaxGraphsPerPlan = 8;
 int launch_as_graph(Plan* p, char* ws, const void* const* grads, int dtype, void* out, const Opts& o,
                     void* stream) {
     std::vector<uintptr_t> key;
-    key.reserve(static_cast<size_t>(p->K) + 6);
+    key.reserve(static_cast<size_t>(p->K) + 8);
     for (int k = 0; k < p->K; ++k) key.push_back(reinterpret_cast<uintptr_t>(grads[k]));
     key.push_back(reinterpret_cast<uintptr_t>(out));
     key.push_back(reinterpret_cast<uintptr_t>(ws));
@@ -1111,6 +1119,7 @@ int launch_as_graph(Plan* p, char* ws, const void* const* grads, int dtype, void
     key.push_back(static_cast<uintptr_t>(dtype));
     key.push_back(static_cast<uintptr_t>(o.out_dtype));
     key.push_back(static_cast<uintptr_t>(o.order));
+    key.push_back(static_cast<uintptr_t>(o.wait_us + 1));
     for (auto& g : p->graphs) {
         if (g.key == key) {
             ADASUM_HIP(hipGraphLaunch(g.exec, static_cast<hipStream_t>(stream)));

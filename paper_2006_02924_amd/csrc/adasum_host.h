@@ -278,6 +278,7 @@ struct TileSet {
 // largest layer takes at most half of its workgroups.  More than 8 operands have forms 1 and 3 only (one step of 16
 // operands is 64 KB), and an even number: an odd one repeats an operand with weight 0.
 constexpr int kResidentRadix = 16;       // operands at most
+constexpr int kResidentWaitUs = 100;     // unless the caller says otherwise
 constexpr int kResidentCus = 256;        // compute units the figures are for; not used on fewer
 constexpr int kDirectUnits = 16;         // units of a layer up to which every workgroup reads all partial sums
 constexpr int resident_slots(int form) { return form == 3 ? 2 * kResidentCus : 3 * kResidentCus; }
@@ -328,7 +329,7 @@ void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_
 // What the workgroups of a resident pass share.  All zero before the first pass; every call has a tag of its own.
 struct ResidentState {
     int32_t* epoch;                 // calls so far
-    int32_t* skipped;               // [unit in launch order]: gave up waiting, done by the second launch
+    int32_t* skipped;               // [unit in launch order]: 1 = gave up waiting, 2 = then done by the second launch
     unsigned long long* partials;   // [unit][entry][2]
     unsigned long long* sums;       // [layer][entry][2]
 };
@@ -342,6 +343,7 @@ struct ResidentCall {
     double* normparts;       // or null: [unit]
     const void* start;       // or null: the after-optimizer form
     int order;
+    int wait_us;             // how long units wait for each other (-1: not at all)
 };
 int launch_resident_f32(const ResidentCall& c, void* stream);
 int launch_resident_bf16(const ResidentCall& c, void* stream);

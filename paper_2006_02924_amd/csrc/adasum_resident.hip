@@ -103,16 +103,72 @@ __device__ __forceinline__ bool await(const unsigned long long* p, Words& w, uns
     return true;
 }
 
-constexpr int kSkipScan = 32;            // units a workgroup of the second launch looks at
-#ifndef ADASUM_WAIT_TICKS
-#define ADASUM_WAIT_TICKS 10000
-#endif
-constexpr long long kWaitTicks = ADASUM_WAIT_TICKS;   // of the 100 MHz clock: 100 us
+constexpr int kSkipScan = 4;             // units a workgroup of the second launch looks at
+constexpr int kTicksPerUs = 100;         // of wall_clock64
 
 // 16 bytes per lane straight from memory into LDS (lane l's at dst + 16 l): no registers are held meanwhile.
 [[maybe_unused]] __device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                      (__attribute__((address_space(3))) void*)dst, 16, 0, 2 /* non-temporal */);
+}
+
+// a value of an earlier launch: one ordinary load, through the caches
+__device__ __forceinline__ double read(const unsigned long long* p) {
+    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+    const u64x2 v = *reinterpret_cast<const u64x2*>(p);
+    Words w;
+    w.lo = v.x;
+    w.hi = v.y;
+    return value(w);
+}
+
+// ---- what both launches do with a layer's Gram matrix ----
+// the weights (by one wave; the workgroup waits for these few instructions)
+template <int R>
+__device__ __forceinline__ void unit_weights(const double* shG, double* shW, double* shQ, int order, int leaves, int lane) {
+    __builtin_amdgcn_s_setprio(3);
+    if (order == ADASUM_ORDER_LINEAR) wave_tree_weights<R>(shG, shW, leaves, order, lane);
+    else if ((R & (R - 1)) == 0 && leaves == R) wave_balanced_weights<R>(shG, shW, shQ, lane);
+    else wave_level_weights<R>(shG, shW, shQ, leaves, lane);
+    __builtin_amdgcn_s_setprio(0);
+}
+
+// the combine of one granule of every row (DELTA: the last row is `start`)
+template <typename TI, typename TO, int R, bool DELTA, bool NTS>
+__device__ __forceinline__ void combine_granule(const Granule<TI, Traits<TI>::VEC> (&q)[R + (DELTA ? 1 : 0)],
+                                                const typename Traits<TI>::acc_t (&w)[R], TO* out,
+                                                typename Traits<TI>::acc_t& nacc) {
+    constexpr int G = Traits<TI>::VEC;
+    typedef typename Traits<TI>::acc_t acc_t;
+    acc_t z[G];
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        acc_t sv = 0;
+        if constexpr (DELTA) sv = element<TI>(q[R].w, k);
+        z[k] = w[0] * (DELTA ? element<TI>(q[0].w, k) - sv : element<TI>(q[0].w, k));
+#pragma unroll
+        for (int r = 1; r < R; ++r)
+            z[k] = fma_t(w[r], DELTA ? element<TI>(q[r].w, k) - sv : element<TI>(q[r].w, k), z[k]);
+        nacc = fma_t(z[k], z[k], nacc);
+        if constexpr (DELTA) z[k] += sv;
+    }
+    store_granule<NTS>(out, z);
+}
+
+// one ragged head/tail element: fp64 arithmetic, one rounding at the store; its square is returned
+template <typename TI, typename TO, int R, bool DELTA>
+__device__ __forceinline__ double combine_ragged(const Operands& ops, const TI* start, const double* shW, TO* out, long long idx) {
+    typedef typename Traits<TO>::acc_t out_acc_t;
+    double sd = 0.0;
+    if constexpr (DELTA) sd = static_cast<double>(load_elem(start + idx));
+    double z = shW[0] * (static_cast<double>(load_elem(static_cast<const TI*>(ops.pack[0]) + idx)) - sd);
+#pragma unroll
+    for (int r = 1; r < R; ++r)
+        z = __builtin_fma(shW[r], static_cast<double>(load_elem(static_cast<const TI*>(ops.pack[r]) + idx)) - sd, z);
+    const out_acc_t zs = static_cast<out_acc_t>(z);
+    if constexpr (DELTA) z += sd;
+    store_elem(out + idx, static_cast<out_acc_t>(z));
+    return static_cast<double>(zs) * static_cast<double>(zs);
 }
 
 // One workgroup per unit.  SV steps of 256 granules (16 bytes) of every operand stay in registers, SL in LDS; WPS
@@ -123,13 +179,12 @@ constexpr long long kWaitTicks = ADASUM_WAIT_TICKS;   // of the 100 MHz clock: 1
 // The order of the sums depends on W alone: identical inputs give bit-identical outputs.
 //
 // Waiting is bounded, because nothing promises that a layer's workgroups run side by side (another stream's kernels
-// may hold part of the chip): after 100 us a workgroup marks its unit and ends.  The second launch (`second`) does the
-// marked units from memory, with the same arithmetic -- by then every partial sum is there -- and moves the tag on.
+// may hold part of the chip): after wait_us a workgroup marks its unit and ends; resident_redo_kernel does it then.
 // DELTA: operands are x - start, the result is start + z (the single pass of the after-optimizer form).
 template <typename TI, typename TO, int R, bool DELTA, int SV, int SL, int WPS>
 __global__ void __launch_bounds__(kThreads, WPS)
-resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ units, int n_units, const ResidentState st,
-                int second, double* __restrict__ gram, double* __restrict__ normparts, const TI* start, int order, int leaves) {
+resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ units, const ResidentState st,
+                int wait_us, double* __restrict__ gram, double* __restrict__ normparts, const TI* start, int order, int leaves) {
     constexpr int G = Traits<TI>::VEC;
     constexpr int NP = R * (R + 1) / 2;
     constexpr int NW = kThreads / 64;
@@ -157,32 +212,10 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     __shared__ __align__(16) unsigned char shStage[MFMA ? NW * 16 * 1024 : 16];
     __shared__ __align__(16) unsigned char shKeep[SL > 0 ? SL * RL * kThreads * 16 : 16];
 
-    int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned tag = static_cast<unsigned>(*st.epoch) + 1u;
-
-    int at = static_cast<int>(blockIdx.x);
-    unsigned long long todo = 0;
-    if (second) {
-        const int u0 = static_cast<int>(blockIdx.x) * kSkipScan;
-        int mine = 0;
-        if (lane < kSkipScan && u0 + lane < n_units) mine = st.skipped[u0 + lane];
-        todo = __ballot(mine != 0);
-        __syncthreads();
-        if (mine != 0 && wave == 0) st.skipped[u0 + lane] = 0;
-        if (blockIdx.x == 0 && tid == 0) *st.epoch = static_cast<int32_t>(tag);
-        if (todo == 0) return;
-    }
-    do {
-    // (opaque to the compiler: what follows from the thread's number is not held in registers across the loop, where
-    // the operands need them; without this the pass spills 40 registers and more)
-    asm volatile("" : "+v"(tid));
-    lane = tid & 63;
-    if (second) {
-        const int b = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        at = static_cast<int>(blockIdx.x) * kSkipScan + b;
-    }
+    const int at = static_cast<int>(blockIdx.x);
     const ResidentUnit t = units[at];
     const int W = t.layer_end - t.layer_first;
     adasum_tile tile;
@@ -225,7 +258,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     const long long eidx = lane < s.nh ? s.start + lane : s.ts + (lane - s.nh);
     __builtin_amdgcn_sched_barrier(0);
 
-    if (!second) {
+    {
         if (tid == 0) shSkip = 0;
         // the ragged head and tail are multiplied and summed in fp64
         if (wave == 0 && lane < nedge) {
@@ -356,15 +389,12 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
             if (W > 1) send(st.partials + (static_cast<long long>(t.unit) * NP + tid) * 2, tot, tag);
             else shG[a * R + b] = shG[b * R + a] = tot;
         }
-    } else {
-        if constexpr (SL > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
     }
 
     if (W > 1) {
-        const long long deadline = static_cast<long long>(wall_clock64()) + kWaitTicks;
+        const long long deadline = static_cast<long long>(wall_clock64()) + static_cast<long long>(wait_us) * kTicksPerUs;
         const int tb = t.layer_first, te = t.layer_end;
-        bool ok = true;
+        bool ok = wait_us >= 0;
         // the sum of entry e over the units u0, u0 + step, ... of the layer, a few loads in flight
         auto sum_units = [&](int e, int u0, int step) {
             constexpr int kAhead = R > 8 ? 8 : 4;
@@ -380,8 +410,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
                 for (int k = 0; k < kAhead; ++k) {
                     const int u = u0 + step * k;
                     if (u < te) {
-                        // (in the second launch every sum is there, and the tag may have moved on already)
-                        if (!second) ok = await(st.partials + (static_cast<long long>(u) * NP + e) * 2, x[k], tag, deadline) && ok;
+                        ok = await(st.partials + (static_cast<long long>(u) * NP + e) * 2, x[k], tag, deadline) && ok;
                         v += value(x[k]);
                     }
                 }
@@ -402,18 +431,11 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
             }
         } else {
             unsigned long long* sums = st.sums + static_cast<long long>(t.layer) * (NP * 2);
-            const int e0 = second ? wave : (t.unit - tb) + W * wave, estep = second ? NW : W * NW;
-            for (int e = e0; e < NP; e += estep) {
+            for (int e = (t.unit - tb) + W * wave; e < NP; e += W * NW) {
                 const double v = wave_sum(sum_units(e, tb + lane, 64));
-                if (second) {
-                    int a, b;
-                    entry_to_ij<R, true>(e, a, b);
-                    if (lane == 0) shG[a * R + b] = shG[b * R + a] = v;
-                } else if (__ballot(!ok) == 0) {
-                    if (lane == 0) send(sums + 2 * e, v, tag);
-                }
+                if (__ballot(!ok) == 0 && lane == 0) send(sums + 2 * e, v, tag);
             }
-            if (!second && tid < NP) {
+            if (tid < NP) {
                 Words x = peek(sums + 2 * tid);
                 ok = await(sums + 2 * tid, x, tag, deadline) && ok;
                 int a, b;
@@ -424,17 +446,11 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
         if (!ok) shSkip = 1;
     }
     __syncthreads();
-    if (!second && shSkip) {
+    if (shSkip) {
         if (tid == 0) st.skipped[at] = 1;
         return;
     }
-    if (wave == 0) {
-        __builtin_amdgcn_s_setprio(3);   // (the workgroup waits for these few instructions)
-        if (order == ADASUM_ORDER_LINEAR) wave_tree_weights<R>(shG, shW, leaves, order, lane);
-        else if ((R & (R - 1)) == 0 && leaves == R) wave_balanced_weights<R>(shG, shW, shQ, lane);
-        else wave_level_weights<R>(shG, shW, shQ, leaves, lane);
-        __builtin_amdgcn_s_setprio(0);
-    }
+    if (wave == 0) unit_weights<R>(shG, shW, shQ, order, leaves, lane);
     if (gram != nullptr && t.unit == t.layer_first)   // (for the statistics)
         for (int i = tid; i < R * R; i += kThreads) gram[static_cast<long long>(t.layer) * (R * R) + i] = shG[i];
     __syncthreads();
@@ -445,22 +461,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     acc_t nacc = 0;
     auto combine = [&](const Granule<TI, G> (&q)[RL], int i) {
         const int j = i * kThreads + tid;
-        if (j < s.ng) {
-            const long long idx = s.bs + static_cast<long long>(j) * G;
-            acc_t z[G];
-#pragma unroll
-            for (int k = 0; k < G; ++k) {
-                acc_t sv = 0;
-                if constexpr (DELTA) sv = element<TI>(q[R].w, k);
-                z[k] = w[0] * (DELTA ? element<TI>(q[0].w, k) - sv : element<TI>(q[0].w, k));
-#pragma unroll
-                for (int r = 1; r < R; ++r)
-                    z[k] = fma_t(w[r], DELTA ? element<TI>(q[r].w, k) - sv : element<TI>(q[r].w, k), z[k]);
-                nacc = fma_t(z[k], z[k], nacc);
-                if constexpr (DELTA) z[k] += sv;
-            }
-            store_granule<NTS>(out + idx, z);
-        }
+        if (j < s.ng) combine_granule<TI, TO, R, DELTA, NTS>(q, w, out + s.bs + static_cast<long long>(j) * G, nacc);
     };
 #pragma unroll
     for (int i = 0; i < SV; ++i)
@@ -481,21 +482,9 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
                 combine(q, SV + i);
             }
     }
-    // ragged head/tail elements: fp64 arithmetic, one rounding at the store
     double enorm = 0.0;
     if (nedge > 0 && wave == 0) {
-        if (lane < nedge) {
-            double sd = 0.0;
-            if constexpr (DELTA) sd = static_cast<double>(load_elem(start + eidx));
-            double z = shW[0] * (static_cast<double>(load_elem(operand(0) + eidx)) - sd);
-#pragma unroll
-            for (int r = 1; r < R; ++r)
-                z = __builtin_fma(shW[r], static_cast<double>(load_elem(operand(r) + eidx)) - sd, z);
-            const out_acc_t zs = static_cast<out_acc_t>(z);
-            enorm = static_cast<double>(zs) * static_cast<double>(zs);
-            if constexpr (DELTA) z += sd;
-            store_elem(out + eidx, static_cast<out_acc_t>(z));
-        }
+        if (lane < nedge) enorm = combine_ragged<TI, TO, R, DELTA>(ops, start, shW, out, eidx);
         if (normparts != nullptr) enorm = wave_sum(enorm);
     }
     if (normparts != nullptr) {
@@ -510,34 +499,165 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
             normparts[t.unit] = tot;
         }
     }
-    if (second) __syncthreads();
-    } while (second && todo != 0);
+}
+
+// The second launch: the units that gave up waiting, from memory, with the same arithmetic in the same order (by now
+// every partial sum is there), and the tag moves on.  A workgroup looks at every gridDim.x-th unit: a layer's units
+// follow each other and tend to give up together.  Usually there is nothing to do, and the launch costs 1 .. 2 us; where
+// every unit gave up FIXME.
+template <typename TI, typename TO, int R, bool DELTA>
+__global__ void __launch_bounds__(kThreads)
+resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ units, int n_units, const ResidentState st,
+                     double* __restrict__ gram, double* __restrict__ normparts, const TI* start, int order, int leaves) {
+    constexpr int G = Traits<TI>::VEC;
+    constexpr int NP = R * (R + 1) / 2;
+    constexpr int NW = kThreads / 64;
+    constexpr int ROWS = kThreads / NP;
+    constexpr int RL = R + (DELTA ? 1 : 0);
+    typedef typename Traits<TI>::acc_t acc_t;
+    constexpr bool NTS = !(sizeof(TI) == 2 && sizeof(TO) == 4 && R <= 2);   // as combine_kernel
+    __shared__ double shR[ROWS * NP];
+    __shared__ double shG[R * R];
+    __shared__ double shW[R];
+    __shared__ double shQ[4 * R];
+    __shared__ double shNorm[NW];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int mine = static_cast<int>(blockIdx.x) + (lane % kSkipScan) * static_cast<int>(gridDim.x);
+    const bool redo = lane < kSkipScan && mine < n_units && st.skipped[mine] == 1;
+    unsigned long long todo = __ballot(redo);
+    __syncthreads();
+    if (redo && wave == 0) st.skipped[mine] = 2;
+    if (blockIdx.x == 0 && tid == 0) *st.epoch = *st.epoch + 1;
+    while (todo != 0) {
+        const int b = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const ResidentUnit t = units[static_cast<int>(blockIdx.x) + b * static_cast<int>(gridDim.x)];
+        adasum_tile tile;
+        tile.start = t.start;
+        tile.len = t.len;
+        tile.layer = t.layer;
+        const Split s = split_tile<G>(tile);
+        const int tb = t.layer_first, te = t.layer_end;
+        auto partial = [&](int u, int e) { return st.partials + (static_cast<long long>(u) * NP + e) * 2; };
+        if (te - tb <= kDirectUnits) {
+            constexpr int kMost = (kDirectUnits + ROWS - 1) / ROWS;
+            const int row = tid / NP, e = tid % NP;
+            double x[kMost], v = 0.0;
+#pragma unroll
+            for (int k = 0; k < kMost; ++k) x[k] = read(partial(tb + row + k * ROWS < te ? tb + row + k * ROWS : te - 1, e));
+#pragma unroll
+            for (int k = 0; k < kMost; ++k)
+                if (tb + row + k * ROWS < te) v += x[k];
+            if (row < ROWS) shR[row * NP + e] = v;
+            __syncthreads();
+            if (tid < NP) {
+                double tot = shR[tid];
+#pragma unroll
+                for (int k = 1; k < ROWS; ++k) tot += shR[k * NP + tid];
+                int i, j;
+                entry_to_ij<R, true>(tid, i, j);
+                shG[i * R + j] = shG[j * R + i] = tot;
+            }
+        } else {
+            // a few entries and rounds of units in flight at a time: a lane adds its units, then the wave its lanes
+            constexpr int EA = 4, UA = 4;
+            for (int e0 = wave * EA; e0 < NP; e0 += NW * EA) {
+                double v[EA];
+#pragma unroll
+                for (int k = 0; k < EA; ++k) v[k] = 0.0;
+                for (int u0 = tb + lane; u0 < te; u0 += 64 * UA) {
+                    double x[UA][EA];
+#pragma unroll
+                    for (int i = 0; i < UA; ++i)
+#pragma unroll
+                        for (int k = 0; k < EA; ++k)
+                            x[i][k] = read(partial(u0 + 64 * i < te ? u0 + 64 * i : te - 1, e0 + k < NP ? e0 + k : NP - 1));
+#pragma unroll
+                    for (int i = 0; i < UA; ++i)
+                        if (u0 + 64 * i < te) {
+#pragma unroll
+                            for (int k = 0; k < EA; ++k) v[k] += x[i][k];
+                        }
+                }
+#pragma unroll
+                for (int k = 0; k < EA; ++k) {
+                    const double tot = wave_sum(v[k]);
+                    int i, j;
+                    entry_to_ij<R, true>(e0 + k < NP ? e0 + k : NP - 1, i, j);
+                    if (lane == 0 && e0 + k < NP) shG[i * R + j] = shG[j * R + i] = tot;
+                }
+            }
+        }
+        __syncthreads();
+        if (wave == 0) unit_weights<R>(shG, shW, shQ, order, leaves, lane);
+        if (gram != nullptr && t.unit == t.layer_first)
+            for (int i = tid; i < R * R; i += kThreads) gram[static_cast<long long>(t.layer) * (R * R) + i] = shG[i];
+        __syncthreads();
+        acc_t w[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[r] = static_cast<acc_t>(shW[r]);
+        acc_t nacc = 0;
+        for (int j = tid; j < s.ng; j += kThreads) {
+            const long long idx = s.bs + static_cast<long long>(j) * G;
+            Granule<TI, G> q[RL];
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_raw(q[r], static_cast<const TI*>(ops.pack[r]) + idx);
+            if constexpr (DELTA) load_raw(q[R], start + idx);
+            combine_granule<TI, TO, R, DELTA, NTS>(q, w, out + idx, nacc);
+        }
+        const int nedge = s.nh + s.nt;
+        double enorm = 0.0;
+        if (nedge > 0 && wave == 0) {
+            if (lane < nedge)
+                enorm = combine_ragged<TI, TO, R, DELTA>(ops, start, shW, out, lane < s.nh ? s.start + lane : s.ts + (lane - s.nh));
+            if (normparts != nullptr) enorm = wave_sum(enorm);
+        }
+        if (normparts != nullptr) {
+            const acc_t ws = wave_sum(nacc);
+            if (lane == 0) shNorm[wave] = static_cast<double>(ws);
+            __syncthreads();
+            if (tid == 0) {
+                double tot = shNorm[0];
+#pragma unroll
+                for (int k = 1; k < NW; ++k) tot += shNorm[k];
+                if (nedge > 0) tot += enorm;
+                normparts[t.unit] = tot;
+            }
+        }
+        __syncthreads();   // (the next unit's sums go through the same memory)
+    }
 }
 
 template <typename TI, typename TO, int R, bool DELTA, int SV, int SL, int WPS>
 int launch_s(const ResidentCall& c, hipStream_t stream) {
-    for (int second = 0; second < 2; ++second) {
-        const int blocks = second ? (c.n_units + kSkipScan - 1) / kSkipScan : c.n_units;
-        hipLaunchKernelGGL((resident_kernel<TI, TO, R, DELTA, SV, SL, WPS>), dim3(static_cast<unsigned>(blocks)),
-                           dim3(kThreads), 0, stream, c.ops, static_cast<TO*>(c.out), c.units, c.n_units, c.state, second,
-                           c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return static_cast<int>(e);
-    }
-    return 0;
+    hipLaunchKernelGGL((resident_kernel<TI, TO, R, DELTA, SV, SL, WPS>), dim3(static_cast<unsigned>(c.n_units)),
+                       dim3(kThreads), 0, stream, c.ops, static_cast<TO*>(c.out), c.units, c.state, c.wait_us,
+                       c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves);
+    return static_cast<int>(hipGetLastError());
+}
+
+template <typename TI, typename TO, int R, bool DELTA>
+int launch_redo(const ResidentCall& c, hipStream_t stream) {
+    hipLaunchKernelGGL((resident_redo_kernel<TI, TO, R, DELTA>), dim3(static_cast<unsigned>((c.n_units + kSkipScan - 1) / kSkipScan)),
+                       dim3(kThreads), 0, stream, c.ops, static_cast<TO*>(c.out), c.units, c.n_units, c.state,
+                       c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves);
+    return static_cast<int>(hipGetLastError());
 }
 
 template <typename TI, typename TO, int R, bool DELTA>
 int launch_r(const ResidentCall& c, hipStream_t stream) {
     constexpr int D = DtypeOf<TI>::value;
-    switch (c.form) {
-        case 1: return launch_s<TI, TO, R, DELTA, 1, 0, 2>(c, stream);
-        case 2:
-            if constexpr (R > 8) return static_cast<int>(hipErrorInvalidValue);
-            else return launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 2), resident_lds_steps(D, R, DELTA, 2), 3>(c, stream);
-        case 3: return launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 3), resident_lds_steps(D, R, DELTA, 3), 2>(c, stream);
-        default: return static_cast<int>(hipErrorInvalidValue);
+    int e = static_cast<int>(hipErrorInvalidValue);
+    if (c.form == 1) e = launch_s<TI, TO, R, DELTA, 1, 0, 2>(c, stream);
+    if constexpr (R <= 8) {
+        if (c.form == 2)
+            e = launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 2), resident_lds_steps(D, R, DELTA, 2), 3>(c, stream);
     }
+    if (c.form == 3)
+        e = launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 3), resident_lds_steps(D, R, DELTA, 3), 2>(c, stream);
+    return e != 0 ? e : launch_redo<TI, TO, R, DELTA>(c, stream);
 }
 
 template <typename TI, typename TO, bool DELTA>
