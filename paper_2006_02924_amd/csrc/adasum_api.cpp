@@ -511,7 +511,7 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
         if (rc != ADASUM_OK) return rc;
         try {
             std::vector<ResidentUnit> units;
-            order_units(p->unit_tiles.tiles, p->unit_tiles.layer_begin, p->resident.form, units);
+            order_units(p->unit_tiles.tiles, p->unit_tiles.layer_begin, resident_slots(dtype, p->resident.R, p->resident.form), units);
             const size_t bytes = units.size() * sizeof(ResidentUnit);
             ADASUM_HIP(hipMalloc(reinterpret_cast<void**>(&p->d_units), bytes));
             ADASUM_HIP(hipMemcpy(p->d_units, units.data(), bytes, hipMemcpyHostToDevice));

@@ -271,35 +271,44 @@ struct TileSet {
 // ---- the resident pass (adasum_resident.hip) ----------------------------------
 //
 // How much a workgroup keeps (16-byte granules per lane and operand, in registers and in LDS) and how many workgroups
-// a compute unit holds.  Form 1: one granule, for problems that the chip holds at once in such pieces (latency counts).
-// Form 2: three workgroups per compute unit; form 3: two, which keep more.  Smaller units overlap better (K = 2 bf16,
-// ResNet-50 sizes: 40 us in form 2, 62 in form 3; K = 6 binary16: 115 and 121), but a layer that takes most of the chip
-// stalls it (K = 8 fp32, whose largest layers have 75 of 84 MB: 260 us in form 2, 217 in form 3): form 2 while the
-// largest layer takes at most half of its workgroups.  More than 8 operands have forms 1 and 3 only (one step of 16
-// operands is 64 KB), and an even number: an odd one repeats an operand with weight 0.
+// a compute unit holds.  Form 1: one granule, for problems that the chip holds at once in such pieces (latency counts)
+// and for tables of tiny layers.  Form 2: three workgroups per compute unit; form 3: two, which keep more.  Smaller units
+// overlap better (K = 2 bf16, ResNet-50 sizes: 40 us in form 2, 62 in form 3; K = 6 binary16: 115 and 121), but a layer
+// that takes most of the chip stalls it (K = 8 fp32, whose largest layers have 75 of 84 MB: 260 us in form 2, 217 in
+// form 3): form 2 while the largest layer takes at most half of its workgroups.  More than 8 operands have forms 1 and 3
+// only (one step of 16 operands is 64 KB), and an even number: an odd one repeats an operand with weight 0.
+// plan_resident has the rules.
 constexpr int kResidentRadix = 16;       // operands at most
 constexpr int kResidentWaitUs = 100;     // unless the caller says otherwise
 constexpr int kResidentCus = 256;        // compute units the figures are for; not used on fewer
 constexpr int kDirectUnits = 16;         // units of a layer up to which every workgroup reads all partial sums
-constexpr int resident_slots(int form) { return form == 3 ? 2 * kResidentCus : 3 * kResidentCus; }
+// More than 8 operands of a 16-bit type: the Gram matrix on the matrix cores, which takes few registers and 64 KB of LDS.
+constexpr bool resident_matrix(int dtype, int R) { return R > 8 && (dtype == ADASUM_BF16 || dtype == ADASUM_F16); }
+constexpr int resident_per_cu(int dtype, int R, int form) { return form == 3 || resident_matrix(dtype, R) ? 2 : 3; }
+constexpr int resident_slots(int dtype, int R, int form) { return resident_per_cu(dtype, R, form) * kResidentCus; }
 // units of a layer at most: its workgroups must be on the chip together
-constexpr int resident_most(int form) { return form == 3 ? resident_slots(3) - 12 : resident_slots(form) / 2; }
+constexpr int resident_most(int dtype, int R, int form) {
+    return form == 3 ? resident_slots(dtype, R, 3) - 12 : resident_slots(dtype, R, form) / 2;
+}
 constexpr int resident_register_steps(int dtype, int R, bool delta, int form) {
-    // (16-bit operands, more than 8: the Gram matrix takes few registers and the LDS)
-    const bool matrix = R > 8 && (dtype == ADASUM_BF16 || dtype == ADASUM_F16);
-    const int rows = form == 2 ? 24 : matrix ? 48 : dtype == ADASUM_F64 || R > 8 ? 32 : 40;
-    const int steps = rows / (R + (delta ? 1 : 0));
+    const int rows = R + (delta ? 1 : 0);
+    // (form 2 has 168 registers: 24 rows of 4, but 16 where the sums of 8 rows, or of 7 in fp64, would spill: K = 8 fp64, a
+    // quarter of ResNet-50, 229 -> 126 us, K = 8 bf16, ResNet-50 sizes, 149 -> 125)
+    const int kept = form == 2 ? (rows == 8 || (rows >= 7 && dtype == ADASUM_F64) ? 16 : 24)
+                     : resident_matrix(dtype, R) ? 48 : dtype == ADASUM_F64 || R > 8 ? 32 : 40;
+    const int steps = kept / rows;
     return steps < 16 ? (steps < 1 ? 1 : steps) : 16;
 }
 constexpr int resident_lds_steps(int dtype, int R, bool delta, int form) {
-    if (R > 8 && (dtype == ADASUM_BF16 || dtype == ADASUM_F16)) return 0;
+    if (resident_matrix(dtype, R)) return 0;
     const int steps = (form == 2 ? 12 : 18) / (R + (delta ? 1 : 0));
     return steps < 8 ? steps : 8;
 }
-constexpr int resident_capacity(int dtype, int R, bool delta, int form) {
-    const int steps = form == 1 ? 1 : resident_register_steps(dtype, R, delta, form) + resident_lds_steps(dtype, R, delta, form);
-    return kThreads * steps * (dtype == ADASUM_F64 ? 2 : dtype == ADASUM_F32 ? 4 : 8);
+// Steps of 256 granules a unit of a form has at most, and the elements of a step.
+constexpr int resident_steps(int dtype, int R, bool delta, int form) {
+    return form == 1 ? 1 : resident_register_steps(dtype, R, delta, form) + resident_lds_steps(dtype, R, delta, form);
 }
+constexpr int resident_step_elems(int dtype) { return kThreads * (dtype == ADASUM_F64 ? 2 : dtype == ADASUM_F32 ? 4 : 8); }
 // Operands a resident kernel is instantiated for that holds a group of `leaves`.
 constexpr int resident_operands(int leaves) { return leaves <= 8 ? leaves : (leaves + 1) / 2 * 2; }
 
@@ -322,8 +331,8 @@ struct ResidentUnit {
     int32_t layer_first, layer_end;    // its layer's units
     int32_t pad;
 };
-// The units in launch order, from the tile table of the plan's capacity.
-void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int form,
+// The units in launch order, from the tile table of the plan's capacity (slots: workgroups that the chip holds).
+void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int slots,
                  std::vector<ResidentUnit>& units);
 
 // What the workgroups of a resident pass share.  All zero before the first pass; every call has a tag of its own.

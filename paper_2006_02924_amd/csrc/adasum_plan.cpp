@@ -254,22 +254,72 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
     if (radices.size() != 1 || K < 2 || K > kResidentRadix || layer_offsets[n_layers] == 0) return p;
     p.R = resident_operands(K);
     if (p.R > 8 && (delta || dtype == ADASUM_F64)) return p;
-    auto fits = [&](int form) {
-        const int64_t cap = resident_capacity(dtype, p.R, delta, form);
-        int64_t most = 0, all = 0;
+    const int64_t N = layer_offsets[n_layers];
+    const int64_t step = resident_step_elems(dtype);
+    int64_t layers = 0;
+    for (int l = 0; l < n_layers; ++l) layers += layer_offsets[l + 1] > layer_offsets[l];
+    struct Count {
+        int64_t most = 0, all = 0;   // units of the layer that has most, and of all
+    };
+    auto count = [&](int64_t cap) {
+        Count c;
         for (int l = 0; l < n_layers; ++l) {
             const int64_t lo = layer_offsets[l], hi = layer_offsets[l + 1];
             const int64_t n = hi > lo ? (hi - 1) / cap - lo / cap + 1 : 0;
-            most = std::max(most, n);
-            all += n;
+            c.most = std::max(c.most, n);
+            c.all += n;
         }
-        if (most > resident_most(form) || all > (form == 1 ? resident_slots(1) : 0x7fffffff)) return false;
+        return c;
+    };
+    auto take = [&](int form, int64_t cap, const Count& c) {
         p.form = form;
         p.capacity = static_cast<int>(cap);
-        p.n_units = all;
-        return true;
+        p.n_units = c.all;
     };
-    if (!fits(1) && !(p.R <= 8 && fits(2))) fits(3);
+    const Count one = count(step);
+    if (one.all > 0x7fffffff) return p;
+    if (one.most <= resident_most(dtype, p.R, 1) && one.all <= resident_slots(dtype, p.R, 1)) {
+        take(1, step, one);
+        return p;
+    }
+    for (int form = p.R <= 8 ? 2 : 3; form <= 3; ++form) {
+        const int steps = resident_steps(dtype, p.R, delta, form), slots = resident_slots(dtype, p.R, form);
+        const Count full = count(step * steps);
+        if (full.most > resident_most(dtype, p.R, form)) continue;
+        // Tables of tiny layers: hardly more units in form 1, which holds more workgroups (K = 2 bf16, 20000 layers of 100 to
+        // 300 elements: 43 us, in form 2 95; 600 layers of 1 to 20000: 24 and 28).
+        if (one.all <= 2 * full.all && one.most <= kDirectUnits) {
+            take(1, step, one);
+            return p;
+        }
+        // As small units as the chip still holds all at once, so that more of it is at work (K = 2 bf16, one layer of 900 000
+        // elements in 220 units instead of 25: 15.8 us for 20.3).
+        if (layers < slots)
+            for (int64_t n = std::max<int64_t>(1, (N + step * (slots - layers) - 1) / (step * (slots - layers))); n < steps; ++n) {
+                const Count c = count(step * n);
+                if (c.all > slots || c.most > resident_most(dtype, p.R, form)) continue;
+                take(form, step * n, c);
+                return p;
+            }
+        // Layers of a little more than half the chip run alone on it, and the rest of it waits with them.  Where such layers
+        // hold most of a table, the other passes are faster: 20 layers of 300 units each, us for this pass and for those,
+        // K = 16 fp32 511 and 416, K = 16 bf16 452 and 419, K = 2 bf16 507 and 460 (fp32 and fp64 of at most 8 rows stay
+        // ahead: K = 8 fp32 431 and 472); of 370 units, K = 16 fp32 583 and 500, K = 16 bf16 515 and 513.  Two layers of 300:
+        // 58 and 81, 53 and 71, 57 and 55.
+        if (form == 3 && (p.R > 8 || dtype == ADASUM_BF16 || dtype == ADASUM_F16)) {
+            int64_t alone = 0, units = 0;
+            for (int l = 0; l < n_layers; ++l) {
+                const int64_t lo = layer_offsets[l], hi = layer_offsets[l + 1], cap = step * steps;
+                const int64_t n = hi > lo ? (hi - 1) / cap - lo / cap + 1 : 0;
+                if (n <= slots / 2 || n > (dtype == ADASUM_F32 && p.R >= 12 ? slots * 9 / 10 : slots * 7 / 10)) continue;
+                ++alone;
+                units += n;
+            }
+            if (alone >= 5 && 2 * units > full.all) return p;
+        }
+        take(form, step * steps, full);
+        return p;
+    }
     return p;
 }
 
@@ -284,13 +334,13 @@ void add_resident(Layout& lay, const ResidentPlan& p) {
     lay.need = lay.total = off;
 }
 
-void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int form,
+void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int slots,
                  std::vector<ResidentUnit>& units) {
     // A layer's units wait for each other, so they should be on the chip together: whole layers are packed into runs of
     // half the workgroups that the chip holds (a larger layer into a run of all of them), the largest that still fits
     // next; the runs with the largest layers last.  In element order, units at the seams of such runs waited a whole
     // run's time: K = 8 fp32, ResNet-50 sizes, 271 us; in this order 232.
-    const int L = static_cast<int>(layer_begin.size()) - 1, slots = resident_slots(form);
+    const int L = static_cast<int>(layer_begin.size()) - 1;
     auto count = [&](int l) { return layer_begin[l + 1] - layer_begin[l]; };
     std::vector<int> by_size;
     for (int l = 0; l < L; ++l)

@@ -195,7 +195,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     constexpr int SWEEPS = (NP + 59) / 60;
     constexpr int NA = (NP + SWEEPS - 1) / SWEEPS;
     // more than 8 operands of a 16-bit type: the Gram matrix on the matrix cores (gram_step below)
-    constexpr bool MFMA = sizeof(TI) == 2 && R > 8;
+    constexpr bool MFMA = resident_matrix(DtypeOf<TI>::value, R);
     typedef typename Traits<TI>::acc_t acc_t;
     typedef typename Traits<TO>::acc_t out_acc_t;
     constexpr bool NTS = !(sizeof(TI) == 2 && sizeof(TO) == 4 && R <= 2);   // as combine_kernel
@@ -211,6 +211,10 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     __shared__ int shSkip;
     __shared__ __align__(16) unsigned char shStage[MFMA ? NW * 16 * 1024 : 16];
     __shared__ __align__(16) unsigned char shKeep[SL > 0 ? SL * RL * kThreads * 16 : 16];
+
+    // (WPS workgroups of the planner's count fit a compute unit: registers by the launch bounds, LDS here)
+    static_assert(WPS * (sizeof(shP) + sizeof(shR) + sizeof(shEdge) + sizeof(shG) + sizeof(shW) + sizeof(shQ) + sizeof(shNorm) +
+                         sizeof(shSkip) + sizeof(shStage) + sizeof(shKeep) + 1280) <= 160 * 1024, "");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -650,13 +654,13 @@ template <typename TI, typename TO, int R, bool DELTA>
 int launch_r(const ResidentCall& c, hipStream_t stream) {
     constexpr int D = DtypeOf<TI>::value;
     int e = static_cast<int>(hipErrorInvalidValue);
-    if (c.form == 1) e = launch_s<TI, TO, R, DELTA, 1, 0, 2>(c, stream);
+    if (c.form == 1) e = launch_s<TI, TO, R, DELTA, 1, 0, resident_per_cu(D, R, 1)>(c, stream);
     if constexpr (R <= 8) {
         if (c.form == 2)
-            e = launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 2), resident_lds_steps(D, R, DELTA, 2), 3>(c, stream);
+            e = launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 2), resident_lds_steps(D, R, DELTA, 2), resident_per_cu(D, R, 2)>(c, stream);
     }
     if (c.form == 3)
-        e = launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 3), resident_lds_steps(D, R, DELTA, 3), 2>(c, stream);
+        e = launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 3), resident_lds_steps(D, R, DELTA, 3), resident_per_cu(D, R, 3)>(c, stream);
     return e != 0 ? e : launch_redo<TI, TO, R, DELTA>(c, stream);
 }
 

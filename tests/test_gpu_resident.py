@@ -14,7 +14,7 @@ LANES = 256                                   # granules of a step
 
 
 def unit_elements(K, dtype, form, delta=False):
-    """Elements of a full unit (adasum_host.h: resident_capacity)."""
+    """Elements of a full unit (adasum_host.h: resident_steps)."""
     vec = 16 // torch.empty(0, dtype=dtype).element_size()
     rows = K + (1 if delta else 0)
     if form == 1:
@@ -22,7 +22,8 @@ def unit_elements(K, dtype, form, delta=False):
     if K > 8:
         rows = (K + 1) // 2 * 2
     matrix = K > 8 and vec == 8
-    registers = {2: 24, 3: 48 if matrix else 32 if dtype == torch.float64 or K > 8 else 40}[form]
+    short = rows == 8 or (rows >= 7 and dtype == torch.float64)
+    registers = {2: 16 if short else 24, 3: 48 if matrix else 32 if dtype == torch.float64 or K > 8 else 40}[form]
     steps = max(1, min(16, registers // rows)) + (0 if matrix else min(8, {2: 12, 3: 18}[form] // rows))
     return LANES * vec * steps
 

@@ -1,11 +1,11 @@
 """Units of the resident pass that give up waiting for their layer's others are done by its second launch, with the same
 bits.  The wait is set from the host: none at all sends every unit of a layer of several through that launch."""
-import numpy as np
 import pytest
 import torch
 
 from paper_2006_02924_amd import binding as B
 from paper_2006_02924_amd import workloads as W
+from tests.resident_util import steps_and_layers
 from tests.test_gpu_resident import unit_elements, workload
 
 pytestmark = pytest.mark.gpu
@@ -14,26 +14,27 @@ CODE = {torch.float32: B.F32, torch.bfloat16: B.BF16, torch.float16: B.F16, torc
 
 
 class Shape:
+    """Layers of one unit, two, the most that exchange directly, more; ragged ends; in forms 2 and 3 more
+    of them than the chip holds at once, so that the units are as large as the form has them."""
+
     def __init__(self, K, dtype, form, delta=False):
         self.K, self.dtype, self.delta = K, dtype, delta
         vec = 16 // torch.empty(0, dtype=dtype).element_size()
-        u = self.unit = unit_elements(K, dtype, form, delta)
-        # one unit, two, the most that exchange directly, more; ragged ends
+        u = unit_elements(K, dtype, form, delta)
         self.sizes = [7, u - 7, u + vec + 3, 0, 16 * u - vec, 17 * u + 5, 33, 70 * u]
-        if form == 2:      # more units of one step than the chip holds at once
-            self.sizes.append(max(0, 769 * unit_elements(K, dtype, 1, delta) - sum(self.sizes)) + 7)
+        if form == 2:
+            self.sizes += [300 * u + 1, 300 * u]
         elif form == 3 and K <= 8:    # a layer of more than half the units of form 2
-            self.sizes.append(385 * unit_elements(K, dtype, 2, delta) + 3)
+            self.sizes += [385 * unit_elements(K, dtype, 2, delta) + 3, 200 * u]
         elif form == 3:
-            self.sizes.append(max(0, 769 * unit_elements(K, dtype, 1) - sum(self.sizes)) + 7)
+            self.sizes += [200 * u + 1, 250 * u]
         self.offs = W.offsets_from_sizes(self.sizes)
-        per_layer = np.bincount(B.plan_tiles(self.offs, u)["layer"], minlength=len(self.sizes))
+        steps, per_layer = steps_and_layers(K, self.offs, CODE[dtype], delta=delta)
         self.units, self.waiting = int(per_layer.sum()), int(per_layer[per_layer > 1].sum())
         self.base = B.adasum_workspace_bytes(K, self.offs, CODE[dtype], delta=delta, separate_passes=True)
         need = B.adasum_workspace_bytes(K, self.offs, CODE[dtype], delta=delta)
-        assert need > self.base                       # (taken as a resident pass)
         self.workspace = torch.full((need,), 0x5a, dtype=torch.uint8, device=DEV)
-        print(f"give up: K={K} {dtype} form {form}, {self.units} units, {self.waiting} in layers of several", flush=True)
+        print(f"give up: K={K} {dtype} form {form}, {steps} steps, {self.units} units, {self.waiting} in layers of several", flush=True)
 
     def redone(self):
         """Units that the second launch did in the call before (the state begins where the other passes' sections end:

@@ -5,6 +5,7 @@ import pytest
 
 from paper_2006_02924_amd import binding as B
 from paper_2006_02924_amd import workloads as W
+from tests.resident_util import steps_and_layers, unit_count
 
 
 def noalloc(lib, K, offs, dtype):
@@ -33,3 +34,46 @@ def test_the_resident_pass_is_taken_by_every_entry_point_or_none(K, dtype, sizes
 def test_what_fits_without_allocation_does_not_depend_on_the_route(lib, K, dtype, sizes):
     """The tables of a resident pass are the smaller ones here and would fit; those of the other passes do not."""
     assert noalloc(lib, K, W.offsets_from_sizes(sizes), dtype) == B.ERR_TOO_LARGE
+
+
+def steps(K, sizes, dtype, **kw):
+    return steps_and_layers(K, W.offsets_from_sizes(sizes), dtype, **kw)
+
+
+def test_units_are_as_small_as_the_chip_holds_at_once():
+    # (one granule a lane: at most half of 768 for one layer)
+    n, units = steps(2, [384 * 2048], B.BF16)
+    assert (n, units.max()) == (1, 384)
+    n, units = steps(2, [900_000], B.BF16)
+    assert n == 2 and units.max() == 220
+    n, units = steps(2, [10_000_000], B.BF16)
+    assert units.max() <= 384 and 1 < n < 18
+    n, units = steps(2, [10_000_000] * 5, B.BF16)
+    assert n == 18 and units.sum() > 768
+    # more than 8 operands of a 16-bit type: 512 workgroups, 256 for one layer
+    n, units = steps(12, [250_000, 250_000, 500_000], B.BF16)
+    assert (n, units.sum()) == (1, 491)
+    n, units = steps(12, [250_000, 250_000, 600_000], B.BF16)
+    assert n == 2
+    n, units = steps(12, [250_000] * 7, B.F32)
+    assert n == 3 and units.sum() > 512
+
+
+def test_tables_of_tiny_layers_take_the_smallest_units():
+    assert steps(2, [200] * 20_000, B.BF16)[0] == 1
+    assert steps(8, [700] * 4_000, B.F64)[0] == 1
+    assert steps(2, [200] * 2_000 + [3_000_000], B.BF16)[0] > 1        # (a layer that would have 1465 of them)
+
+
+@pytest.mark.parametrize("K,dtype,unit", [(16, B.F32, 3072), (16, B.BF16, 6144), (2, B.BF16, 24 * 2048)])
+def test_many_layers_that_each_leave_the_chip_half_idle_take_the_other_passes(K, dtype, unit):
+    assert unit_count(K, W.offsets_from_sizes([300 * unit] * 5), dtype) == 0
+    assert unit_count(K, W.offsets_from_sizes([300 * unit] * 4), dtype)
+    assert unit_count(K, W.offsets_from_sizes([200 * unit] * 5), dtype)
+    assert unit_count(K, W.offsets_from_sizes([(470 if dtype == B.F32 else 400) * unit] * 5), dtype)
+    assert bool(unit_count(K, W.offsets_from_sizes([400 * unit] * 5), dtype)) == (dtype != B.F32)
+    assert unit_count(K, W.offsets_from_sizes([300 * unit] * 5 + [200 * unit] * 9), dtype)
+
+
+def test_fp32_of_few_rows_stays():
+    assert unit_count(8, W.offsets_from_sizes([300 * 7168] * 20), B.F32)
