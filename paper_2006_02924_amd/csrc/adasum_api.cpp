@@ -256,6 +256,25 @@ int default_radix(int K, int order, int dtype, bool delta, bool separate, const 
     return wide;
 }
 
+// What a plan with the resident pass and a wide default needs of a caller's workspace.
+int whole_workspace(int K, const Opts& o, int dtype, const int64_t* offsets, int L, size_t* bytes) {
+    try {
+        std::vector<int> radices;
+        const bool delta = o.delta_start != nullptr;
+        Replaced replaced;
+        const int radix = o.radix != 0 ? o.radix : default_radix(K, o.order, dtype, delta, o.separate != 0, offsets, L, &replaced);
+        const int rc = o.order == ADASUM_ORDER_LINEAR ? build_linear_passes(K, radix, radices) : build_levels(K, radix, radices);
+        if (rc != ADASUM_OK) return rc;
+        Layout lay = problem_layout(K, radices, o.order, dtype, delta, o.fuse != 0, o.separate != 0, offsets, L);
+        lay.total = std::max(lay.total, replaced.workspace);
+        (void)route_resident(K, radices, dtype, delta, o.separate != 0, offsets, L, lay);
+        *bytes = lay.total;
+    } catch (const std::bad_alloc&) {
+        return ADASUM_ERR_OUT_OF_MEMORY;
+    }
+    return ADASUM_OK;
+}
+
 // ---- plans -------------------------------------------------------------------
 
 // One tile table on the host and on the device.
@@ -347,6 +366,7 @@ struct Plan {
     int fuse = 0;                         // laid out for the sibling-fused radix-2 schedule
     int separate = 0;                     // cache key: made with separate_passes
     int lean = 0;                         // cache key: without what makes the workspace larger (make_plan)
+    size_t whole_bytes = 0;               // of a lean plan in the cache: what the plan with all of it would need
     int feed = 0;                         // passes leave the next pass's Gram entries where they can
                                           // (pass_feeds_next): tree order, no delta form, no fuse
     std::vector<int64_t> offsets;
@@ -533,10 +553,12 @@ int make_plan(int K, int radix, int order, int dtype, bool delta, bool fuse, boo
 // The library's own cache of plans, keyed by shape.
 // `order` is a tree order or kStepPlans (the step entry points keep plans of their own).
 constexpr int kStepPlans = 100;
-int find_or_make_plan(int K, int radix, int order, int in_dtype, int out_dtype, bool delta, bool fuse, bool separate,
-                      const int64_t* offsets, int n_layers, Plan** out, bool lean = false) {
+// *out = the cached plan, or null.
+int find_plan(int K, int radix, int order, int in_dtype, int out_dtype, bool delta, bool fuse, bool separate,
+              const int64_t* offsets, int n_layers, bool lean, Plan** out) {
     const int node_type = node_dtype(in_dtype);
     int device = 0;
+    *out = nullptr;
     ADASUM_HIP(hipGetDevice(&device));
     for (size_t i = 0; i < g_plans.size(); ++i) {
         Plan* p = g_plans[i].get();
@@ -551,12 +573,20 @@ int find_or_make_plan(int K, int radix, int order, int in_dtype, int out_dtype, 
             return ADASUM_OK;
         }
     }
+    return ADASUM_OK;
+}
+
+int find_or_make_plan(int K, int radix, int order, int in_dtype, int out_dtype, bool delta, bool fuse, bool separate,
+                      const int64_t* offsets, int n_layers, Plan** out, bool lean = false, size_t whole_bytes = 0) {
+    int rc = find_plan(K, radix, order, in_dtype, out_dtype, delta, fuse, separate, offsets, n_layers, lean, out);
+    if (rc != ADASUM_OK || *out != nullptr) return rc;
     // a bounded cache: the least recently used plan goes (hipFree waits for work in flight)
     while (g_plans.size() >= kMaxPlans) g_plans.erase(g_plans.begin());
     std::unique_ptr<Plan> p;
-    const int rc = make_plan(K, radix, order == kStepPlans ? ADASUM_ORDER_TREE : order, in_dtype, delta, fuse,
-                             separate, order != kStepPlans, lean, offsets, n_layers, p);
+    rc = make_plan(K, radix, order == kStepPlans ? ADASUM_ORDER_TREE : order, in_dtype, delta, fuse,
+                   separate, order != kStepPlans, lean, offsets, n_layers, p);
     if (rc != ADASUM_OK) return rc;
+    p->whole_bytes = whole_bytes;
     p->order = order;
     p->in_dtype = in_dtype;
     p->out_dtype = out_dtype;
@@ -1261,15 +1291,25 @@ int reduce_impl(const void* const* grads, int K, const int64_t* layer_offsets, i
 
     std::lock_guard<std::mutex> lock(g_mutex);
     Plan* p = nullptr;
-    rc = find_or_make_plan(K, o.radix, o.order, dtype, o.out_dtype,
-                           o.delta_start != nullptr, o.fuse != 0, o.separate != 0, layer_offsets, n_layers, &p);
-    if (rc != ADASUM_OK) return rc;
-    if (o.workspace != nullptr && o.workspace_bytes < p->lay.total) {
-        // a workspace that holds the other passes' sections only is enough for those
-        rc = find_or_make_plan(K, o.radix, o.order, dtype, o.out_dtype, o.delta_start != nullptr, o.fuse != 0,
-                               o.separate != 0, layer_offsets, n_layers, &p, true);
-        if (rc != ADASUM_OK) return rc;
+    const bool delta = o.delta_start != nullptr, fuse = o.fuse != 0, separate = o.separate != 0;
+    bool lean = false;
+    size_t whole = 0;
+    if (o.workspace != nullptr) {
+        // a workspace that holds the other passes' sections only is enough for those (a plan of either kind knows
+        // what the whole one needs; no plan is made to find out)
+        for (int l = 0; l < 2 && whole == 0; ++l) {
+            rc = find_plan(K, o.radix, o.order, dtype, o.out_dtype, delta, fuse, separate, layer_offsets, n_layers, l != 0, &p);
+            if (rc != ADASUM_OK) return rc;
+            if (p != nullptr) whole = l != 0 ? p->whole_bytes : p->lay.total;
+        }
+        if (whole == 0) {
+            rc = whole_workspace(K, o, dtype, layer_offsets, n_layers, &whole);
+            if (rc != ADASUM_OK) return rc;
+        }
+        lean = o.workspace_bytes < whole;
     }
+    rc = find_or_make_plan(K, o.radix, o.order, dtype, o.out_dtype, delta, fuse, separate, layer_offsets, n_layers, &p, lean, whole);
+    if (rc != ADASUM_OK) return rc;
     return execute_plan(p, grads, dtype, out, o, stream);
 }
 
@@ -1520,14 +1560,14 @@ int adasum_plan_create(int K, const int64_t* layer_offsets, int n_layers, int dt
     h->opts = o;
     h->opts.delta_start = nullptr;
     if (layer_offsets[n_layers] > 0) {
-        rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, o.separate != 0, true, false,
-                       layer_offsets, n_layers, h->plan);
-        if (rc != ADASUM_OK) return rc;
-        if (o.workspace != nullptr && o.workspace_bytes < h->plan->lay.total) {
-            rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, o.separate != 0, true, true,
-                           layer_offsets, n_layers, h->plan);
+        size_t whole = 0;
+        if (o.workspace != nullptr) {
+            rc = whole_workspace(K, o, dtype, layer_offsets, n_layers, &whole);
             if (rc != ADASUM_OK) return rc;
         }
+        rc = make_plan(K, h->opts.radix, o.order, dtype, h->for_delta, o.fuse != 0, o.separate != 0, true,
+                       o.workspace != nullptr && o.workspace_bytes < whole, layer_offsets, n_layers, h->plan);
+        if (rc != ADASUM_OK) return rc;
         if (o.workspace != nullptr && o.workspace_bytes < h->plan->lay.total) return ADASUM_ERR_WORKSPACE;
         // everything execute needs exists from here on: it allocates nothing
         if (h->plan->resident.form == 0) {
@@ -1598,22 +1638,7 @@ int adasum_workspace_bytes(int K, const int64_t* layer_offsets, int n_layers, in
     Opts o;
     rc = read_opts(opts, dtype, o);
     if (rc != ADASUM_OK && rc != ADASUM_ERR_WORKSPACE) return rc;
-    try {
-        std::vector<int> radices;
-        const bool delta = o.delta_start != nullptr;
-        Replaced replaced;
-        const int radix = o.radix != 0 ? o.radix : default_radix(K, o.order, dtype, delta, o.separate != 0, layer_offsets, n_layers, &replaced);
-        rc = o.order == ADASUM_ORDER_LINEAR ? build_linear_passes(K, radix, radices)
-                                            : build_levels(K, radix, radices);
-        if (rc != ADASUM_OK) return rc;
-        Layout lay = problem_layout(K, radices, o.order, dtype, delta, o.fuse != 0, o.separate != 0, layer_offsets, n_layers);
-        lay.total = std::max(lay.total, replaced.workspace);
-        (void)route_resident(K, radices, dtype, delta, o.separate != 0, layer_offsets, n_layers, lay);
-        *bytes = lay.total;
-    } catch (const std::bad_alloc&) {
-        return ADASUM_ERR_OUT_OF_MEMORY;
-    }
-    return ADASUM_OK;
+    return whole_workspace(K, o, dtype, layer_offsets, n_layers, bytes);
 }
 
 static int step_common(const void* const* x, int R, const int64_t* layer_offsets, int n_layers, int dtype) {

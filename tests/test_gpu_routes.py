@@ -40,3 +40,40 @@ def test_the_default_where_radices_change_places(K, sizes, radix):
         assert same[64]        # (64 is 32 up to 32 workers)
     else:
         assert sum(same.values()) == 1, same
+
+
+def test_shapes_with_a_small_workspace_take_one_place_each_in_the_plan_cache():
+    """40 shapes whose workspaces have no room for the resident pass: 40 plans of the 64 that are kept, so the second
+    round through them makes none.  (Making one takes a dozen device allocations and copies, some hundred us.)"""
+    import time
+    B.shutdown()
+    shapes = [(W.offsets_from_sizes([1000 + i, 70_000 + 3 * i, 33]), i) for i in range(40)]
+    grads = [torch.randn(90_000, device=DEV) for _ in range(8)]
+    ws = []
+    for offs, _ in shapes:
+        small = B.adasum_workspace_bytes(8, offs, B.F32, separate_passes=True)
+        assert small < B.adasum_workspace_bytes(8, offs, B.F32)
+        ws.append(torch.empty(small, dtype=torch.uint8, device=DEV))
+    took = []
+    for turn in range(4):
+        if turn == 1:                      # (the first round loaded the kernels)
+            B.shutdown()
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for (offs, i), w in zip(shapes, ws):
+            n = offs[-1]
+            out = torch.empty(n, device=DEV)
+            B.adasum_reduce([g[:n] for g in grads], offs, out, workspace=w)
+        torch.cuda.synchronize()
+        took.append(time.perf_counter() - t)
+    print(f"rounds: {[round(1e3 * x, 2) for x in took]} ms", flush=True)
+    assert min(took[2:]) < 0.5 * took[1]
+    # with room for it the resident pass is taken, beside the lean plan of the same shape
+    offs = shapes[0][0]
+    roomy = torch.empty(B.adasum_workspace_bytes(8, offs, B.F32), dtype=torch.uint8, device=DEV)
+    views = [g[: offs[-1]] for g in grads]
+    for _ in range(2):
+        assert torch.equal(B.adasum_reduce(views, offs, workspace=roomy), B.adasum_reduce(views, offs))
+        a = B.adasum_reduce(views, offs, workspace=ws[0])
+        b = B.adasum_reduce(views, offs, separate_passes=True)
+        assert torch.equal(a, b)
