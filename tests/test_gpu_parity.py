@@ -1080,6 +1080,8 @@ _FEED_CASES = [(K, radix, dtype)
                for dtype in (torch.float32, torch.bfloat16, torch.float16, torch.float64)
                # (fp64 passes take at most 8 workers: its wide cases are the radix-8 ones)
                if not (dtype == torch.float64 and radix == 0 and K > 64)]
+# (16-bit types take a wide first pass by default here: the 16-operand combine that feeds the next pass by name)
+_FEED_CASES += [(K, 16, dtype) for K in (32, 64, 100, 128, 256, 1024) for dtype in (torch.bfloat16, torch.float16)]
 
 
 @pytest.mark.parametrize("K,radix,dtype", _FEED_CASES)
@@ -1088,7 +1090,7 @@ def test_passes_that_feed_the_next_one(K, radix, dtype):
     (sibling groups of a tile in one workgroup, one wave each), unless separate_passes asks every
     pass to reduce its own operands.  Both are the same tree: each against the oracle, and against
     each other to the rounding of the dot products; statistics alike; reruns identical."""
-    say(f"feeding passes K={K} radix={radix} {dtype}; passes {B.plan_levels(K, radix if radix else (8 if dtype == torch.float64 else 0))}")
+    say(f"feeding passes K={K} radix={radix} {dtype}" + (f"; passes {B.plan_levels(K, radix)}" if radix else ""))
     sizes = np.diff(RAGGED).tolist()
     if dtype == torch.float64:
         w = _fp64_workload(sizes, K, 1200 + K)
