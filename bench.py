@@ -220,17 +220,15 @@ def timed_steps(B, w, out, *, out_dtype, radix, order, graph, start, steps, warm
     return dt, B.profile_collect()
 
 
-def effective_radix(w, radix, order, delta):
-    """The radix a call with `radix` (0: the library's default) is taken with; mirrors default_radix in adasum_api.cpp
-    for the workloads here (all far from the limits of the entry point without allocation)."""
+def taken_radix(w, radix, delta, prof):
+    """The radix a call with `radix` (0: the library's default) was taken with: a wide first pass shows in the names of
+    the kernels that ran."""
+    import re
     import torch
     if radix:
         return radix
-    if delta or w.dtype == torch.float64:
-        return 8
-    if w.K > 16 and order == "tree" and w.dtype in (torch.bfloat16, torch.float16):
-        return 64 if w.K > 32 and w.N >= 4_000_000 else 32
-    return 16
+    wide = [int(m.group(1)) for k in prof or [] for m in [re.match(r"gram<[^>]*R=(32|64)\b", k["name"])] if m]
+    return max(wide) if wide else 8 if delta or w.dtype == torch.float64 else 16
 
 
 def kernel_summary(prof, steps, ms_per_step, workload, verbose_tag=None):
@@ -283,7 +281,7 @@ def run_other(B, name, *, radix=0, steps=10, warmup=2, w=None, fuse=False, separ
     es = w.grads[0].element_size()
     row = {"workload": f"{name}: K={w.K}, {w.n_layers} tensors, N={w.N}, stored and output "
                        f"{str(w.dtype).replace('torch.', '')}",
-           "passes": B.plan_levels(w.K, effective_radix(w, radix, order, delta)) if order == "tree" else None,
+           "passes": B.plan_levels(w.K, taken_radix(w, radix, delta, prof)) if order == "tree" else None,
            "steps": steps, "warmup": warmup,
            "ms_per_step": ms, "input_GBps": w.input_bytes / (ms * 1e-3) / 1e9, "input_GB": w.input_bytes / 1e9,
            "generated_in_s": gen_s}
@@ -294,7 +292,7 @@ def run_other(B, name, *, radix=0, steps=10, warmup=2, w=None, fuse=False, separ
                     "dominant_kernel": roof["kernel"], "dominant_kernel_avg_ms": roof["kernel_avg_ms"],
                     "dominant_kernel_GBps": roof["achieved"], "dominant_kernel_frac": roof["frac"],
                     "ms_per_step_with_events": dtp / steps * 1e3})
-        eff = effective_radix(w, radix, order, delta)
+        eff = taken_radix(w, radix, delta, prof)
         t = measured_traffic((name if eff == 16 or (eff == 8 and not radix) else f"{name}_radix{eff}") + ("_fused" if fuse else "")
                              + ("_separate" if separate else ""), roof["kernel"]) if (order == "tree" and not delta) else None
         row["dominant_kernel_traffic"] = t["bytes"] if t else None
@@ -391,8 +389,8 @@ def main():
 
     ms_per_step = dt / args.steps * 1e3
     value = w.input_bytes / (dt / args.steps) / 1e9
-    eff = effective_radix(w, args.radix, args.order, args.delta)
-    levels = B.plan_levels(w.K, eff) if args.order == "tree" else None
+    eff = taken_radix(w, args.radix, args.delta, prof)
+    levels = B.plan_levels(w.K, eff) if args.order == "tree" and prof else None
 
     roofline = kernel_summary(prof, args.steps, ms_per_step, args.workload, verbose_tag="")
     if roofline is not None:

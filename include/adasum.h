@@ -336,8 +336,10 @@ ADASUM_API int adasum_plan_tiles(const int64_t* layer_offsets, int n_layers, int
  * radix 8 -> {8, 8}; K = 128 -> {8, 8, 2}.  Their product is K for a power of
  * two, else the next power of two: the first pass's groups are then sub-trees
  * with fewer leaves than its radix (see adasum_plan_groups), e.g. K = 12,
- * radix 8 -> {8, 2} with two groups of 6.  *n_levels receives the count; at
- * most `cap` entries are written. */
+ * radix 8 -> {8, 2} with two groups of 6.  radix 0 stands for 16 here: what a
+ * reduction that names none takes depends on its types, options and layer table
+ * too (adasum_options.radix).  *n_levels receives the count; at most `cap`
+ * entries are written. */
 ADASUM_API int adasum_plan_levels(int K, int radix, int* radices, int cap, int* n_levels);
 
 /* The groups of the first pass of the tree order: group g reduces workers

@@ -401,6 +401,8 @@ def plan_tiles(layer_offsets: Sequence[int], capacity: int = 0) -> np.ndarray:
 
 
 def plan_levels(K: int, radix: int = 0) -> List[int]:
+    """Radix of every pass of the tree order.  Radix 0 stands for 16: what a reduction that names none
+    takes depends on its types, options and layer table too."""
     lib = load()
     buf = (C.c_int * 64)()
     n = C.c_int(0)
@@ -409,7 +411,7 @@ def plan_levels(K: int, radix: int = 0) -> List[int]:
 
 
 def plan_groups(K: int, radix: int = 0) -> List[int]:
-    """Worker ranges of the first pass's groups: G + 1 boundaries."""
+    """Worker ranges of the first pass's groups: G + 1 boundaries (radix 0: as plan_levels)."""
     lib = load()
     n = C.c_int(0)
     check(lib.adasum_plan_groups(K, radix, None, 0, C.byref(n)))
