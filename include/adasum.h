@@ -10,15 +10,18 @@
  *   - the operator's scalars are taken per layer of the fused gradient buffer,
  *     Section 3.6 (last paragraph) and Section 4.4.3 (boundary bookkeeping);
  *   - dot products and squared norms: each lane accumulates a short run in fp32,
- *     a wave adds its lanes in fp32, everything above that (and the ragged
+ *     a wave adds its lanes in fp32 (the matrix cores: 64 or 128 products in a row),
+ *     everything above that (and the ragged
  *     head/tail elements of a layer) is summed in fp64; the operator's scalars
  *     are computed in fp64 (Section 4.4.1 asks for double accumulation).  fp64
  *     inputs are reduced in fp64 throughout;
- *   - up to 16 workers whose layers fit on the chip are reduced in one resident pass:
+ *   - up to 16 workers whose layers fit on the chip are reduced in one resident pass
+ *     (fp64 and the after-optimizer form: up to 8; left to right: 2, 4, 8 or 16):
  *     a piece of a layer stays in a workgroup's registers and LDS while the layer's
  *     scalars are worked out, so every input is read once.  Workgroups of a layer wait
  *     for each other, at most 100 us; what that leaves undone (when other kernels hold
- *     much of the chip) a second launch does from memory, with the same result;
+ *     much of the chip) a second launch does from memory, with the same result.  Programs
+ *     that reduce large models beside other kernels: see separate_passes;
  *   - layers of at most 16 elements are reduced by the definition itself, pair by
  *     pair in fp64 over all K workers with nothing stored in between: vectors that
  *     short can nearly cancel at a tree node, where stored fp32 nodes lose digits.
@@ -155,8 +158,11 @@ typedef struct adasum_options {
                                   Gram matrix of the next pass's group (it handles the sibling groups of
                                   a tile in one workgroup, one wave each, and the waves exchange what they
                                   wrote), so that only the first pass reads its operands twice;
-                                  1: every pass makes a reduce pass of its own over its operands (for
-                                  measurements; the result is the same up to rounding).  A struct_bytes
+                                  1: every pass makes a reduce pass of its own over its operands, and there is
+                                  no resident pass (for measurements, and for programs whose other kernels hold
+                                  much of the chip meanwhile: ResNet-50 sizes of 8 or 16 workers reduced beside
+                                  a stream of small matrix products take 0.6 times as long this way, alone 1.1
+                                  to 1.4 times; the result is the same up to rounding).  A struct_bytes
                                   that ends before this field reads as 0. */
     int32_t  reserved1;        /* must be 0 */
     int32_t  resident_wait_us; /* microseconds that the workgroups of a layer wait for each other in the resident pass before
@@ -237,7 +243,8 @@ ADASUM_API int adasum_plan_create(int K, const int64_t* layer_offsets, int n_lay
  * NULL): DEVICE, as in adasum_reduce_ex.  Same checks, same errors. */
 ADASUM_API int adasum_plan_execute(adasum_plan* plan, const void* const* grads, void* out,
                                    double* layer_stats, const void* delta_start, void* stream);
-/* Bytes of workspace the plan uses (what adasum_workspace_bytes reports for its shape). */
+/* Bytes of workspace the plan uses (what adasum_workspace_bytes reports for its shape; less for a
+ * plan made with a smaller workspace). */
 ADASUM_API int adasum_plan_workspace_bytes(const adasum_plan* plan, size_t* bytes);
 ADASUM_API int adasum_plan_destroy(adasum_plan* plan);
 

@@ -4,6 +4,13 @@
 // scalars and combines from what it kept.  One launch takes the place of gram_kernel, gram_finish_kernel and
 // combine_kernel, and operands that those read twice cross the fabric between the memory and the compute dies once.
 //
+// Its layers of some waves of units need the chip for themselves: beside other kernels units wait longer for each other,
+// and some give up (see resident_redo_kernel).  Measured beside 8192^3 bf16 matrix products, copies of 1 GB and small
+// products (512 x 4096 x 4096) on another stream, us per reduction, three kernels in brackets: ResNet-50 sizes, K = 2 bf16 856
+// (1593), 68 (97), 56 (66); K = 8 fp32 1348 (1847), 368 (520), 503 (331); K = 16 bf16 1805 (1851), 1218 (529), 588 (366); a
+// quarter of them, K = 8 bf16, 1595 (1646), 106 (126), 75 (107).  So programs that reduce large models of 8 and more workers
+// beside small or streaming kernels are better off with separate_passes.
+//
 // What bounds it.  Re-reading is what the three kernels lose: the Infinity Cache gives a compute die no more bandwidth
 // than memory does (7.1 TB/s, measured on 64 .. 256 MB re-read in a loop against 7.0 TB/s fresh), so bytes have to stay
 // in registers and LDS to be saved.  The chip holds some 110 MB there, about 15 us of memory traffic; a unit lives
@@ -11,8 +18,9 @@
 // layer's slowest unit), the scalars (1 us) and its stores.  So the pass is bound by how much is kept over how long:
 // hence as much as the register file takes per unit, LDS filled straight from memory beside it, an exchange without
 // atomics, flags or fences (a fence of agent scope cost 1.4 x the whole pass), and launch order (order_units).
-// Measured against the three kernels, us per reduction: ResNet-50 sizes, K = 8 fp32 298 -> 215, K = 2 bf16 51 -> 36,
-// K = 6 binary16 152 -> 109, K = 16 bf16 with statistics 316 -> 276; 400 odd tensors, K = 12 bf16, 182 -> 102.
+// Measured against the three kernels, us per reduction: ResNet-50 sizes, K = 8 fp32 298 -> 214, K = 2 bf16 51 -> 36,
+// K = 6 binary16 152 -> 108, K = 16 bf16 with statistics 316 -> 272; 400 odd tensors, K = 12 bf16, 182 -> 100.  K = 8 fp32
+// reads 842 MB of 818 MB of gradients, K = 16 bf16 924 MB of 818: the exchange is the rest.
 #include <hip/hip_runtime.h>
 
 #include "adasum_host.h"
@@ -507,8 +515,9 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
 
 // The second launch: the units that gave up waiting, from memory, with the same arithmetic in the same order (by now
 // every partial sum is there), and the tag moves on.  A workgroup looks at every gridDim.x-th unit: a layer's units
-// follow each other and tend to give up together.  Usually there is nothing to do, and the launch costs 1 .. 2 us; where
-// every unit gave up FIXME.
+// follow each other and tend to give up together.  Usually there is nothing to do, and the launch costs 4 us at 3726
+// units.  Where every unit gave up it streams like a combine pass: K = 8 fp32 ResNet-50 sizes 337 us in all (with 32 units
+// a workgroup 713; three kernels 297), K = 16 bf16 630 (1861; 305), K = 2 bf16 94 (322; 51).
 template <typename TI, typename TO, int R, bool DELTA>
 __global__ void __launch_bounds__(kThreads)
 resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ units, int n_units, const ResidentState st,

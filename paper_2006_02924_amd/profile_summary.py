@@ -57,6 +57,10 @@ def library_name(kernel_name: str):
         return f"combine<{args[0]},{args[1]},R={args[2]}>+gram{args[3]}"
     if kind == "gram_finish" and len(args) >= 2:
         return f"gram_finish<R={args[0]},{'diag' if args[1] == 'true' else 'offdiag'}>"
+    if kind == "resident" and len(args) >= 4:
+        return f"resident<{args[0]},{args[1]},R={args[2]}>" + (" (delta)" if args[3] == "true" else "")
+    if kind == "resident_redo" and len(args) >= 3:
+        return f"resident_redo<{args[0]},{args[1]},R={args[2]}>"
     if kind == "parts_coarsen":
         return "gram_from_combine"       # (the name bench.py times that launch under)
     return kind + (f"<{','.join(args)}>" if args else "")
@@ -118,7 +122,7 @@ def cmd_traffic(args):
     def by_name(path, counter):
         acc = collections.OrderedDict()
         for (name, _grid), counters in read_counters(path).items():
-            if counter in counters and (name.startswith("gram<") or name.startswith("combine<")):
+            if counter in counters and name.startswith(("gram<", "combine<", "resident<")):
                 a = acc.setdefault(name, [0, 0.0])
                 a[0] += counters[counter][0]
                 a[1] += counters[counter][1]
