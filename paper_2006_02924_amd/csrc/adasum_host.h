@@ -292,9 +292,9 @@ constexpr int resident_most(int dtype, int R, int form) {
 }
 constexpr int resident_register_steps(int dtype, int R, bool delta, int form) {
     const int rows = R + (delta ? 1 : 0);
-    // (form 2 has 168 registers: 24 rows of 4, but 16 where the sums of 8 rows, or of 7 in fp64, would spill: K = 8 fp64, a
+    // (form 2 has 168 registers: 24 rows of 4, but 16 where the sums of 8 rows, or of 7 in fp64, would spill (and 21 for 3 rows): K = 8 fp64, a
     // quarter of ResNet-50, 229 -> 126 us, K = 8 bf16, ResNet-50 sizes, 149 -> 125)
-    const int kept = form == 2 ? (rows == 8 || (rows >= 7 && dtype == ADASUM_F64) ? 16 : 24)
+    const int kept = form == 2 ? (rows == 8 || (rows >= 7 && dtype == ADASUM_F64) ? 16 : rows == 3 ? 21 : 24)
                      : resident_matrix(dtype, R) ? 48 : dtype == ADASUM_F64 || R > 8 ? 32 : 40;
     const int steps = kept / rows;
     return steps < 16 ? (steps < 1 ? 1 : steps) : 16;

@@ -287,8 +287,10 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
         const Count full = count(step * steps);
         if (full.most > resident_most(dtype, p.R, form)) continue;
         // Tables of tiny layers: hardly more units in form 1, which holds more workgroups (K = 2 bf16, 20000 layers of 100 to
-        // 300 elements: 43 us, in form 2 95; 600 layers of 1 to 20000: 24 and 28).
-        if (one.all <= 2 * full.all && one.most <= kDirectUnits) {
+        // 300 elements: 43 us, in form 2 95; 600 layers of 1 to 20000: 24 and 28).  (The kernels on the matrix cores hold
+        // as many workgroups in either form: with 12 to 16 rows form 1 is still ahead, K = 16 332 us for 542, with 10 it is
+        // not, 288 for 277.)
+        if (one.all <= 2 * full.all && one.most <= kDirectUnits && !(resident_matrix(dtype, p.R) && p.R < 12)) {
             take(1, step, one);
             return p;
         }

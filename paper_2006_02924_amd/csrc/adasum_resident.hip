@@ -23,6 +23,8 @@
 // reads 842 MB of 818 MB of gradients, K = 16 bf16 924 MB of 818: the exchange is the rest.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "adasum_host.h"
 #include "adasum_device.h"
 
@@ -111,7 +113,9 @@ __device__ __forceinline__ bool await(const unsigned long long* p, Words& w, uns
     return true;
 }
 
-constexpr int kSkipScan = 4;             // units a workgroup of the second launch looks at
+// Units a workgroup of the second launch looks at: 4, more where that would take more than 2048 workgroups (20000 units,
+// K = 9 bf16: with 5000 workgroups 279.6 us, with 1024 277.8), 32 at most.
+constexpr int kSkipScan = 4, kSkipScanMost = 32, kSkipBlocks = 2048;
 constexpr int kTicksPerUs = 100;         // of wall_clock64
 
 // 16 bytes per lane straight from memory into LDS (lane l's at dst + 16 l): no registers are held meanwhile.
@@ -537,8 +541,8 @@ resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int mine = static_cast<int>(blockIdx.x) + (lane % kSkipScan) * static_cast<int>(gridDim.x);
-    const bool redo = lane < kSkipScan && mine < n_units && st.skipped[mine] == 1;
+    const long long mine = static_cast<long long>(blockIdx.x) + static_cast<long long>(lane) * gridDim.x;
+    const bool redo = mine < n_units && st.skipped[mine] == 1;
     unsigned long long todo = __ballot(redo);
     __syncthreads();
     if (redo && wave == 0) st.skipped[mine] = 2;
@@ -546,7 +550,7 @@ resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict
     while (todo != 0) {
         const int b = __builtin_ctzll(todo);
         todo &= todo - 1;
-        const ResidentUnit t = units[static_cast<int>(blockIdx.x) + b * static_cast<int>(gridDim.x)];
+        const ResidentUnit t = units[static_cast<long long>(blockIdx.x) + static_cast<long long>(b) * gridDim.x];
         adasum_tile tile;
         tile.start = t.start;
         tile.len = t.len;
@@ -653,7 +657,9 @@ int launch_s(const ResidentCall& c, hipStream_t stream) {
 
 template <typename TI, typename TO, int R, bool DELTA>
 int launch_redo(const ResidentCall& c, hipStream_t stream) {
-    hipLaunchKernelGGL((resident_redo_kernel<TI, TO, R, DELTA>), dim3(static_cast<unsigned>((c.n_units + kSkipScan - 1) / kSkipScan)),
+    auto blocks = [&](int scan) { return (static_cast<long long>(c.n_units) + scan - 1) / scan; };
+    const long long n = blocks(kSkipScan) <= kSkipBlocks ? blocks(kSkipScan) : std::max<long long>(kSkipBlocks, blocks(kSkipScanMost));
+    hipLaunchKernelGGL((resident_redo_kernel<TI, TO, R, DELTA>), dim3(static_cast<unsigned>(n)),
                        dim3(kThreads), 0, stream, c.ops, static_cast<TO*>(c.out), c.units, c.n_units, c.state,
                        c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves);
     return static_cast<int>(hipGetLastError());

@@ -23,7 +23,7 @@ def unit_elements(K, dtype, form, delta=False):
         rows = (K + 1) // 2 * 2
     matrix = K > 8 and vec == 8
     short = rows == 8 or (rows >= 7 and dtype == torch.float64)
-    registers = {2: 16 if short else 24, 3: 48 if matrix else 32 if dtype == torch.float64 or K > 8 else 40}[form]
+    registers = {2: 16 if short else 21 if rows == 3 else 24, 3: 48 if matrix else 32 if dtype == torch.float64 or K > 8 else 40}[form]
     steps = max(1, min(16, registers // rows)) + (0 if matrix else min(8, {2: 12, 3: 18}[form] // rows))
     return LANES * vec * steps
 

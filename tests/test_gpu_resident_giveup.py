@@ -91,6 +91,22 @@ def test_left_to_right_order(K, dtype):
     assert s.redone() == s.waiting and torch.equal(want, got)
 
 
+@pytest.mark.parametrize("layers", [2_000, 20_000])
+def test_many_units(layers):
+    """More units than 2048 workgroups of the second launch look at four each, and fewer; every tenth layer has two."""
+    sizes = [1500 if l % 10 else 2100 for l in range(layers)]
+    w = workload(sizes, 3, torch.bfloat16, 4)
+    steps, units = steps_and_layers(3, w.layer_offsets, B.BF16)
+    assert steps == 1 and units.sum() > layers
+    base = B.adasum_workspace_bytes(3, w.layer_offsets, B.BF16, separate_passes=True)
+    ws = torch.empty(B.adasum_workspace_bytes(3, w.layer_offsets, B.BF16), dtype=torch.uint8, device=DEV)
+    want = B.adasum_reduce(w.grads, w.layer_offsets)
+    got = B.adasum_reduce(w.grads, w.layer_offsets, workspace=ws, resident_wait_us=-1)
+    assert torch.equal(want, got)
+    flags = ws[base:][: 4 * (1 + int(units.sum()))].view(torch.int32)[1:]
+    assert int((flags == 2).sum()) == int(units[units > 1].sum())
+
+
 def test_held_plan_captured_and_replayed():
     """The second launch moves the tag on for the next call whatever it had to do."""
     K, sizes = 4, [3000, 17, 900000, 1]

@@ -62,6 +62,10 @@ def test_units_are_as_small_as_the_chip_holds_at_once():
 def test_tables_of_tiny_layers_take_the_smallest_units():
     assert steps(2, [200] * 20_000, B.BF16)[0] == 1
     assert steps(8, [700] * 4_000, B.F64)[0] == 1
+    assert unit_count(16, W.offsets_from_sizes([6145] * 700), B.BF16)[0] > 2 * 700      # (three or four units of one step each)
+    crossing = [2048 * 2 - 8] * 600                                                    # 2 .. 3 units of one step, 1 .. 2 of four
+    assert len(B.plan_tiles(W.offsets_from_sizes(crossing), 4 * 2048)) in unit_count(9, W.offsets_from_sizes(crossing), B.BF16)
+    assert len(B.plan_tiles(W.offsets_from_sizes(crossing), 2048)) in unit_count(12, W.offsets_from_sizes(crossing), B.BF16)
     assert steps(2, [200] * 2_000 + [3_000_000], B.BF16)[0] > 1        # (a layer that would have 1465 of them)
 
 
