@@ -8,7 +8,7 @@
 // and some give up (see resident_redo_kernel).  Measured beside 8192^3 bf16 matrix products, copies of 1 GB and small
 // products (512 x 4096 x 4096) on another stream, us per reduction, three kernels in brackets: ResNet-50 sizes, K = 2 bf16 856
 // (1593), 68 (97), 56 (66); K = 8 fp32 1348 (1847), 368 (520), 503 (331); K = 16 bf16 1805 (1851), 1218 (529), 588 (366); a
-// quarter of them, K = 8 bf16, 1595 (1646), 106 (126), 75 (107).  So programs that reduce large models of 8 and more workers
+// quarter of them, K = 8 bf16, 1555 (1618), 96 (126), 72 (94).  So programs that reduce large models of 8 and more workers
 // beside small or streaming kernels are better off with separate_passes.
 //
 // What bounds it.  Re-reading is what the three kernels lose: the Infinity Cache gives a compute die no more bandwidth

@@ -49,7 +49,8 @@ def main():
     torch.cuda.synchronize()
     out_dtype = w.dtype if args.out_dtype == "same" else torch.float32
     print(f"[report] {w.name}: K={w.K} N={w.N} layers={w.n_layers} {w.dtype} -> {out_dtype}", flush=True)
-    print(f"[report] radix {args.radix}: passes {B.plan_levels(w.K, args.radix)}", flush=True)
+    passes = B.plan_levels(w.K, args.radix) if args.radix else None   # (the default's depend on types and sizes too)
+    print(f"[report] radix {args.radix}: passes {passes}", flush=True)
     out = B.adasum_reduce(w.grads, w.layer_offsets, out_dtype=out_dtype, radix=args.radix)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -110,7 +111,7 @@ def main():
     worst = int(np.argmax(err))
     big = sizes >= U.TINY_LAYER
     row = {
-        "config": args.config, "K": w.K, "radix": args.radix, "passes": B.plan_levels(w.K, args.radix), "layers": w.n_layers, "layers_checked": int(w.n_layers - len(skipped)),
+        "config": args.config, "K": w.K, "radix": args.radix, "passes": passes, "layers": w.n_layers, "layers_checked": int(w.n_layers - len(skipped)),
         "layers_without_reference": skipped, "out_dtype": str(out_dtype).replace("torch.", ""),
         "gpu_ms": gpu_ms, "input_GBps": w.input_bytes / gpu_ms / 1e6,
         "max_rel_l2": float(err.max()), "max_rel_l2_layer": worst, "max_rel_l2_layer_size": int(sizes[worst]),

@@ -81,3 +81,22 @@ def test_many_layers_that_each_leave_the_chip_half_idle_take_the_other_passes(K,
 
 def test_fp32_of_few_rows_stays():
     assert unit_count(8, W.offsets_from_sizes([300 * 7168] * 20), B.F32)
+
+
+def test_the_wait_option(lib):
+    """Values out of range and the reserved word are refused; a struct that ends before them reads as 0."""
+    def call(**fields):
+        o = B.Options()
+        o.struct_bytes = C.sizeof(B.Options)
+        o.out_dtype = -1
+        for k, v in fields.items():
+            setattr(o, k, v)
+        grads = (C.c_void_p * 2)(C.c_void_p(1 << 40), C.c_void_p(2 << 40))
+        return lib.adasum_reduce_ex(grads, 2, (C.c_int64 * 1)(0), 0, B.F32, C.c_void_p(3 << 40), C.byref(o), None)
+
+    for us in (0, 1, 10_000, -1):
+        assert call(resident_wait_us=us) == B.OK
+    for bad in ({"resident_wait_us": -2}, {"resident_wait_us": 10_001}, {"reserved2": 1}):
+        assert call(**bad) == B.ERR_INVALID_ARG
+        assert call(struct_bytes=B.Options.resident_wait_us.offset, **bad) == B.OK
+    assert call(struct_bytes=B.Options.resident_wait_us.offset, reserved1=1) == B.ERR_INVALID_ARG
