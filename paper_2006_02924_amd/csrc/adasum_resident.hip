@@ -84,33 +84,63 @@ __device__ __forceinline__ f32x4_t mfma_square(const u32x4& x, const f32x4_t& c)
 // ---- values that one workgroup of a launch writes and others read ----
 // A double travels as two 8-byte words, each with half of its bits and the call's tag: a reader knows from the word
 // itself whether it was written in this call, so there are no flags, no counters and nothing to wait for between a
-// value and its announcement.  Accesses are relaxed and of agent scope (they go past the compute dies' own caches).
-__device__ __forceinline__ void send(unsigned long long* p, double v, unsigned tag) {
-    const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(v));
-    const unsigned long long t = static_cast<unsigned long long>(tag) << 32;
-    __hip_atomic_store(p, t | (b & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// value and its announcement.  Both words go in one 16-byte access (a tag for each half, so it need not be atomic), past
+// the compute dies' own caches.
+constexpr int kPastCaches = 16;   // (the sc1 bit: agent scope)
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+__device__ __forceinline__ buffer_t buffer_of(const void* base, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
 }
-struct Words {
-    unsigned long long lo, hi;
-};
-__device__ __forceinline__ Words peek(const unsigned long long* p) {
-    Words w;
-    w.lo = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    w.hi = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return w;
+__device__ __forceinline__ void send(buffer_t b, int offset, double v, unsigned tag) {
+    const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(v));
+    u32x4 w;
+    w.x = static_cast<unsigned>(bits);
+    w.y = tag;
+    w.z = static_cast<unsigned>(bits >> 32);
+    w.w = tag;
+    __builtin_amdgcn_raw_buffer_store_b128(w, b, offset, 0, kPastCaches);
 }
-__device__ __forceinline__ double value(const Words& w) {
-    return __longlong_as_double(static_cast<long long>((w.hi << 32) | (w.lo & 0xffffffffull)));
+__device__ __forceinline__ u32x4 peek(buffer_t b, int offset) { return __builtin_amdgcn_raw_buffer_load_b128(b, offset, 0, kPastCaches); }
+__device__ __forceinline__ bool tagged(const u32x4& w, unsigned tag) { return w.y == tag && w.w == tag; }
+__device__ __forceinline__ double value(const u32x4& w) {
+    return __longlong_as_double(static_cast<long long>(w.z) << 32 | static_cast<long long>(w.x));
 }
-// Looks again until the value is there, or the time is up (false).
-__device__ __forceinline__ bool await(const unsigned long long* p, Words& w, unsigned tag, long long deadline) {
-    while (static_cast<unsigned>(w.lo >> 32) != tag || static_cast<unsigned>(w.hi >> 32) != tag) {
+// Looks at N values side by side, and at all of them again until they are there or the time is up (false).  (One after another,
+// each that was late would take a trip through memory of its own.)
+template <int N>
+__device__ __forceinline__ bool await(buffer_t b, const int (&offset)[N], u32x4 (&w)[N], unsigned tag, long long deadline) {
+    for (;;) {
+        bool there = true;
+#pragma unroll
+        for (int k = 0; k < N; ++k) w[k] = peek(b, offset[k]);
+#pragma unroll
+        for (int k = 0; k < N; ++k) there = there && tagged(w[k], tag);
+        if (there) return true;
         if (static_cast<long long>(wall_clock64()) > deadline) return false;
         __builtin_amdgcn_s_sleep(2);
-        w = peek(p);
+        asm volatile("" ::: "memory");   // (the next look is another)
     }
-    return true;
+}
+// Where entry e of the layer's unit number u lies (of W units, NP entries), in bytes: runs of kRun entries of every unit follow each
+// other, so that the lanes that sum a run over the units read whole memory sectors.  (With the NP entries of a unit in one
+// piece each lane's 16 bytes are a sector of their own, again with every look, and 136 waves of a layer look at 384 units:
+// K = 16 bf16, ResNet-50 sizes, 271 us instead of 242, K = 8 fp32 207 instead of 190.)
+constexpr int kRun = 4;
+template <int NP>
+__device__ __forceinline__ int partial_at(int u, int e, int W) {
+    const int run = e / kRun * kRun;
+    return (run * W + u * (NP - run < kRun ? NP - run : kRun) + (e - run)) * 16;
+}
+// A workgroup sums a run: kRun lanes side by side per unit, kRunUnits units at a time.
+constexpr int kRunUnits = kThreads / kRun;
+// Units of a layer up to which every workgroup reads all partial sums itself.  (K = 2 bf16, ResNet-50 sizes: 37.4 us with 4,
+// 38.4 with 16, 40.7 with 170; K = 8 fp32 and K = 16 bf16 take the same with 4 to 32, 1.5 % longer with 2.)
+constexpr int direct_units(int R) { return R == 2 ? 4 : kDirectUnits; }
+// the sum over the units of a wave; lanes 0 .. kRun - 1 hold the entries'
+__device__ __forceinline__ double run_sum(double v) {
+#pragma unroll
+    for (int m = 32; m >= kRun; m >>= 1) v += __shfl_xor(v, m, 64);
+    return v;
 }
 
 // Units a workgroup of the second launch looks at: 4, more where that would take more than 2048 workgroups (20000 units,
@@ -136,14 +166,7 @@ __device__ __forceinline__ void each(F&& f) {
 }
 
 // a value of an earlier launch: one ordinary load, through the caches
-__device__ __forceinline__ double read(const unsigned long long* p) {
-    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
-    const u64x2 v = *reinterpret_cast<const u64x2*>(p);
-    Words w;
-    w.lo = v.x;
-    w.hi = v.y;
-    return value(w);
-}
+__device__ __forceinline__ double read(buffer_t b, int offset) { return value(__builtin_amdgcn_raw_buffer_load_b128(b, offset, 0, 0)); }
 
 // ---- what both launches do with a layer's Gram matrix ----
 // the weights (by one wave; the workgroup waits for these few instructions)
@@ -210,7 +233,7 @@ __device__ __forceinline__ double combine_ragged(const Operands& ops, const TI* 
 // waves per SIMD are resident, i.e. WPS workgroups per compute unit.
 //
 // A layer of W units gets its Gram matrix in one trip when W is small (every workgroup reads the W partial matrices)
-// and in two otherwise (wave w of the q-th workgroup sums entry q + W w over the units; everybody reads the sums).
+// and in two otherwise (the q-th workgroup sums the q-th run of entries over the units; everybody reads the sums).
 // The order of the sums depends on W alone: identical inputs give bit-identical outputs.
 //
 // Waiting is bounded, because nothing promises that a layer's workgroups run side by side (another stream's kernels
@@ -224,6 +247,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     constexpr int NP = R * (R + 1) / 2;
     constexpr int NW = kThreads / 64;
     constexpr int ROWS = kThreads / NP;
+    constexpr int kDirect = direct_units(R);
     constexpr int kEdge = 2 * (G - 1);
     constexpr int RL = R + (DELTA ? 1 : 0);   // rows kept: the operands, and `start`
     // entries accumulated side by side: more than some 60 do not fit beside what is kept, and take more sweeps over it
@@ -237,7 +261,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     static_assert(ROWS >= 1 && SV >= 1 && R <= 16 && !(MFMA && SL > 0), "");
 
     __shared__ double shP[NW * (MFMA ? 256 : NP)];
-    __shared__ double shR[ROWS * NP];
+    __shared__ double shR[ROWS * NP > NW * kRun ? ROWS * NP : NW * kRun];
     __shared__ double shEdge[R][kEdge > 0 ? kEdge : 1];
     __shared__ double shG[R * R];
     __shared__ double shW[R];
@@ -257,6 +281,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     const int at = static_cast<int>(blockIdx.x);
     const ResidentUnit t = units[at];
     const int W = t.layer_end - t.layer_first;
+    const buffer_t partials = buffer_of(st.partials + static_cast<long long>(t.layer_first) * (NP * 2), W * NP * 16);
     adasum_tile tile;
     tile.start = t.start;
     tile.len = t.len;
@@ -423,40 +448,37 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
 #pragma unroll
             for (int w = 1; w < NW; ++w) tot += shP[w * (MFMA ? 256 : NP) + cell];
             for (int k = 0; k < nedge; ++k) tot += shEdge[a][k] * shEdge[b][k];
-            if (W > 1) send(st.partials + (static_cast<long long>(t.unit) * NP + tid) * 2, tot, tag);
+            if (W > 1) send(partials, partial_at<NP>(t.unit - t.layer_first, tid, W), tot, tag);
             else shG[a * R + b] = shG[b * R + a] = tot;
         }
     }
 
     if (W > 1) {
         const long long deadline = static_cast<long long>(wall_clock64()) + static_cast<long long>(wait_us) * kTicksPerUs;
-        const int tb = t.layer_first, te = t.layer_end;
         bool ok = wait_us >= 0;
-        // the sum of entry e over the units u0, u0 + step, ... of the layer, a few loads in flight
-        auto sum_units = [&](int e, int u0, int step) {
-            constexpr int kAhead = R > 8 ? 8 : 4;
+        // the sum of entry e over the units u0, u0 + step, ... of the layer, kAhead of them looked at side by side
+        auto sum_ahead = [&](auto ahead, int e, int u0, int step) {
+            constexpr int kAhead = decltype(ahead)::value;
             double v = 0.0;
-            for (; u0 < te; u0 += step * kAhead) {
-                Words x[kAhead];
+            for (; u0 < W; u0 += step * kAhead) {
+                int offset[kAhead];
+                u32x4 x[kAhead];
 #pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    const int u = u0 + step * k;
-                    x[k] = peek(st.partials + (static_cast<long long>(u < te ? u : te - 1) * NP + e) * 2);
-                }
+                for (int k = 0; k < kAhead; ++k) offset[k] = partial_at<NP>(u0 + step * k < W ? u0 + step * k : W - 1, e, W);
+                ok = await(partials, offset, x, tag, deadline) && ok;
 #pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    const int u = u0 + step * k;
-                    if (u < te) {
-                        ok = await(st.partials + (static_cast<long long>(u) * NP + e) * 2, x[k], tag, deadline) && ok;
-                        v += value(x[k]);
-                    }
-                }
+                for (int k = 0; k < kAhead; ++k)
+                    if (u0 + step * k < W) v += value(x[k]);
             }
             return v;
         };
-        if (W <= kDirectUnits) {
+        auto sum_units = [&](int e, int u0, int step) {
+            if (W <= step) return sum_ahead(std::integral_constant<int, 1>(), e, u0, step);
+            return W <= 2 * step ? sum_ahead(std::integral_constant<int, 2>(), e, u0, step) : sum_ahead(std::integral_constant<int, 4>(), e, u0, step);
+        };
+        if (W <= kDirect) {
             const int row = tid / NP, e = tid % NP;
-            if (row < ROWS) shR[row * NP + e] = sum_units(e, tb + row, ROWS);
+            if (row < ROWS) shR[row * NP + e] = sum_units(e, row, ROWS);
             __syncthreads();
             if (tid < NP) {
                 double tot = shR[tid];
@@ -467,17 +489,29 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
                 shG[a * R + b] = shG[b * R + a] = tot;
             }
         } else {
-            unsigned long long* sums = st.sums + static_cast<long long>(t.layer) * (NP * 2);
-            for (int e = (t.unit - tb) + W * wave; e < NP; e += W * NW) {
-                const double v = wave_sum(sum_units(e, tb + lane, 64));
-                if (__ballot(!ok) == 0 && lane == 0) send(sums + 2 * e, v, tag);
+            const buffer_t sums = buffer_of(st.sums + static_cast<long long>(t.layer) * (NP * 2), NP * 16);
+            for (int run = (t.unit - t.layer_first) * kRun; run < NP; run += W * kRun) {
+                const int e = run + tid % kRun;
+                const double v = run_sum(sum_units(e < NP ? e : NP - 1, tid / kRun, kRunUnits));
+                if (__ballot(!ok) != 0 && lane == 0) shSkip = 1;
+                if (lane < kRun) shR[wave * kRun + lane] = v;
+                __syncthreads();
+                if (tid < kRun && e < NP && !shSkip) {
+                    double tot = shR[tid];
+#pragma unroll
+                    for (int w = 1; w < NW; ++w) tot += shR[w * kRun + tid];
+                    send(sums, e * 16, tot, tag);
+                }
+                __syncthreads();   // (the next run's sums go through the same memory)
             }
             if (tid < NP) {
-                Words x = peek(sums + 2 * tid);
-                ok = await(sums + 2 * tid, x, tag, deadline) && ok;
+                const int offset[1] = {tid * 16};
+                u32x4 x[1];
+                if (lane == 0) ok = await(sums, offset, x, tag, deadline) && ok;   // (one lane's looks are enough until then)
+                ok = await(sums, offset, x, tag, deadline) && ok;
                 int a, b;
                 entry_to_ij<R, true>(tid, a, b);
-                shG[a * R + b] = shG[b * R + a] = value(x);
+                shG[a * R + b] = shG[b * R + a] = value(x[0]);
             }
         }
         if (!ok) shSkip = 1;
@@ -551,10 +585,11 @@ resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict
     constexpr int NP = R * (R + 1) / 2;
     constexpr int NW = kThreads / 64;
     constexpr int ROWS = kThreads / NP;
+    constexpr int kDirect = direct_units(R);
     constexpr int RL = R + (DELTA ? 1 : 0);
     typedef typename Traits<TI>::acc_t acc_t;
     constexpr bool NTS = !(sizeof(TI) == 2 && sizeof(TO) == 4 && R <= 2);   // as combine_kernel
-    __shared__ double shR[ROWS * NP];
+    __shared__ double shR[ROWS * NP > NW * kRun ? ROWS * NP : NW * kRun];
     __shared__ double shG[R * R];
     __shared__ double shW[R];
     __shared__ double shQ[4 * R];
@@ -577,17 +612,23 @@ resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict
         tile.len = t.len;
         tile.layer = t.layer;
         const Split s = split_tile<G>(tile);
-        const int tb = t.layer_first, te = t.layer_end;
-        auto partial = [&](int u, int e) { return st.partials + (static_cast<long long>(u) * NP + e) * 2; };
-        if (te - tb <= kDirectUnits) {
-            constexpr int kMost = (kDirectUnits + ROWS - 1) / ROWS;
-            const int row = tid / NP, e = tid % NP;
+        const int W = t.layer_end - t.layer_first;
+        const buffer_t partials = buffer_of(st.partials + static_cast<long long>(t.layer_first) * (NP * 2), W * NP * 16);
+        // the sum of entry e over the units u0, u0 + step, ... of the layer: all loads in flight at a time
+        auto sum_units = [&](auto most, int e, int u0, int step) {
+            constexpr int kMost = decltype(most)::value;
             double x[kMost], v = 0.0;
 #pragma unroll
-            for (int k = 0; k < kMost; ++k) x[k] = read(partial(tb + row + k * ROWS < te ? tb + row + k * ROWS : te - 1, e));
+            for (int k = 0; k < kMost; ++k) x[k] = read(partials, partial_at<NP>(u0 + k * step < W ? u0 + k * step : W - 1, e, W));
 #pragma unroll
             for (int k = 0; k < kMost; ++k)
-                if (tb + row + k * ROWS < te) v += x[k];
+                if (u0 + k * step < W) v += x[k];
+            return v;
+        };
+        if (W <= kDirect) {
+            constexpr int kMost = (kDirect + ROWS - 1) / ROWS;
+            const int row = tid / NP, e = tid % NP;
+            const double v = sum_units(std::integral_constant<int, kMost>(), e, row, ROWS);
             if (row < ROWS) shR[row * NP + e] = v;
             __syncthreads();
             if (tid < NP) {
@@ -599,33 +640,22 @@ resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict
                 shG[i * R + j] = shG[j * R + i] = tot;
             }
         } else {
-            // a few entries and rounds of units in flight at a time: a lane adds its units, then the wave its lanes
-            constexpr int EA = 4, UA = 4;
-            for (int e0 = wave * EA; e0 < NP; e0 += NW * EA) {
-                double v[EA];
+            // (a layer has at most 768 units)
+            constexpr int kMost = (3 * kResidentCus + kRunUnits - 1) / kRunUnits;
+            for (int run = 0; run < NP; run += kRun) {
+                const int e = run + tid % kRun;
+                const double v = run_sum(sum_units(std::integral_constant<int, kMost>(), e < NP ? e : NP - 1, tid / kRun, kRunUnits));
+                if (lane < kRun) shR[wave * kRun + lane] = v;
+                __syncthreads();
+                if (tid < kRun && e < NP) {
+                    double tot = shR[tid];
 #pragma unroll
-                for (int k = 0; k < EA; ++k) v[k] = 0.0;
-                for (int u0 = tb + lane; u0 < te; u0 += 64 * UA) {
-                    double x[UA][EA];
-#pragma unroll
-                    for (int i = 0; i < UA; ++i)
-#pragma unroll
-                        for (int k = 0; k < EA; ++k)
-                            x[i][k] = read(partial(u0 + 64 * i < te ? u0 + 64 * i : te - 1, e0 + k < NP ? e0 + k : NP - 1));
-#pragma unroll
-                    for (int i = 0; i < UA; ++i)
-                        if (u0 + 64 * i < te) {
-#pragma unroll
-                            for (int k = 0; k < EA; ++k) v[k] += x[i][k];
-                        }
-                }
-#pragma unroll
-                for (int k = 0; k < EA; ++k) {
-                    const double tot = wave_sum(v[k]);
+                    for (int w = 1; w < NW; ++w) tot += shR[w * kRun + tid];
                     int i, j;
-                    entry_to_ij<R, true>(e0 + k < NP ? e0 + k : NP - 1, i, j);
-                    if (lane == 0 && e0 + k < NP) shG[i * R + j] = shG[j * R + i] = tot;
+                    entry_to_ij<R, true>(e, i, j);
+                    shG[i * R + j] = shG[j * R + i] = tot;
                 }
+                __syncthreads();
             }
         }
         __syncthreads();
