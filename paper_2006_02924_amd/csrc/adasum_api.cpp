@@ -375,7 +375,6 @@ struct Plan {
     ResidentPlan resident;                // the whole reduction as one resident pass (form 0: the other passes run)
     TileTable unit_tiles;                 // its units in element order
     ResidentUnit* d_units = nullptr;      // and in launch order
-    bool resident_unfinished = false;     // a call's second launch failed: its tag was not moved on
     std::map<int, TileTable> comb_tables; // by capacity, built on first use
     std::vector<int> radices;
     std::vector<SmallLayer> small;        // layers reduced by the definition in fp64 (see kSmallLayer)
@@ -762,8 +761,6 @@ int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* o
     const Layout& lay = p->lay;
     const int L = lay.n_layers, K = p->K;
     const TileSet tiles = p->unit_tiles.view();
-    const int rc = small_gather(p, ws, grads, dtype, o, stream);
-    if (rc != ADASUM_OK) return rc;
     ResidentCall c;
     c.out_dtype = o.out_dtype;
     c.R = p->resident.R;
@@ -776,15 +773,16 @@ int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* o
     c.out = out;
     c.units = p->d_units;
     c.state.epoch = reinterpret_cast<int32_t*>(ws + lay.off_resident);
-    c.state.skipped = c.state.epoch + 1;
+    c.state.outcome = c.state.epoch + 1;
     c.state.partials = reinterpret_cast<unsigned long long*>(ws + lay.off_words);
     c.state.sums = c.state.partials + lay.partial_words;
     c.gram = o.layer_stats ? reinterpret_cast<double*>(ws + lay.off_gram) : nullptr;
     c.normparts = o.layer_stats ? reinterpret_cast<double*>(ws + lay.off_normparts) : nullptr;
     c.start = o.delta_start;
     c.order = o.order;
+    c.small = {p->d_small, tiles.layer_begin, p->n_small};
     c.wait_us = o.wait_us == 0 ? kResidentWaitUs : o.wait_us;
-    if (o.workspace != nullptr || p->borrowed || p->resident_unfinished) {
+    if (o.workspace != nullptr || p->borrowed) {
         // memory that is not the plan's own holds anything, and after a failed launch the next tag's words may be there
         ADASUM_LAUNCH(launch_zero_words(c.state.epoch, static_cast<int64_t>((lay.total - lay.off_resident) / sizeof(int32_t)), stream));
     }
@@ -796,12 +794,10 @@ int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* o
                    : dtype == ADASUM_BF16 ? (wide ? launch_resident_wide_bf16 : launch_resident_bf16)
                    : dtype == ADASUM_F16  ? (wide ? launch_resident_wide_f16 : launch_resident_f16)
                                           : launch_resident_f64;
-    p->resident_unfinished = true;
     ADASUM_TIMED(namebuf, bytes, stream, launch(c, stream));
-    p->resident_unfinished = false;
     if (o.layer_stats != nullptr)
         ADASUM_LAUNCH(launch_resident_stats(c.normparts, tiles, c.gram, c.R, K, L, o.layer_stats, stream));
-    return small_reduce(p, ws, out, o, stream);
+    return ADASUM_OK;
 }
 
 // ---- the level scheduler -------------------------------------------------------

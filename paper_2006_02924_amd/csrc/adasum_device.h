@@ -216,6 +216,21 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// x of the lane N places on in the same row of 16 lanes, round the row.  (Adding what is turned by 8, 4, 2 and 1 in this order
+// gives every lane the row's sum, with the bits of __shfl_xor by 8, 4, 2 and 1, without a trip through LDS for each.)
+template <int N>
+__device__ __forceinline__ double turned(double x) {
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), 0x120 + N, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), 0x120 + N, 0xf, 0xf, true);
+    return __longlong_as_double(static_cast<long long>(hi) << 32 | static_cast<long long>(static_cast<unsigned>(lo)));
+}
+__device__ __forceinline__ double of_lane(double x, int lane) {
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), lane), hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), lane);
+    return __longlong_as_double(static_cast<long long>(hi) << 32 | static_cast<long long>(static_cast<unsigned>(lo)));
+}
+
 // Sums every one of N per-lane values over the 64 lanes of a wave with N + N/2 + ... shuffles
 // instead of 6 N: at the step with mask m a lane whose bit m is clear keeps the even-indexed
 // values and hands the odd-indexed ones to its partner (and the other way round), so each step

@@ -329,7 +329,7 @@ struct ResidentUnit {
     int32_t len, layer;
     int32_t unit;                      // its place among the units in element order
     int32_t layer_first, layer_end;    // its layer's units
-    int32_t pad;
+    int32_t small;                     // elements of its layer if those are at most kSmallLayer, else 0
 };
 // The units in launch order, from the tile table of the plan's capacity (slots: workgroups that the chip holds).
 void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int slots,
@@ -338,9 +338,15 @@ void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_
 // What the workgroups of a resident pass share.  All zero before the first pass; every call has a tag of its own.
 struct ResidentState {
     int32_t* epoch;                 // calls so far
-    int32_t* skipped;               // [unit in launch order]: 1 = gave up waiting, 2 = then done by the second launch
+    int32_t* outcome;               // [unit in launch order]: what became of it and in which call (outcome_word)
     unsigned long long* partials;   // [unit][entry][2]
     unsigned long long* sums;       // [layer][entry][2]
+};
+// The layers of at most kSmallLayer elements, and the first unit of every layer.
+struct SmallTable {
+    const SmallLayer* layers;
+    const int32_t* unit_begin;
+    int n;
 };
 struct ResidentCall {
     int out_dtype, R, leaves, form, n_units;
@@ -352,6 +358,7 @@ struct ResidentCall {
     double* normparts;       // or null: [unit]
     const void* start;       // or null: the after-optimizer form
     int order;
+    SmallTable small;
     int wait_us;             // how long units wait for each other (-1: not at all)
 };
 int launch_resident_f32(const ResidentCall& c, void* stream);

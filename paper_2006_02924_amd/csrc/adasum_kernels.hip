@@ -2224,7 +2224,11 @@ resident_units_kernel(const adasum_tile* __restrict__ tiles, int n, const int32_
     u.unit = i;
     u.layer_first = layer_begin[t.layer];
     u.layer_end = layer_begin[t.layer + 1];
-    u.pad = 0;
+    // (a small layer is cut into two units at most)
+    int elems = 0;
+    if (u.layer_end - u.layer_first <= 2)
+        for (int j = u.layer_first; j < u.layer_end; ++j) elems += tiles[j].len;
+    u.small = elems <= kSmallLayer ? elems : 0;
     units[i] = u;
 }
 

@@ -370,7 +370,9 @@ void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_
     units.clear();
     units.reserve(tiles.size());
     for (size_t i = runs.size(); i-- > 0;)
-        for (int l : runs[i].layers)
+        for (int l : runs[i].layers) {
+            int64_t elems = 0;
+            for (int32_t t = layer_begin[l]; t < layer_begin[l + 1]; ++t) elems += tiles[t].len;
             for (int32_t t = layer_begin[l]; t < layer_begin[l + 1]; ++t) {
                 ResidentUnit u;
                 u.start = tiles[t].start;
@@ -379,9 +381,10 @@ void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_
                 u.unit = t;
                 u.layer_first = layer_begin[l];
                 u.layer_end = layer_begin[l + 1];
-                u.pad = 0;
+                u.small = elems <= kSmallLayer ? static_cast<int32_t>(elems) : 0;
                 units.push_back(u);
             }
+        }
 }
 
 }  // namespace adasum

@@ -5,7 +5,7 @@
 // combine_kernel, and operands that those read twice cross the fabric between the memory and the compute dies once.
 //
 // Its layers of some waves of units need the chip for themselves: beside other kernels units wait longer for each other,
-// and some give up (see resident_redo_kernel).  Measured beside 8192^3 bf16 matrix products, copies of 1 GB and small
+// and some give up (see redo_units).  Measured beside 8192^3 bf16 matrix products, copies of 1 GB and small
 // products (512 x 4096 x 4096) on another stream, us per reduction, three kernels in brackets: ResNet-50 sizes, K = 2 bf16 856
 // (1593), 68 (97), 56 (66); K = 8 fp32 1348 (1847), 368 (520), 503 (331); K = 16 bf16 1805 (1851), 1218 (529), 588 (366); a
 // quarter of them, K = 8 bf16, 1555 (1618), 96 (126), 72 (94).  So programs that reduce large models of 8 and more workers
@@ -121,6 +121,15 @@ __device__ __forceinline__ bool await(buffer_t b, const int (&offset)[N], u32x4 
         asm volatile("" ::: "memory");   // (the next look is another)
     }
 }
+// The tag of a call: calls before it, and one, in the low bits of the word that counts them.  Above those bits the launch's last workgroups
+// count themselves while it runs.
+constexpr int kTagMask = 0xffffff, kArrival = kTagMask + 1;
+__device__ __forceinline__ unsigned tag_of(int epoch) { return static_cast<unsigned>(epoch & kTagMask) + 1u; }
+// What became of a unit, with the call it is of.
+constexpr int kGaveUp = 1, kRedone = 2, kDone = 4;
+__device__ __forceinline__ int outcome_word(unsigned tag, int what) { return static_cast<int>((tag - 1u) << 3) | what; }
+__device__ __forceinline__ bool of_call(int word, unsigned tag) { return (word & 7) != 0 && word >> 3 == static_cast<int>(tag - 1u); }
+
 // Where entry e of the layer's unit number u lies (of W units, NP entries), in bytes: runs of kRun entries of every unit follow each
 // other, so that the lanes that sum a run over the units read whole memory sectors.  (With the NP entries of a unit in one
 // piece each lane's 16 bytes are a sector of their own, again with every look, and 136 waves of a layer look at 384 units:
@@ -143,10 +152,15 @@ __device__ __forceinline__ double run_sum(double v) {
     return v;
 }
 
-// Units a workgroup of the second launch looks at: 4, more where that would take more than 2048 workgroups (20000 units,
-// K = 9 bf16: with 5000 workgroups 279.6 us, with 1024 277.8), 32 at most.
-constexpr int kSkipScan = 4, kSkipScanMost = 32, kSkipBlocks = 2048;
+// Units a workgroup looks at that sees to those which gave up: 4, and more where the chip would not hold all such workgroups of a
+// launch of their own at once (K = 16 bf16, ResNet-50 sizes, with nothing to do: 1080 of them 8.2 us, 512 4.8), or
+// kArrival's place in its word has no room for them at the end of the launch itself.
+constexpr int kRedoScan = 4, kRedoBlocks = 96;
+constexpr int redo_per_cu(int R) { return R > 8 ? 2 : 4; }
+// form 1, whose units are small
+template <int SV, int SL> constexpr bool kRedoInLaunch = SV == 1 && SL == 0;
 constexpr int kTicksPerUs = 100;         // of wall_clock64
+constexpr long long kNoLimit = 0x7fffffffffffffffLL;
 
 // 16 bytes per lane straight from memory into LDS (lane l's at dst + 16 l; base: the same for all lanes): no registers are
 // held meanwhile.  A buffer load: after a global_load_lds, which counts as a flat access, the compiler waits for every
@@ -154,6 +168,12 @@ constexpr int kTicksPerUs = 100;         // of wall_clock64
 [[maybe_unused]] __device__ __forceinline__ void load_to_lds(const void* base, unsigned offset, void* dst) {
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, offset, 0, 0, 2 /* non-temporal */);
+}
+
+__device__ __forceinline__ unsigned long long same_for_all(unsigned long long v) {
+    const unsigned lo = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+    const unsigned hi = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)));
+    return static_cast<unsigned long long>(hi) << 32 | lo;
 }
 
 // f(0), f(1), ... f(N - 1), each argument a constant of its own type
@@ -165,10 +185,7 @@ __device__ __forceinline__ void each(F&& f) {
     }
 }
 
-// a value of an earlier launch: one ordinary load, through the caches
-__device__ __forceinline__ double read(buffer_t b, int offset) { return value(__builtin_amdgcn_raw_buffer_load_b128(b, offset, 0, 0)); }
-
-// ---- what both launches do with a layer's Gram matrix ----
+// ---- what is done with a layer's Gram matrix, by a unit and by those that redo it ----
 // the weights (by one wave; the workgroup waits for these few instructions)
 template <int R>
 __device__ __forceinline__ void unit_weights(const double* shG, double* shW, double* shQ, int order, int leaves, int lane) {
@@ -229,6 +246,252 @@ __device__ __forceinline__ double combine_ragged(const Operands& ops, const TI* 
     return static_cast<double>(zs) * static_cast<double>(zs);
 }
 
+// A layer of at most kSmallLayer elements, by the definition itself (as small_reduce_kernel, and with its bits): one wave, pair by
+// pair in fp64 in the order of the recursion, nothing stored in between.  Lanes 16 j .. 16 j + 15 hold the layer's elements
+// four times over, so that one sum over 16 lanes gives the dot product and both squared norms.  In launches of their own,
+// one before the pass that copies these layers and one after it, they cost 18 us of 98 (400 odd tensors, K = 12 bf16), here 4.
+// v: LDS, R x 16.  norm: where the squared norm of the result goes; gram: a matrix whose trace is the operands' squared norms
+// summed (either or both null).
+template <typename TI, typename TO, int R, bool DELTA>
+__device__ __forceinline__ void small_unit(const Operands& ops, const TI* start, TO* out, long long first, int len, int order,
+                                           int leaves, double (*v)[16], int lane, double* norm, double* gram) {
+    const int e = lane & 15, what = lane >> 4;
+    const bool live = e < len;
+    const long long idx = first + (live ? e : 0);
+    double base = 0.0;
+    if constexpr (DELTA) base = static_cast<double>(load_elem(start + idx));
+    double leafsq = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < R; ++k) {
+        double x = static_cast<double>(load_elem(static_cast<const TI*>(ops.pack[k]) + idx)) - base;
+        x = live && k < leaves ? x : 0.0;
+        leafsq = __builtin_fma(x, x, leafsq);
+        if (what == 0) v[k][e] = x;
+    }
+    __builtin_amdgcn_wave_barrier();
+    auto sum16 = [](double x) {
+        x += turned<8>(x);
+        x += turned<4>(x);
+        x += turned<2>(x);
+        return x + turned<1>(x);
+    };
+    auto pair = [&](double a, double b) {
+        const double s = sum16(what == 0 ? a * b : what == 1 ? a * a : b * b);
+        const double d = of_lane(s, 0), n1 = of_lane(s, 16), n2 = of_lane(s, 32);
+        const double ca = n1 > 0.0 ? 1.0 - d / (2.0 * n1) : 1.0;
+        const double cb = n2 > 0.0 ? 1.0 - d / (2.0 * n2) : 1.0;
+        return ca * a + cb * b;
+    };
+    double r = v[0][e];
+    int depth = 0;   // of the stack of finished sub-trees, kept where the leaves were
+    for (int k = 1; k < leaves; ++k) {
+        const double x = v[k][e];
+        if (order == ADASUM_ORDER_LINEAR) {
+            r = pair(r, x);
+            continue;
+        }
+        v[depth++][e] = r;
+        r = x;
+        // as many merges as nodes of the halving tree end with leaf k
+        for (int a = 0, b = leaves, merges = 0;;) {
+            if (b - a < 2) {
+                for (; merges > 0; --merges) r = pair(v[--depth][e], r);
+                break;
+            }
+            if (b == k + 1) ++merges;
+            const int mid = a + (b - a) / 2;
+            if (k < mid) b = mid;
+            else a = mid;
+        }
+    }
+    const double rsq = sum16(r * r);
+    leafsq = sum16(leafsq);
+    if (lane == 0 && norm != nullptr) *norm = rsq;
+    if (gram != nullptr && lane < R) gram[lane * (R + 1)] = lane == 0 ? leafsq : 0.0;   // (its trace is what is asked for)
+    if (live && what == 0) store_elem(out + idx, static_cast<typename Traits<TO>::acc_t>(DELTA ? r + base : r));
+}
+
+// The block-th four of a table's small layers, a wave each.
+template <typename TI, typename TO, int R, bool DELTA>
+__device__ __forceinline__ void small_layers(const Operands& ops, TO* out, SmallTable small, int block, double* __restrict__ gram,
+                                             double* __restrict__ normparts, const TI* start, int order, int leaves,
+                                             double (*shSmall)[kSmallLayer]) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = block * (kThreads / 64) + wave;
+    if (i >= small.n) return;
+    const SmallLayer l = small.layers[i];
+    double* norm = nullptr;
+    if (normparts != nullptr) {   // (a layer may be cut into two units)
+        norm = normparts + small.unit_begin[l.layer];
+        if (small.unit_begin[l.layer + 1] - small.unit_begin[l.layer] > 1 && lane == 0) norm[1] = 0.0;
+    }
+    small_unit<TI, TO, R, DELTA>(ops, start, out, l.start, l.len, order, leaves, shSmall + wave * R, lane, norm,
+                                 gram != nullptr ? gram + static_cast<long long>(l.layer) * (R * R) : nullptr);
+}
+
+// Units that gave up waiting, from memory, with the same arithmetic in the same order; and the tag moves on.  A workgroup
+// (`first` of `step`) looks at every step-th unit: a layer's units follow each other and tend to give up together.
+// SAME_LAUNCH: by the last workgroups of the launch itself, for reductions that the chip holds all at once in small units: a
+// second launch costs 4 us of 19 there.  They wait for every unit's outcome, without a limit: units are dispatched before them
+// and end within their own limit whatever these do.
+template <typename TI, typename TO, int R, bool DELTA, bool SAME_LAUNCH>
+__device__ __forceinline__ void redo_units(const Operands& ops, TO* out, const ResidentUnit* __restrict__ units, int n_units, int first,
+                                           int step, const ResidentState& st, double* __restrict__ gram,
+                                           double* __restrict__ normparts, const TI* start, int order, int leaves, double* shR,
+                                           double* shG, double* shW, double* shQ, double* shNorm, unsigned long long* shTodo) {
+    constexpr int G = Traits<TI>::VEC;
+    constexpr int NP = R * (R + 1) / 2;
+    constexpr int NW = kThreads / 64;
+    constexpr int ROWS = kThreads / NP;
+    constexpr int kDirect = direct_units(R);
+    constexpr int RL = R + (DELTA ? 1 : 0);
+    typedef typename Traits<TI>::acc_t acc_t;
+    constexpr bool NTS = !(sizeof(TI) == 2 && sizeof(TO) == 4 && R <= 2);   // as combine_kernel
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned tag = SAME_LAUNCH ? tag_of(__hip_atomic_load(st.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0u;
+    auto outcome = [&](int i) __attribute__((always_inline)) {
+        if constexpr (!SAME_LAUNCH) return st.outcome[i] & 7;
+        for (;;) {
+            const int word = __hip_atomic_load(st.outcome + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (of_call(word, tag)) return word & 7;
+            __builtin_amdgcn_s_sleep(8);
+        }
+    };
+    int layer = -1;
+    for (int i0 = first; i0 < n_units; i0 += step * kThreads) {
+        const int mine = i0 + tid * step;
+        const bool redo = mine < n_units && outcome(mine) == kGaveUp;
+        const unsigned long long some = __ballot(redo);
+        if (lane == 0) shTodo[wave] = some;
+        __syncthreads();
+        if (tid == 0 && i0 + step * kThreads >= n_units) {
+            if constexpr (!SAME_LAUNCH) {
+                if (first == 0) *st.epoch = static_cast<int>(tag_of(*st.epoch) & kTagMask);
+            } else if (__hip_atomic_fetch_add(st.epoch, kArrival, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kArrival == step - 1) {
+                // (the last of them to have seen its units' outcomes: all that read the tag have done so)
+                __hip_atomic_store(st.epoch, static_cast<int>(tag & kTagMask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        for (int w0 = 0; w0 < NW; ++w0) for (unsigned long long todo = same_for_all(shTodo[w0]); todo != 0; todo &= todo - 1) {
+            const int b = w0 * 64 + __builtin_ctzll(todo);
+            const int at = i0 + b * step;
+            const ResidentUnit t = units[at];
+            adasum_tile tile;
+            tile.start = t.start;
+            tile.len = t.len;
+            tile.layer = t.layer;
+            const Split s = split_tile<G>(tile);
+            const int W = t.layer_end - t.layer_first;
+            if (t.layer != layer) {   // (else its weights are there from the unit before)
+                layer = t.layer;
+                const buffer_t partials = buffer_of(st.partials + static_cast<long long>(t.layer_first) * (NP * 2), W * NP * 16);
+                // the sum of entry e over the units u0, u0 + step, ... of the layer (which have all been sent, or will be)
+                auto sum_units = [&](int e, int u0, int step) __attribute__((always_inline)) {
+                    constexpr int kAhead = 4;
+                    double v = 0.0;
+                    for (; u0 < W; u0 += step * kAhead) {
+                        int offset[kAhead];
+                        u32x4 x[kAhead];
+#pragma unroll
+                        for (int k = 0; k < kAhead; ++k) offset[k] = partial_at<NP>(u0 + k * step < W ? u0 + k * step : W - 1, e, W);
+                        if constexpr (SAME_LAUNCH) {
+                            await(partials, offset, x, tag, kNoLimit);
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < kAhead; ++k) x[k] = __builtin_amdgcn_raw_buffer_load_b128(partials, offset[k], 0, 0);
+                        }
+#pragma unroll
+                        for (int k = 0; k < kAhead; ++k)
+                            if (u0 + k * step < W) v += value(x[k]);
+                    }
+                    return v;
+                };
+                if (W <= kDirect) {
+                    const int row = tid / NP, e = tid % NP;
+                    if (row < ROWS) shR[row * NP + e] = sum_units(e, row, ROWS);
+                    __syncthreads();
+                    if (tid < NP) {
+                        double tot = shR[tid];
+#pragma unroll
+                        for (int k = 1; k < ROWS; ++k) tot += shR[k * NP + tid];
+                        int i, j;
+                        entry_to_ij<R, true>(tid, i, j);
+                        shG[i * R + j] = shG[j * R + i] = tot;
+                    }
+                } else {
+                    for (int run = 0; run < NP; run += kRun) {
+                        const int e = run + tid % kRun;
+                        const double v = run_sum(sum_units(e < NP ? e : NP - 1, tid / kRun, kRunUnits));
+                        if (lane < kRun) shR[wave * kRun + lane] = v;
+                        __syncthreads();
+                        if (tid < kRun && e < NP) {
+                            double tot = shR[tid];
+#pragma unroll
+                            for (int w = 1; w < NW; ++w) tot += shR[w * kRun + tid];
+                            int i, j;
+                            entry_to_ij<R, true>(e, i, j);
+                            shG[i * R + j] = shG[j * R + i] = tot;
+                        }
+                        __syncthreads();
+                    }
+                }
+                __syncthreads();
+                if (wave == 0) unit_weights<R>(shG, shW, shQ, order, leaves, lane);
+                if (gram != nullptr && t.unit == t.layer_first)
+                    for (int i = tid; i < R * R; i += kThreads) gram[static_cast<long long>(t.layer) * (R * R) + i] = shG[i];
+                __syncthreads();
+            }
+            acc_t w[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) w[r] = static_cast<acc_t>(shW[r]);
+            acc_t nacc = 0;
+            for (int j = tid; j < s.ng; j += kThreads) {
+                const long long idx = s.bs + static_cast<long long>(j) * G;
+                Granule<TI, G> q[RL];
+#pragma unroll
+                for (int r = 0; r < R; ++r) load_raw(q[r], static_cast<const TI*>(ops.pack[r]) + idx);
+                if constexpr (DELTA) load_raw(q[R], start + idx);
+                combine_granule<TI, TO, R, DELTA, NTS>(q, w, out + idx, nacc);
+            }
+            const int nedge = s.nh + s.nt;
+            double enorm = 0.0;
+            if (nedge > 0 && wave == 0) {
+                if (lane < nedge)
+                    enorm = combine_ragged<TI, TO, R, DELTA>(ops, start, shW, out, lane < s.nh ? s.start + lane : s.ts + (lane - s.nh));
+                if (normparts != nullptr) enorm = wave_sum(enorm);
+            }
+            if (normparts != nullptr) {
+                const acc_t ws = wave_sum(nacc);
+                if (lane == 0) shNorm[wave] = static_cast<double>(ws);
+                __syncthreads();
+                if (tid == 0) {
+                    double tot = shNorm[0];
+#pragma unroll
+                    for (int k = 1; k < NW; ++k) tot += shNorm[k];
+                    if (nedge > 0) tot += enorm;
+                    normparts[t.unit] = tot;
+                }
+            }
+            if (tid == 0) st.outcome[at] += kRedone - kGaveUp;
+            __syncthreads();   // (the next unit's sums go through the same memory)
+        }
+        __syncthreads();
+    }
+}
+
+struct ResidentArgs {
+    Operands ops;
+    void* out;
+    const ResidentUnit* units;
+    ResidentState state;
+    SmallTable small;
+    double* gram;
+    double* normparts;
+    const void* start;
+    int n_units, n_redo, wait_us, order, leaves;
+};
+
 // One workgroup per unit.  SV steps of 256 granules (16 bytes) of every operand stay in registers, SL in LDS; WPS
 // waves per SIMD are resident, i.e. WPS workgroups per compute unit.
 //
@@ -237,12 +500,12 @@ __device__ __forceinline__ double combine_ragged(const Operands& ops, const TI* 
 // The order of the sums depends on W alone: identical inputs give bit-identical outputs.
 //
 // Waiting is bounded, because nothing promises that a layer's workgroups run side by side (another stream's kernels
-// may hold part of the chip): after wait_us a workgroup marks its unit and ends; resident_redo_kernel does it then.
+// may hold part of the chip): after wait_us a workgroup marks its unit and ends; redo_units does it then.
+// The layers of at most kSmallLayer elements are left to small_layers.
 // DELTA: operands are x - start, the result is start + z (the single pass of the after-optimizer form).
 template <typename TI, typename TO, int R, bool DELTA, int SV, int SL, int WPS>
 __global__ void __launch_bounds__(kThreads, WPS)
-resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ units, const ResidentState st,
-                int wait_us, double* __restrict__ gram, double* __restrict__ normparts, const TI* start, int order, int leaves) {
+resident_kernel(const ResidentArgs args) {
     constexpr int G = Traits<TI>::VEC;
     constexpr int NP = R * (R + 1) / 2;
     constexpr int NW = kThreads / 64;
@@ -268,18 +531,45 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     __shared__ double shQ[4 * R];
     __shared__ double shNorm[NW];
     __shared__ int shSkip;
+    __shared__ unsigned long long shTodo[NW];
+    __shared__ double shSmall[kRedoInLaunch<SV, SL> && !MFMA ? NW * R : 1][kSmallLayer];
     __shared__ __align__(16) unsigned char shStage[MFMA ? NW * 16 * 1024 : 16];
     __shared__ __align__(16) unsigned char shKeep[SL > 0 ? SL * RL * kThreads * 16 : 16];
 
     // (WPS workgroups of the planner's count fit a compute unit: registers by the launch bounds, LDS here)
     static_assert(WPS * (sizeof(shP) + sizeof(shR) + sizeof(shEdge) + sizeof(shG) + sizeof(shW) + sizeof(shQ) + sizeof(shNorm) +
-                         sizeof(shSkip) + sizeof(shStage) + sizeof(shKeep) + 1280) <= 160 * 1024, "");
+                         sizeof(shSkip) + sizeof(shTodo) + sizeof(shSmall) + sizeof(shStage) + sizeof(shKeep) + 1280) <= 160 * 1024, "");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned tag = static_cast<unsigned>(*st.epoch) + 1u;
     const int at = static_cast<int>(blockIdx.x);
-    const ResidentUnit t = units[at];
+    if constexpr (kRedoInLaunch<SV, SL>) {
+        const int n_units = args.n_units, n_redo = args.n_redo;
+        if (at >= n_units + n_redo) {
+            small_layers<TI, TO, R, DELTA>(args.ops, static_cast<TO*>(args.out), args.small, at - n_units - n_redo, args.gram, args.normparts,
+                                           static_cast<const TI*>(args.start), args.order, args.leaves,
+                                           MFMA ? reinterpret_cast<double(*)[kSmallLayer]>(shStage) : shSmall);
+            return;
+        }
+        if (at >= n_units) {
+            redo_units<TI, TO, R, DELTA, true>(args.ops, static_cast<TO*>(args.out), args.units, n_units, at - n_units, n_redo, args.state,
+                                               args.gram, args.normparts, static_cast<const TI*>(args.start), args.order, args.leaves, shR,
+                                               shG, shW, shQ, shNorm, shTodo);
+            return;
+        }
+    }
+    const Operands& ops = args.ops;
+    const ResidentUnit* __restrict__ const units = args.units;
+    const ResidentState st = args.state;
+    const TI* const start = static_cast<const TI*>(args.start);
+    const ResidentUnit t = units[at];   // (before any atomic access: scalar loads)
+    // (while it runs, only the last workgroups of this launch itself write to that word)
+    const unsigned tag = tag_of(kRedoInLaunch<SV, SL> ? __hip_atomic_load(st.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *st.epoch);
+    auto decide = [&](int what) __attribute__((always_inline)) {
+        if constexpr (!kRedoInLaunch<SV, SL>) {
+            if (what == kGaveUp && tid == 0) st.outcome[at] = kGaveUp;
+        } else if (tid == 0) __hip_atomic_store(st.outcome + at, outcome_word(tag, what), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     const int W = t.layer_end - t.layer_first;
     const buffer_t partials = buffer_of(st.partials + static_cast<long long>(t.layer_first) * (NP * 2), W * NP * 16);
     adasum_tile tile;
@@ -453,11 +743,25 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
         }
     }
 
+    if (t.small > 0) {   // (small_layers does it; a branch on it further up would cut the load of `t` in two)
+        decide(kDone);
+        return;
+    }
+    // The other arguments are read here: fetched at the start with the rest, they do not fit the scalar registers beside the
+    // operands' addresses, and a kernel that has to put some away elsewhere starts its waves later (K = 16 bf16, ResNet-50
+    // sizes, 246 us instead of 241).
+    typedef const __attribute__((address_space(4))) ResidentArgs* arguments_t;
+    arguments_t late = (arguments_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(late));
+    TO* const out = static_cast<TO*>(late->out);
+    double* const gram = late->gram;
+    double* const normparts = late->normparts;
+    const int order = late->order, leaves = late->leaves, wait_us = late->wait_us;
     if (W > 1) {
         const long long deadline = static_cast<long long>(wall_clock64()) + static_cast<long long>(wait_us) * kTicksPerUs;
         bool ok = wait_us >= 0;
         // the sum of entry e over the units u0, u0 + step, ... of the layer, kAhead of them looked at side by side
-        auto sum_ahead = [&](auto ahead, int e, int u0, int step) {
+        auto sum_ahead = [&](auto ahead, int e, int u0, int step) __attribute__((always_inline)) {
             constexpr int kAhead = decltype(ahead)::value;
             double v = 0.0;
             for (; u0 < W; u0 += step * kAhead) {
@@ -472,7 +776,7 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
             }
             return v;
         };
-        auto sum_units = [&](int e, int u0, int step) {
+        auto sum_units = [&](int e, int u0, int step) __attribute__((always_inline)) {
             if (W <= step) return sum_ahead(std::integral_constant<int, 1>(), e, u0, step);
             return W <= 2 * step ? sum_ahead(std::integral_constant<int, 2>(), e, u0, step) : sum_ahead(std::integral_constant<int, 4>(), e, u0, step);
         };
@@ -518,14 +822,14 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     }
     __syncthreads();
     if (shSkip) {
-        if (tid == 0) st.skipped[at] = 1;
+        decide(kGaveUp);
         return;
     }
+    decide(kDone);
     if (wave == 0) unit_weights<R>(shG, shW, shQ, order, leaves, lane);
     if (gram != nullptr && t.unit == t.layer_first)   // (for the statistics)
         for (int i = tid; i < R * R; i += kThreads) gram[static_cast<long long>(t.layer) * (R * R) + i] = shG[i];
     __syncthreads();
-
     acc_t w[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) w[r] = static_cast<acc_t>(shW[r]);
@@ -572,147 +876,57 @@ resident_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ un
     }
 }
 
-// The second launch: the units that gave up waiting, from memory, with the same arithmetic in the same order (by now
-// every partial sum is there), and the tag moves on.  A workgroup looks at every gridDim.x-th unit: a layer's units
-// follow each other and tend to give up together.  Usually there is nothing to do, and the launch costs 4 us at 3726
-// units.  Where every unit gave up it streams like a combine pass: K = 8 fp32 ResNet-50 sizes 337 us in all (with 32 units
-// a workgroup 713; three kernels 297), K = 16 bf16 630 (1861; 305), K = 2 bf16 94 (322; 51).
+// The second launch of the other forms.  Usually there is nothing to do, and it costs 4 us at 3726 units.  Where every unit gave
+// up it streams like a combine pass: ResNet-50 sizes, K = 8 fp32 318 us in all, K = 16 bf16 598, K = 2 bf16 93.
 template <typename TI, typename TO, int R, bool DELTA>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, redo_per_cu(R))
 resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ units, int n_units, const ResidentState st,
-                     double* __restrict__ gram, double* __restrict__ normparts, const TI* start, int order, int leaves) {
-    constexpr int G = Traits<TI>::VEC;
+                     double* __restrict__ gram, double* __restrict__ normparts, const TI* start, int order, int leaves, int n_redo,
+                     const SmallTable small) {
     constexpr int NP = R * (R + 1) / 2;
     constexpr int NW = kThreads / 64;
     constexpr int ROWS = kThreads / NP;
-    constexpr int kDirect = direct_units(R);
-    constexpr int RL = R + (DELTA ? 1 : 0);
-    typedef typename Traits<TI>::acc_t acc_t;
-    constexpr bool NTS = !(sizeof(TI) == 2 && sizeof(TO) == 4 && R <= 2);   // as combine_kernel
+    const int at = static_cast<int>(blockIdx.x);
     __shared__ double shR[ROWS * NP > NW * kRun ? ROWS * NP : NW * kRun];
     __shared__ double shG[R * R];
     __shared__ double shW[R];
     __shared__ double shQ[4 * R];
     __shared__ double shNorm[NW];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const long long mine = static_cast<long long>(blockIdx.x) + static_cast<long long>(lane) * gridDim.x;
-    const bool redo = mine < n_units && st.skipped[mine] == 1;
-    unsigned long long todo = __ballot(redo);
-    __syncthreads();
-    if (redo && wave == 0) st.skipped[mine] = 2;
-    if (blockIdx.x == 0 && tid == 0) *st.epoch = *st.epoch + 1;
-    while (todo != 0) {
-        const int b = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        const ResidentUnit t = units[static_cast<long long>(blockIdx.x) + static_cast<long long>(b) * gridDim.x];
-        adasum_tile tile;
-        tile.start = t.start;
-        tile.len = t.len;
-        tile.layer = t.layer;
-        const Split s = split_tile<G>(tile);
-        const int W = t.layer_end - t.layer_first;
-        const buffer_t partials = buffer_of(st.partials + static_cast<long long>(t.layer_first) * (NP * 2), W * NP * 16);
-        // the sum of entry e over the units u0, u0 + step, ... of the layer: all loads in flight at a time
-        auto sum_units = [&](auto most, int e, int u0, int step) {
-            constexpr int kMost = decltype(most)::value;
-            double x[kMost], v = 0.0;
-#pragma unroll
-            for (int k = 0; k < kMost; ++k) x[k] = read(partials, partial_at<NP>(u0 + k * step < W ? u0 + k * step : W - 1, e, W));
-#pragma unroll
-            for (int k = 0; k < kMost; ++k)
-                if (u0 + k * step < W) v += x[k];
-            return v;
-        };
-        if (W <= kDirect) {
-            constexpr int kMost = (kDirect + ROWS - 1) / ROWS;
-            const int row = tid / NP, e = tid % NP;
-            const double v = sum_units(std::integral_constant<int, kMost>(), e, row, ROWS);
-            if (row < ROWS) shR[row * NP + e] = v;
-            __syncthreads();
-            if (tid < NP) {
-                double tot = shR[tid];
-#pragma unroll
-                for (int k = 1; k < ROWS; ++k) tot += shR[k * NP + tid];
-                int i, j;
-                entry_to_ij<R, true>(tid, i, j);
-                shG[i * R + j] = shG[j * R + i] = tot;
-            }
-        } else {
-            // (a layer has at most 768 units)
-            constexpr int kMost = (3 * kResidentCus + kRunUnits - 1) / kRunUnits;
-            for (int run = 0; run < NP; run += kRun) {
-                const int e = run + tid % kRun;
-                const double v = run_sum(sum_units(std::integral_constant<int, kMost>(), e < NP ? e : NP - 1, tid / kRun, kRunUnits));
-                if (lane < kRun) shR[wave * kRun + lane] = v;
-                __syncthreads();
-                if (tid < kRun && e < NP) {
-                    double tot = shR[tid];
-#pragma unroll
-                    for (int w = 1; w < NW; ++w) tot += shR[w * kRun + tid];
-                    int i, j;
-                    entry_to_ij<R, true>(e, i, j);
-                    shG[i * R + j] = shG[j * R + i] = tot;
-                }
-                __syncthreads();
-            }
-        }
-        __syncthreads();
-        if (wave == 0) unit_weights<R>(shG, shW, shQ, order, leaves, lane);
-        if (gram != nullptr && t.unit == t.layer_first)
-            for (int i = tid; i < R * R; i += kThreads) gram[static_cast<long long>(t.layer) * (R * R) + i] = shG[i];
-        __syncthreads();
-        acc_t w[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) w[r] = static_cast<acc_t>(shW[r]);
-        acc_t nacc = 0;
-        for (int j = tid; j < s.ng; j += kThreads) {
-            const long long idx = s.bs + static_cast<long long>(j) * G;
-            Granule<TI, G> q[RL];
-#pragma unroll
-            for (int r = 0; r < R; ++r) load_raw(q[r], static_cast<const TI*>(ops.pack[r]) + idx);
-            if constexpr (DELTA) load_raw(q[R], start + idx);
-            combine_granule<TI, TO, R, DELTA, NTS>(q, w, out + idx, nacc);
-        }
-        const int nedge = s.nh + s.nt;
-        double enorm = 0.0;
-        if (nedge > 0 && wave == 0) {
-            if (lane < nedge)
-                enorm = combine_ragged<TI, TO, R, DELTA>(ops, start, shW, out, lane < s.nh ? s.start + lane : s.ts + (lane - s.nh));
-            if (normparts != nullptr) enorm = wave_sum(enorm);
-        }
-        if (normparts != nullptr) {
-            const acc_t ws = wave_sum(nacc);
-            if (lane == 0) shNorm[wave] = static_cast<double>(ws);
-            __syncthreads();
-            if (tid == 0) {
-                double tot = shNorm[0];
-#pragma unroll
-                for (int k = 1; k < NW; ++k) tot += shNorm[k];
-                if (nedge > 0) tot += enorm;
-                normparts[t.unit] = tot;
-            }
-        }
-        __syncthreads();   // (the next unit's sums go through the same memory)
-    }
+    __shared__ unsigned long long shTodo[NW];
+    __shared__ double shSmall[NW * R][kSmallLayer];
+    if (at >= n_redo)
+        small_layers<TI, TO, R, DELTA>(ops, out, small, at - n_redo, gram, normparts, start, order, leaves, shSmall);
+    else
+        redo_units<TI, TO, R, DELTA, false>(ops, out, units, n_units, at, n_redo, st, gram, normparts, start, order, leaves, shR, shG,
+                                            shW, shQ, shNorm, shTodo);
 }
 
 template <typename TI, typename TO, int R, bool DELTA, int SV, int SL, int WPS>
 int launch_s(const ResidentCall& c, hipStream_t stream) {
-    hipLaunchKernelGGL((resident_kernel<TI, TO, R, DELTA, SV, SL, WPS>), dim3(static_cast<unsigned>(c.n_units)),
-                       dim3(kThreads), 0, stream, c.ops, static_cast<TO*>(c.out), c.units, c.state, c.wait_us,
-                       c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves);
-    return static_cast<int>(hipGetLastError());
-}
-
-template <typename TI, typename TO, int R, bool DELTA>
-int launch_redo(const ResidentCall& c, hipStream_t stream) {
-    auto blocks = [&](int scan) { return (static_cast<long long>(c.n_units) + scan - 1) / scan; };
-    const long long n = blocks(kSkipScan) <= kSkipBlocks ? blocks(kSkipScan) : std::max<long long>(kSkipBlocks, blocks(kSkipScanMost));
-    hipLaunchKernelGGL((resident_redo_kernel<TI, TO, R, DELTA>), dim3(static_cast<unsigned>(n)),
+    const bool same = kRedoInLaunch<SV, SL> && c.n_units <= WPS * kResidentCus;
+    const int redo = std::min((c.n_units + kRedoScan - 1) / kRedoScan, same ? kRedoBlocks : redo_per_cu(R) * kResidentCus);
+    const int small = (c.small.n + kThreads / 64 - 1) / (kThreads / 64);
+    ResidentArgs args;
+    args.ops = c.ops;
+    args.out = c.out;
+    args.units = c.units;
+    args.state = c.state;
+    args.small = c.small;
+    args.gram = c.gram;
+    args.normparts = c.normparts;
+    args.start = c.start;
+    args.n_units = c.n_units;
+    args.n_redo = redo;
+    args.wait_us = c.wait_us;
+    args.order = c.order;
+    args.leaves = c.leaves;
+    hipLaunchKernelGGL((resident_kernel<TI, TO, R, DELTA, SV, SL, WPS>), dim3(static_cast<unsigned>(c.n_units + (same ? redo + small : 0))),
+                       dim3(kThreads), 0, stream, args);
+    const int e = static_cast<int>(hipGetLastError());
+    if (same || e != 0) return e;
+    hipLaunchKernelGGL((resident_redo_kernel<TI, TO, R, DELTA>), dim3(static_cast<unsigned>(redo + small)),
                        dim3(kThreads), 0, stream, c.ops, static_cast<TO*>(c.out), c.units, c.n_units, c.state,
-                       c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves);
+                       c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves, redo, c.small);
     return static_cast<int>(hipGetLastError());
 }
 
@@ -727,7 +941,7 @@ int launch_r(const ResidentCall& c, hipStream_t stream) {
     }
     if (c.form == 3)
         e = launch_s<TI, TO, R, DELTA, resident_register_steps(D, R, DELTA, 3), resident_lds_steps(D, R, DELTA, 3), resident_per_cu(D, R, 3)>(c, stream);
-    return e != 0 ? e : launch_redo<TI, TO, R, DELTA>(c, stream);
+    return e;
 }
 
 template <typename TI, typename TO, bool DELTA>
