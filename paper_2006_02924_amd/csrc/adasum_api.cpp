@@ -375,6 +375,7 @@ struct Plan {
     ResidentPlan resident;                // the whole reduction as one resident pass (form 0: the other passes run)
     TileTable unit_tiles;                 // its units in element order
     ResidentUnit* d_units = nullptr;      // and in launch order
+    bool prepared = false;                // borrowed memory whose resident section is set to zero already
     std::map<int, TileTable> comb_tables; // by capacity, built on first use
     std::vector<int> radices;
     std::vector<SmallLayer> small;        // layers reduced by the definition in fp64 (see kSmallLayer)
@@ -782,7 +783,7 @@ int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* o
     c.order = o.order;
     c.small = {p->d_small, tiles.layer_begin, p->n_small};
     c.wait_us = o.wait_us == 0 ? kResidentWaitUs : o.wait_us;
-    if (o.workspace != nullptr || p->borrowed) {
+    if ((o.workspace != nullptr || p->borrowed) && !p->prepared) {
         // memory that is not the plan's own holds anything, and after a failed launch the next tag's words may be there
         ADASUM_LAUNCH(launch_zero_words(c.state.epoch, static_cast<int64_t>((lay.total - lay.off_resident) / sizeof(int32_t)), stream));
     }
@@ -1448,8 +1449,35 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
     ADASUM_HIP(hipGetDevice(&plan.device));
 
     int64_t* d_offsets = reinterpret_cast<int64_t*>(base + off_offsets);
-    ADASUM_LAUNCH(launch_put_offsets(layer_offsets, L, d_offsets, stream));
-    if (plan.resident.form > 0) {
+    plan.prepared = plan.resident.form > 0 && L <= kSetupLayers;
+    if (!plan.prepared) ADASUM_LAUNCH(launch_put_offsets(layer_offsets, L, d_offsets, stream));
+    if (plan.prepared) {
+        TileTable& u = plan.unit_tiles;
+        u.n_borrowed = plan.resident.n_units;
+        u.d_layer_begin = reinterpret_cast<int32_t*>(base + off_unit_begin);
+        plan.d_units = reinterpret_cast<ResidentUnit*>(base + off_units);
+        plan.d_small = reinterpret_cast<SmallLayer*>(base + off_small);
+        // (where the chip holds all units at once their order does not matter)
+        std::vector<int> order;
+        const int slots = resident_slots(dtype, plan.resident.R, plan.resident.form);
+        if (plan.resident.n_units > slots) {
+            try {
+                std::vector<int32_t> begin(static_cast<size_t>(L) + 1, 0);
+                for (int l = 0; l < L; ++l) {
+                    const int64_t lo = layer_offsets[l], hi = layer_offsets[l + 1], cap = plan.resident.capacity;
+                    begin[l + 1] = begin[l] + (hi > lo ? static_cast<int32_t>((hi - 1) / cap - lo / cap + 1) : 0);
+                }
+                order_layers(begin, slots, order);
+            } catch (const std::bad_alloc&) {
+                return ADASUM_ERR_OUT_OF_MEMORY;
+            }
+        }
+        const Layout& lay = plan.lay;
+        ADASUM_LAUNCH(launch_resident_setup(layer_offsets, L, plan.resident.capacity, order, static_cast<int>(plan.resident.n_units),
+                                            plan.d_units, u.d_layer_begin, plan.d_small,
+                                            reinterpret_cast<int32_t*>(base + off_ws + lay.off_resident),
+                                            static_cast<int64_t>((lay.total - lay.off_resident) / sizeof(int32_t)), stream));
+    } else if (plan.resident.form > 0) {
         TileTable& u = plan.unit_tiles;
         u.n_borrowed = plan.resident.n_units;
         u.d_tiles = reinterpret_cast<adasum_tile*>(base + off_unit_tiles);
@@ -1482,7 +1510,7 @@ int reduce_noalloc_impl(const void* const* grads, int K, const int64_t* layer_of
         return ADASUM_ERR_OUT_OF_MEMORY;
     }
     plan.d_small = reinterpret_cast<SmallLayer*>(base + off_small);
-    ADASUM_LAUNCH(launch_build_small(d_offsets, L, plan.n_small, plan.d_small, stream));
+    if (!plan.prepared) ADASUM_LAUNCH(launch_build_small(d_offsets, L, plan.n_small, plan.d_small, stream));
     if (plan.wide_spans.n_parts > 0) {
         // the host-built span table travels like the layer table: as 8-byte words in kernel arguments
         TileTable& w = plan.wide_spans;

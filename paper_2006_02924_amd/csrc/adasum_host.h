@@ -331,6 +331,8 @@ struct ResidentUnit {
     int32_t layer_first, layer_end;    // its layer's units
     int32_t small;                     // elements of its layer if those are at most kSmallLayer, else 0
 };
+// The layers that have units, in launch order (slots: workgroups that the chip holds).
+void order_layers(const std::vector<int32_t>& layer_begin, int slots, std::vector<int>& layers);
 // The units in launch order, from the tile table of the plan's capacity (slots: workgroups that the chip holds).
 void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int slots,
                  std::vector<ResidentUnit>& units);
@@ -372,6 +374,12 @@ int launch_resident_wide_f16(const ResidentCall& c, void* stream);
 int launch_zero_words(int32_t* p, int64_t n, void* stream);
 // The units in element order from their tile table (where nothing may be copied from the host).
 int launch_resident_units(const TileSet& t, ResidentUnit* units, void* stream);
+// All that a resident pass finds in memory before it starts, in one launch, for tables of at most kSetupLayers layers: the units
+// (layers in the order given, which may be empty: in element order), the first unit of every layer, the table of small
+// layers, and `n_words` words of zeros.
+constexpr int kSetupLayers = 383;
+int launch_resident_setup(const int64_t* layer_offsets, int n_layers, int64_t capacity, const std::vector<int>& order, int n_units,
+                          ResidentUnit* units, int32_t* layer_begin, SmallLayer* small, int32_t* words, int64_t n_words, void* stream);
 // stats[layer] = squared norm of the result (its units' sums), sum of the leaves' (the trace of the Gram matrix).
 int launch_resident_stats(const double* normparts, const TileSet& t, const double* gram, int R, int leaves, int n_layers,
                           double* stats, void* stream);

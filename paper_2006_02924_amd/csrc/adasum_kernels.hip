@@ -2240,6 +2240,122 @@ int launch_resident_units(const TileSet& t, ResidentUnit* units, void* stream) {
     return check_launch();
 }
 
+// The layer table and the layers' launch order travel in the kernel's arguments.  Every workgroup works out where the layers' units
+// begin (a few hundred layers: one sum over the workgroup) and writes its share of everything.  As five launches, one after the
+// other, this took some 15 us of the 99 of a reduction (ResNet-50 sizes, K = 6 binary16: 91 now); it is all latency.
+struct SetupChunk {
+    long long offset[kSetupLayers + 1];
+    unsigned short order[kSetupLayers];
+};
+__global__ void __launch_bounds__(kThreads)
+resident_setup_kernel(const SetupChunk c, int n_layers, int n_ordered, long long capacity, int n_units, ResidentUnit* __restrict__ units,
+                      int32_t* __restrict__ layer_begin, SmallLayer* __restrict__ small, u32x4* __restrict__ words, long long n_quads) {
+    __shared__ long long offset[kSetupLayers + 1];
+    __shared__ int begin[kSetupLayers + 1], at[kSetupLayers + 1];   // first units: in element order, and in launch order
+    __shared__ int sums[2][kThreads / 64];
+    __shared__ unsigned short order[kSetupLayers + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (long long i = static_cast<long long>(blockIdx.x) * kThreads + tid; i < n_quads; i += static_cast<long long>(gridDim.x) * kThreads)
+        words[i] = u32x4{0u, 0u, 0u, 0u};
+    for (int l = tid; l <= n_layers; l += kThreads) offset[l] = c.offset[l];
+    for (int p = tid; p < n_ordered; p += kThreads) order[p] = c.order[p];
+    __syncthreads();
+    auto count = [&](int l) {
+        const long long lo = offset[l], hi = offset[l + 1];
+        return hi > lo ? static_cast<int>((hi - 1) / capacity - lo / capacity + 1) : 0;
+    };
+    // two neighbours a lane (of the layers, and of their order), summed over the lanes and waves before it
+    static_assert(kSetupLayers + 1 <= 2 * kThreads, "");
+    int n[2][2], before[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        n[0][i] = 2 * tid + i < n_layers ? count(2 * tid + i) : 0;
+        n[1][i] = 2 * tid + i < n_ordered ? count(order[2 * tid + i]) : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        int v = n[k][0] + n[k][1];
+        before[k] = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(v, d, 64);
+            if (lane >= d) v += o;
+        }
+        if (lane == 63) sums[k][wave] = v;
+        before[k] = v - before[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        for (int w = 0; w < wave; ++w) before[k] += sums[k][w];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (2 * tid + i <= n_layers) begin[2 * tid + i] = before[0] + (i == 1 ? n[0][0] : 0);
+        if (2 * tid + i <= n_ordered) at[2 * tid + i] = before[1] + (i == 1 ? n[1][0] : 0);
+    }
+    __syncthreads();
+    const int* const first = n_ordered > 0 ? at : begin;
+    const int n_first = n_ordered > 0 ? n_ordered : n_layers;
+    for (int i = static_cast<int>(blockIdx.x) * kThreads + tid; i < n_units; i += static_cast<int>(gridDim.x) * kThreads) {
+        int a = 0, b = n_first;   // the last place whose first unit is not after i
+        while (b - a > 1) {
+            const int mid = (a + b) / 2;
+            if (first[mid] <= i) a = mid;
+            else b = mid;
+        }
+        const int l = n_ordered > 0 ? order[a] : a, k = i - first[a];
+        const long long lo = offset[l], hi = offset[l + 1], tile = lo / capacity + k;
+        ResidentUnit u;
+        u.start = k == 0 ? lo : tile * capacity;
+        u.len = static_cast<int32_t>(((tile + 1) * capacity < hi ? (tile + 1) * capacity : hi) - u.start);
+        u.layer = l;
+        u.unit = begin[l] + k;
+        u.layer_first = begin[l];
+        u.layer_end = begin[l + 1];
+        u.small = hi - lo <= kSmallLayer ? static_cast<int32_t>(hi - lo) : 0;
+        units[i] = u;
+    }
+    if (blockIdx.x == 0) {
+        for (int l = tid; l <= n_layers; l += kThreads) layer_begin[l] = begin[l];
+    }
+    if (blockIdx.x == gridDim.x - 1 && wave == 0) {
+        int found = 0;
+        for (int l0 = 0; l0 < n_layers; l0 += 64) {
+            const int l = l0 + lane;
+            const long long len = l < n_layers ? offset[l + 1] - offset[l] : 0;
+            const bool is = len >= 1 && len <= kSmallLayer;
+            const unsigned long long mask = __ballot(is);
+            if (is) {
+                SmallLayer s;
+                s.start = offset[l];
+                s.len = static_cast<int32_t>(len);
+                s.layer = l;
+                s.coff = 0;   // (a place in a copy that the resident pass has not)
+                s.pad = 0;
+                small[found + __popcll(mask & ((1ull << lane) - 1))] = s;
+            }
+            found += __popcll(mask);
+        }
+    }
+}
+
+int launch_resident_setup(const int64_t* layer_offsets, int n_layers, int64_t capacity, const std::vector<int>& order, int n_units,
+                          ResidentUnit* units, int32_t* layer_begin, SmallLayer* small, int32_t* words, int64_t n_words, void* stream) {
+    if (n_layers < 1 || n_layers > kSetupLayers || order.size() > static_cast<size_t>(n_layers) || capacity < 1 || n_units < 1 ||
+        n_words < 0 || n_words % 4 != 0 || (reinterpret_cast<uintptr_t>(words) & 15) != 0)
+        return static_cast<int>(hipErrorInvalidValue);
+    SetupChunk c;
+    std::memset(&c, 0, sizeof(c));
+    for (int l = 0; l <= n_layers; ++l) c.offset[l] = layer_offsets[l];
+    for (size_t i = 0; i < order.size(); ++i) c.order[i] = static_cast<unsigned short>(order[i]);
+    const long long quads = n_words / 4;
+    const long long blocks = std::min<long long>(std::max<long long>((quads + 2 * kThreads - 1) / (2 * kThreads), (n_units + kThreads - 1) / kThreads), 512);
+    hipLaunchKernelGGL(resident_setup_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, static_cast<hipStream_t>(stream), c,
+                       n_layers, static_cast<int>(order.size()), static_cast<long long>(capacity), n_units, units, layer_begin, small,
+                       reinterpret_cast<u32x4*>(words), quads);
+    return check_launch();
+}
+
 // (an empty layer has no units and no Gram matrix: zeros)
 __global__ void __launch_bounds__(64)
 resident_stats_kernel(const double* __restrict__ normparts, const int32_t* __restrict__ layer_begin,

@@ -336,8 +336,7 @@ void add_resident(Layout& lay, const ResidentPlan& p) {
     lay.need = lay.total = off;
 }
 
-void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int slots,
-                 std::vector<ResidentUnit>& units) {
+void order_layers(const std::vector<int32_t>& layer_begin, int slots, std::vector<int>& layers) {
     // A layer's units wait for each other, so they should be on the chip together: whole layers are packed into runs of
     // half the workgroups that the chip holds (a larger layer into a run of all of them), the largest that still fits
     // next; the runs with the largest layers last.  In element order, units at the seams of such runs waited a whole
@@ -367,24 +366,31 @@ void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_
         runs[r].layers.push_back(l);
         runs[r].room -= n;
     }
+    layers.clear();
+    for (size_t i = runs.size(); i-- > 0;) layers.insert(layers.end(), runs[i].layers.begin(), runs[i].layers.end());
+}
+
+void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_t>& layer_begin, int slots,
+                 std::vector<ResidentUnit>& units) {
+    std::vector<int> layers;
+    order_layers(layer_begin, slots, layers);
     units.clear();
     units.reserve(tiles.size());
-    for (size_t i = runs.size(); i-- > 0;)
-        for (int l : runs[i].layers) {
-            int64_t elems = 0;
-            for (int32_t t = layer_begin[l]; t < layer_begin[l + 1]; ++t) elems += tiles[t].len;
-            for (int32_t t = layer_begin[l]; t < layer_begin[l + 1]; ++t) {
-                ResidentUnit u;
-                u.start = tiles[t].start;
-                u.len = tiles[t].len;
-                u.layer = l;
-                u.unit = t;
-                u.layer_first = layer_begin[l];
-                u.layer_end = layer_begin[l + 1];
-                u.small = elems <= kSmallLayer ? static_cast<int32_t>(elems) : 0;
-                units.push_back(u);
-            }
+    for (int l : layers) {
+        int64_t elems = 0;
+        for (int32_t t = layer_begin[l]; t < layer_begin[l + 1]; ++t) elems += tiles[t].len;
+        for (int32_t t = layer_begin[l]; t < layer_begin[l + 1]; ++t) {
+            ResidentUnit u;
+            u.start = tiles[t].start;
+            u.len = tiles[t].len;
+            u.layer = l;
+            u.unit = t;
+            u.layer_first = layer_begin[l];
+            u.layer_end = layer_begin[l + 1];
+            u.small = elems <= kSmallLayer ? static_cast<int32_t>(elems) : 0;
+            units.push_back(u);
         }
+    }
 }
 
 }  // namespace adasum
