@@ -125,12 +125,12 @@ def check(code: int) -> None:
 # ---- marshalling helpers ------------------------------------------------------
 
 def _offsets(layer_offsets: Sequence[int]):
-    arr = (C.c_int64 * len(layer_offsets))(*[int(o) for o in layer_offsets])
+    arr = (C.c_int64 * len(layer_offsets))(*map(int, layer_offsets))
     return arr, len(layer_offsets) - 1
 
 
 def _ptr_array(tensors):
-    return (C.c_void_p * len(tensors))(*[C.c_void_p(t.data_ptr()) for t in tensors])
+    return (C.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors])
 
 
 def _dtype_code(t) -> int:
@@ -159,18 +159,24 @@ def _torch_dtype(code: int):
 def _stream(stream) -> C.c_void_p:
     import torch
     if stream is None:
+        # (torch.cuda.current_stream() makes a Stream object around the same handle; a call over a small model is bound by what
+        # happens here)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return C.c_void_p(raw(torch.cuda.current_device()))
         stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
 
 def _check_inputs(tensors, N):
-    dev = tensors[0].device
-    if dev.type != "cuda":
+    first = tensors[0]
+    if not first.is_cuda:
         raise ValueError("libadasum works on device memory only (no CPU path)")
+    dev, dtype = first.get_device(), first.dtype
     for t in tensors:
-        if t.device != dev or t.dtype != tensors[0].dtype:
+        if not t.is_cuda or t.get_device() != dev or t.dtype != dtype:
             raise ValueError("all gradients must share device and dtype")
-        if not t.is_contiguous() or t.dim() != 1 or t.numel() != N:
+        if t.dim() != 1 or t.numel() != N or not t.is_contiguous():
             raise ValueError("every gradient must be a contiguous 1-D buffer of layer_offsets[-1] elements")
 
 
