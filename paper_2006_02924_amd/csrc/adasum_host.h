@@ -300,7 +300,7 @@ constexpr int resident_register_steps(int dtype, int R, bool delta, int form) {
     return steps < 16 ? (steps < 1 ? 1 : steps) : 16;
 }
 constexpr int resident_lds_steps(int dtype, int R, bool delta, int form) {
-    if (resident_matrix(dtype, R)) return 0;
+    if (resident_matrix(dtype, R)) return form == 3 ? 1 : 0;   // (in the 64 KB that the others pass through)
     const int steps = (form == 2 ? 12 : 18) / (R + (delta ? 1 : 0));
     return steps < 8 ? steps : 8;
 }

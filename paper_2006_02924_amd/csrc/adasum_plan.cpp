@@ -284,7 +284,9 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
     }
     for (int form = p.R <= 8 ? 2 : 3; form <= 3; ++form) {
         const int steps = resident_steps(dtype, p.R, delta, form), slots = resident_slots(dtype, p.R, form);
-        const Count full = count(step * steps);
+        // (what suits the pass is judged by the steps in registers where LDS has one on top)
+        const int judged = resident_matrix(dtype, p.R) ? resident_register_steps(dtype, p.R, delta, form) : steps;
+        const Count full = count(step * judged);
         if (full.most > resident_most(dtype, p.R, form)) continue;
         // Tables of tiny layers: hardly more units in form 1, which holds more workgroups (K = 2 bf16, 20000 layers of 100 to
         // 300 elements: 43 us, in form 2 95; 600 layers of 1 to 20000: 24 and 28).  (The kernels on the matrix cores hold
@@ -297,7 +299,7 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
         // As small units as the chip still holds all at once, so that more of it is at work (K = 2 bf16, one layer of 900 000
         // elements in 220 units instead of 25: 15.8 us for 20.3).
         if (layers < slots)
-            for (int64_t n = std::max<int64_t>(1, (N + step * (slots - layers) - 1) / (step * (slots - layers))); n < steps; ++n) {
+            for (int64_t n = std::max<int64_t>(1, (N + step * (slots - layers) - 1) / (step * (slots - layers))); n < judged; ++n) {
                 const Count c = count(step * n);
                 if (c.all > slots || c.most > resident_most(dtype, p.R, form)) continue;
                 take(form, step * n, c);
@@ -311,7 +313,7 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
         if (form == 3 && (p.R > 8 || dtype == ADASUM_BF16 || dtype == ADASUM_F16)) {
             int64_t alone = 0, units = 0;
             for (int l = 0; l < n_layers; ++l) {
-                const int64_t lo = layer_offsets[l], hi = layer_offsets[l + 1], cap = step * steps;
+                const int64_t lo = layer_offsets[l], hi = layer_offsets[l + 1], cap = step * judged;
                 const int64_t n = hi > lo ? (hi - 1) / cap - lo / cap + 1 : 0;
                 if (n <= slots / 2 || n > (dtype == ADASUM_F32 && p.R >= 12 ? slots * 9 / 10 : slots * 7 / 10)) continue;
                 ++alone;
@@ -319,7 +321,10 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
             }
             if (alone >= 5 && 2 * units > full.all) return p;
         }
-        take(form, step * steps, full);
+        // (the step in LDS comes after the others: nothing for units that the chip holds at once without it, nor for small layers)
+        const Count larger = judged == steps ? full : count(step * steps);
+        if (full.all > slots && larger.all * 10 <= full.all * 9) take(form, step * steps, larger);
+        else take(form, step * judged, full);
         return p;
     }
     return p;
