@@ -282,7 +282,8 @@ constexpr int kResidentRadix = 16;       // operands at most
 constexpr int kResidentWaitUs = 100;     // unless the caller says otherwise
 constexpr int kResidentCus = 256;        // compute units the figures are for; not used on fewer
 constexpr int kDirectUnits = 16;         // units of a layer up to which every workgroup reads all partial sums
-// More than 8 operands of a 16-bit type: the Gram matrix on the matrix cores, which takes few registers and 64 KB of LDS.
+// More than 8 operands of a 16-bit type: the Gram matrix on the matrix cores, which takes few registers and 64 KB of LDS (in form 3
+// a unit's last step then stays there).
 constexpr bool resident_matrix(int dtype, int R) { return R > 8 && (dtype == ADASUM_BF16 || dtype == ADASUM_F16); }
 constexpr int resident_per_cu(int dtype, int R, int form) { return form == 3 || resident_matrix(dtype, R) ? 2 : 3; }
 constexpr int resident_slots(int dtype, int R, int form) { return resident_per_cu(dtype, R, form) * kResidentCus; }

@@ -14,13 +14,13 @@
 // What bounds it.  Re-reading is what the three kernels lose: the Infinity Cache gives a compute die no more bandwidth
 // than memory does (7.1 TB/s, measured on 64 .. 256 MB re-read in a loop against 7.0 TB/s fresh), so bytes have to stay
 // in registers and LDS to be saved.  The chip holds some 110 MB there, about 15 us of memory traffic; a unit lives
-// through its loads (5 .. 12 us), the exchange (5 .. 10 us: two trips through memory under load, and waiting for the
-// layer's slowest unit), the scalars (1 us) and its stores.  So the pass is bound by how much is kept over how long:
+// through its loads (5 .. 16 us: a compute unit alone loads some 33 GB/s, 229 KB in 7 us, so memory is full only while nearly
+// all of them load), the exchange (4 .. 10 us: two trips through memory under load, and waiting for the layer's slowest
+// unit), the scalars (1 us) and its stores.  So the pass is bound by how much is kept over how long:
 // hence as much as the register file takes per unit, LDS filled straight from memory beside it, an exchange without
 // atomics, flags or fences (a fence of agent scope cost 1.4 x the whole pass), and launch order (order_units).
-// Measured against the three kernels, us per reduction: ResNet-50 sizes, K = 8 fp32 298 -> 214, K = 2 bf16 51 -> 36,
-// K = 6 binary16 152 -> 108, K = 16 bf16 with statistics 316 -> 272; 400 odd tensors, K = 12 bf16, 182 -> 100.  K = 8 fp32
-// reads 842 MB of 818 MB of gradients, K = 16 bf16 924 MB of 818: the exchange is the rest.
+// Measured against the three kernels, us per reduction: ResNet-50 sizes, K = 8 fp32 298 -> 190, K = 2 bf16 51 -> 36,
+// K = 6 binary16 152 -> 88, K = 16 bf16 with statistics 316 -> 214; 400 odd tensors, K = 12 bf16, 182 -> 84.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -604,7 +604,17 @@ resident_kernel(const ResidentArgs args) {
     Granule<TI, G> raw[SV][RL];
     // step SV + i, row r: this wave's 1 KB
     auto keep = [&](int i, int r) { return shKeep + ((i * RL + r) * NW + wave) * 1024; };
-    if (s.ng > 0) {
+    // (Where units have many steps, one that has a single step does not load the rest for nothing, and waits here, so that the
+    // steps of the others can still be told apart: K = 2 bf16, ResNet-50 sizes, 36.0 us instead of 37.7.  With 7 steps of 8
+    // rows it is K = 8 fp32 192 instead of 191.)
+    if (SV >= 10 && s.ng <= kThreads) {
+        if (s.ng > 0) {
+            const unsigned off = granule_at(0);
+#pragma unroll
+            for (int r = 0; r < RL; ++r) load_raw(raw[0][r], reinterpret_cast<const TI*>(reinterpret_cast<const char*>(row_at(r)) + off));
+            __builtin_amdgcn_s_waitcnt(0x0f70);   // (no vector loads in flight)
+        }
+    } else if (s.ng > 0) {
 #pragma unroll
         for (int i = 0; i < SV + (MFMA ? 0 : SL); ++i) {
             __builtin_amdgcn_sched_barrier(0);
