@@ -376,6 +376,7 @@ struct Plan {
     TileTable unit_tiles;                 // its units in element order
     ResidentUnit* d_units = nullptr;      // and in launch order
     bool prepared = false;                // borrowed memory whose resident section is set to zero already
+    bool resident_unfinished = false;     // its own memory may hold words under the tag of the next call (execute_plan)
     std::map<int, TileTable> comb_tables; // by capacity, built on first use
     std::vector<int> radices;
     std::vector<SmallLayer> small;        // layers reduced by the definition in fp64 (see kSmallLayer)
@@ -784,7 +785,7 @@ int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* o
     c.small = {p->d_small, tiles.layer_begin, p->n_small};
     c.wait_us = o.wait_us == 0 ? kResidentWaitUs : o.wait_us;
     if ((o.workspace != nullptr || p->borrowed) && !p->prepared) {
-        // memory that is not the plan's own holds anything, and after a failed launch the next tag's words may be there
+        // memory that is not the plan's own holds anything
         ADASUM_LAUNCH(launch_zero_words(c.state.epoch, static_cast<int64_t>((lay.total - lay.off_resident) / sizeof(int32_t)), stream));
     }
     char namebuf[48];
@@ -795,7 +796,13 @@ int run_resident(Plan* p, char* ws, const void* const* grads, int dtype, void* o
                    : dtype == ADASUM_BF16 ? (wide ? launch_resident_wide_bf16 : launch_resident_bf16)
                    : dtype == ADASUM_F16  ? (wide ? launch_resident_wide_f16 : launch_resident_f16)
                                           : launch_resident_f64;
-    ADASUM_TIMED(namebuf, bytes, stream, launch(c, stream));
+    // (the last launch of a call moves the tag on: where it fails, words that an earlier one of the call sent carry the next call's)
+    auto enqueue = [&]() {
+        const int e = launch(c, stream);
+        if (e != 0 && o.workspace == nullptr && !p->borrowed) p->resident_unfinished = true;
+        return e;
+    };
+    ADASUM_TIMED(namebuf, bytes, stream, enqueue());
     if (o.layer_stats != nullptr)
         ADASUM_LAUNCH(launch_resident_stats(c.normparts, tiles, c.gram, c.R, K, L, o.layer_stats, stream));
     return ADASUM_OK;
@@ -1260,6 +1267,17 @@ int execute_plan(Plan* p, const void* const* grads, int dtype, void* out, const 
     bool eager = false;
     rc = begin_on_stream(p, stream, &eager);
     if (rc != ADASUM_OK) return rc;
+    if (p->resident_unfinished && o.workspace == nullptr) {
+        // a call failed between its launches: the section starts anew.  (A call that is being captured does so in every replay, and
+        // the next eager one too.)
+        const int e = launch_zero_words(reinterpret_cast<int32_t*>(ws + p->lay.off_resident),
+                                        static_cast<int64_t>((p->lay.total - p->lay.off_resident) / sizeof(int32_t)), stream);
+        if (e != 0) {
+            g_last_hip_error = e;
+            return end_on_stream(p, stream, eager, ADASUM_ERR_HIP);
+        }
+        if (eager) p->resident_unfinished = false;
+    }
     if (o.use_graph && !g_profile) rc = launch_as_graph(p, ws, grads, dtype, out, o, stream);
     else if (p->K == 1) rc = run_copy(p, ws, grads, dtype, out, o, stream);
     else if (o.order == ADASUM_ORDER_LINEAR) rc = run_linear(p, ws, grads, dtype, out, o, stream);
