@@ -934,6 +934,14 @@ resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict
                                             shW, shQ, shNorm, shTodo);
 }
 
+// One launch, and what became of this one: the thread's last error may be an older one, of a call that is not ours, and the second
+// launch of a pass must not fall out for that once the first is on its way.
+template <typename... P>
+int enqueue(void (*kernel)(P...), int blocks, hipStream_t stream, P... args) {
+    void* at[] = {const_cast<void*>(static_cast<const void*>(&args))...};
+    return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), at, 0, stream));
+}
+
 template <typename TI, typename TO, int R, bool DELTA, int SV, int SL, int WPS>
 int launch_s(const ResidentCall& c, hipStream_t stream) {
     const bool same = kRedoInLaunch<SV, SL> && c.n_units <= WPS * kResidentCus;
@@ -953,14 +961,10 @@ int launch_s(const ResidentCall& c, hipStream_t stream) {
     args.wait_us = c.wait_us;
     args.order = c.order;
     args.leaves = c.leaves;
-    hipLaunchKernelGGL((resident_kernel<TI, TO, R, DELTA, SV, SL, WPS>), dim3(static_cast<unsigned>(c.n_units + (same ? redo + small : 0))),
-                       dim3(kThreads), 0, stream, args);
-    const int e = static_cast<int>(hipGetLastError());
+    const int e = enqueue(resident_kernel<TI, TO, R, DELTA, SV, SL, WPS>, c.n_units + (same ? redo + small : 0), stream, args);
     if (same || e != 0) return e;
-    hipLaunchKernelGGL((resident_redo_kernel<TI, TO, R, DELTA>), dim3(static_cast<unsigned>(redo + small)),
-                       dim3(kThreads), 0, stream, c.ops, static_cast<TO*>(c.out), c.units, c.n_units, c.state,
-                       c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves, redo, c.small);
-    return static_cast<int>(hipGetLastError());
+    return enqueue(resident_redo_kernel<TI, TO, R, DELTA>, redo + small, stream, c.ops, static_cast<TO*>(c.out), c.units, c.n_units, c.state,
+                   c.gram, c.normparts, static_cast<const TI*>(c.start), c.order, c.leaves, redo, c.small);
 }
 
 template <typename TI, typename TO, int R, bool DELTA>
