@@ -634,10 +634,11 @@ resident_kernel(const ResidentArgs args) {
             // either operand.  What is kept has a row's granules along the lanes, so a step goes through LDS (a wave's own
             // 16 KB, no barrier): granule c of row r lies at place c ^ r, conflict-free both ways.  Four accumulators
             // where the vector units would need R (R + 1) / 2: 136 of them took three sweeps over what is kept (K = 16 bf16
-            // on a sixteenth of ResNet-50: 82 us with spills, 30 this way).  The products are exact; four instructions in a row accumulate 128 of them, the rest are ordinary fp32 additions.
+            // on a sixteenth of ResNet-50: 82 us with spills, 30 this way).  The products are exact; four instructions in a row accumulate 128 of them in fp32, and those
+            // sums are added up in fp64, so that a unit of more steps is no less exact.
             unsigned char* stage = shStage + wave * (16 * 1024);
             const int m = lane & 15, kg = lane >> 4;
-            float sum[4] = {0.f, 0.f, 0.f, 0.f};
+            double sum[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int r = R; r < 16; ++r) *reinterpret_cast<u32x4*>(stage + r * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
             auto multiply_staged = [&]() __attribute__((always_inline)) {
@@ -651,7 +652,7 @@ resident_kernel(const ResidentArgs args) {
                         acc = mfma_square<TI>(x, acc);
                     }
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) sum[v] += acc[v];
+                    for (int v = 0; v < 4; ++v) sum[v] += static_cast<double>(acc[v]);
                 }
                 __builtin_amdgcn_wave_barrier();
             };
@@ -691,7 +692,7 @@ resident_kernel(const ResidentArgs args) {
             }
             // (accumulator v of a lane: row 4 (lane / 16) + v, column lane % 16)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) shP[wave * 256 + (4 * kg + v) * 16 + m] = static_cast<double>(sum[v]);
+            for (int v = 0; v < 4; ++v) shP[wave * 256 + (4 * kg + v) * 16 + m] = sum[v];
         } else {
 #pragma unroll
         for (int sweep = 0; sweep < SWEEPS; ++sweep) {
