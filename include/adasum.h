@@ -20,7 +20,9 @@
  *     a piece of a layer stays in a workgroup's registers and LDS while the layer's
  *     scalars are worked out, so every input is read once.  Workgroups of a layer wait
  *     for each other, at most 100 us; what that leaves undone (when other kernels hold
- *     much of the chip) a second launch does from memory, with the same result.  Programs
+ *     much of the chip) is done from memory, with the same result, by a second launch or,
+ *     for reductions that the chip holds all at once in small pieces, by the last workgroups
+ *     of the launch, which wait until the others have ended.  Programs
  *     that reduce large models beside other kernels: see separate_passes;
  *   - layers of at most 16 elements are reduced by the definition itself, pair by
  *     pair in fp64 over all K workers with nothing stored in between: vectors that
@@ -166,8 +168,9 @@ typedef struct adasum_options {
                                   that ends before this field reads as 0. */
     int32_t  reserved1;        /* must be 0 */
     int32_t  resident_wait_us; /* microseconds that the workgroups of a layer wait for each other in the resident pass before
-                                  they leave their pieces to its second launch: 0 = 100; 1 .. 10000; -1 = none at all, for
-                                  programs whose other kernels always hold much of the chip, and for tests of that launch.
+                                  they leave their pieces to those that do them from memory (a second launch, or the last
+                                  workgroups of the same one): 0 = 100; 1 .. 10000; -1 = none at all, for
+                                  programs whose other kernels always hold much of the chip, and for tests of that part.
                                   The result is the same bit for bit.  A struct_bytes that ends before this field reads
                                   as 0. */
     int32_t  reserved2;        /* must be 0 */
@@ -269,7 +272,8 @@ ADASUM_API int adasum_plan_destroy(adasum_plan* plan);
  * single pass keeps no intermediate nodes, for BERT-Large (335 M elements) at K <= 64 with radix 64.
  * Every call on one GPU uses the same array and finds the previous call's contents there:
  * each call rebuilds all it reads (nothing needs to start at zero), and two calls that
- * overlap in time on one GPU -- on different streams without an ordering between them -- race.
+ * overlap in time on one GPU -- on different streams without an ordering between them -- race:
+ * their results are not defined, NaN among them, and they may take some seconds, but end.
  * Calls on one stream, or ordered by events, are safe.
  */
 #define ADASUM_NOALLOC_SCRATCH_BYTES (64u << 20)

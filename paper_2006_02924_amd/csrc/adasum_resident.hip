@@ -27,6 +27,7 @@
 
 #include "adasum_host.h"
 #include "adasum_device.h"
+#include "adasum_outcome.h"
 
 namespace adasum {
 namespace {
@@ -105,10 +106,10 @@ __device__ __forceinline__ bool tagged(const u32x4& w, unsigned tag) { return w.
 __device__ __forceinline__ double value(const u32x4& w) {
     return __longlong_as_double(static_cast<long long>(w.z) << 32 | static_cast<long long>(w.x));
 }
-// Looks at N values side by side, and at all of them again until they are there or the time is up (false).  (One after another,
+// Looks at N values side by side, and at all of them again until they are there or `more` says no (false).  (One after another,
 // each that was late would take a trip through memory of its own.)
-template <int N>
-__device__ __forceinline__ bool await(buffer_t b, const int (&offset)[N], u32x4 (&w)[N], unsigned tag, long long deadline) {
+template <int N, typename More>
+__device__ __forceinline__ bool await(buffer_t b, const int (&offset)[N], u32x4 (&w)[N], unsigned tag, More&& more) {
     for (;;) {
         bool there = true;
 #pragma unroll
@@ -116,7 +117,7 @@ __device__ __forceinline__ bool await(buffer_t b, const int (&offset)[N], u32x4 
 #pragma unroll
         for (int k = 0; k < N; ++k) there = there && tagged(w[k], tag);
         if (there) return true;
-        if (static_cast<long long>(wall_clock64()) > deadline) return false;
+        if (!more()) return false;
         __builtin_amdgcn_s_sleep(2);
         asm volatile("" ::: "memory");   // (the next look is another)
     }
@@ -125,10 +126,6 @@ __device__ __forceinline__ bool await(buffer_t b, const int (&offset)[N], u32x4 
 // count themselves while it runs.
 constexpr int kTagMask = 0xffffff, kArrival = kTagMask + 1;
 __device__ __forceinline__ unsigned tag_of(int epoch) { return static_cast<unsigned>(epoch & kTagMask) + 1u; }
-// What became of a unit, with the call it is of.
-constexpr int kGaveUp = 1, kRedone = 2, kDone = 4;
-__device__ __forceinline__ int outcome_word(unsigned tag, int what) { return static_cast<int>((tag - 1u) << 3) | what; }
-__device__ __forceinline__ bool of_call(int word, unsigned tag) { return (word & 7) != 0 && word >> 3 == static_cast<int>(tag - 1u); }
 
 // Where entry e of the layer's unit number u lies (of W units, NP entries), in bytes: runs of kRun entries of every unit follow each
 // other, so that the lanes that sum a run over the units read whole memory sectors.  (With the NP entries of a unit in one
@@ -160,7 +157,9 @@ constexpr int redo_per_cu(int R) { return R > 8 ? 2 : 4; }
 // form 1, whose units are small
 template <int SV, int SL> constexpr bool kRedoInLaunch = SV == 1 && SL == 0;
 constexpr int kTicksPerUs = 100;         // of wall_clock64
-constexpr long long kNoLimit = 0x7fffffffffffffffLL;
+// Looks that the last workgroups of a launch take at something that is on its way, more than a microsecond each.  Nothing that runs as
+// it should comes near it.  (Counted in looks, not in time: while the chip is another process's they do not run out.)
+constexpr int kMostLooks = 1 << 21;
 
 // 16 bytes per lane straight from memory into LDS (lane l's at dst + 16 l; base: the same for all lanes): no registers are
 // held meanwhile.  A buffer load: after a global_load_lds, which counts as a flat access, the compiler waits for every
@@ -332,13 +331,15 @@ __device__ __forceinline__ void small_layers(const Operands& ops, TO* out, Small
 // Units that gave up waiting, from memory, with the same arithmetic in the same order; and the tag moves on.  A workgroup
 // (`first` of `step`) looks at every step-th unit: a layer's units follow each other and tend to give up together.
 // SAME_LAUNCH: by the last workgroups of the launch itself, for reductions that the chip holds all at once in small units: a
-// second launch costs 4 us of 19 there.  They wait for every unit's outcome, without a limit: units are dispatched before them
-// and end within their own limit whatever these do.
+// second launch costs 4 us of 19 there.  They wait for every unit's outcome: units are dispatched before them and end within their
+// own limit whatever these do.  Where that does not hold -- calls that overlap in one memory, against the rule, clear each other's
+// words -- they still end after kMostLooks, and units whose outcome or whose layer's sums are not there are made NaN.
 template <typename TI, typename TO, int R, bool DELTA, bool SAME_LAUNCH>
 __device__ __forceinline__ void redo_units(const Operands& ops, TO* out, const ResidentUnit* __restrict__ units, int n_units, int first,
                                            int step, const ResidentState& st, double* __restrict__ gram,
                                            double* __restrict__ normparts, const TI* start, int order, int leaves, double* shR,
-                                           double* shG, double* shW, double* shQ, double* shNorm, unsigned long long* shTodo) {
+                                           double* shG, double* shW, double* shQ, double* shNorm, unsigned long long* shTodo,
+                                           int* shLate) {
     constexpr int G = Traits<TI>::VEC;
     constexpr int NP = R * (R + 1) / 2;
     constexpr int NW = kThreads / 64;
@@ -350,26 +351,31 @@ __device__ __forceinline__ void redo_units(const Operands& ops, TO* out, const R
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned tag = SAME_LAUNCH ? tag_of(__hip_atomic_load(st.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0u;
+    int looks = kMostLooks;
     auto outcome = [&](int i) __attribute__((always_inline)) {
         if constexpr (!SAME_LAUNCH) return st.outcome[i] & 7;
-        for (;;) {
-            const int word = __hip_atomic_load(st.outcome + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (of_call(word, tag)) return word & 7;
-            __builtin_amdgcn_s_sleep(8);
-        }
+        return await_outcome([&]() __attribute__((always_inline)) { return __hip_atomic_load(st.outcome + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                             tag,
+                             [&]() __attribute__((always_inline)) {
+                                 __builtin_amdgcn_s_sleep(8);
+                                 return --looks > 0;
+                             });
     };
+    if (SAME_LAUNCH && tid == 0) *shLate = 0;   // (long before anybody has looked in vain for the last time)
     int layer = -1;
     for (int i0 = first; i0 < n_units; i0 += step * kThreads) {
         const int mine = i0 + tid * step;
-        const bool redo = mine < n_units && outcome(mine) == kGaveUp;
-        const unsigned long long some = __ballot(redo);
+        const int what = mine < n_units ? outcome(mine) : static_cast<int>(kDone);
+        const unsigned long long some = __ballot(SAME_LAUNCH ? what != kDone : what == kGaveUp);
         if (lane == 0) shTodo[wave] = some;
+        if (SAME_LAUNCH && what == kOverdue) *shLate = 1;
         __syncthreads();
         if (tid == 0 && i0 + step * kThreads >= n_units) {
             if constexpr (!SAME_LAUNCH) {
                 if (first == 0) *st.epoch = static_cast<int>(tag_of(*st.epoch) & kTagMask);
-            } else if (__hip_atomic_fetch_add(st.epoch, kArrival, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kArrival == step - 1) {
-                // (the last of them to have seen its units' outcomes: all that read the tag have done so)
+            } else if (*shLate || __hip_atomic_fetch_add(st.epoch, kArrival, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kArrival == step - 1) {
+                // (the last of them to have seen its units' outcomes: all that read the tag have done so.  Late ones leave no arrivals
+                // for the next call.)
                 __hip_atomic_store(st.epoch, static_cast<int>(tag & kTagMask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
@@ -383,7 +389,7 @@ __device__ __forceinline__ void redo_units(const Operands& ops, TO* out, const R
             tile.layer = t.layer;
             const Split s = split_tile<G>(tile);
             const int W = t.layer_end - t.layer_first;
-            if (t.layer != layer) {   // (else its weights are there from the unit before)
+            if (t.layer != layer && !(SAME_LAUNCH && *shLate)) {   // (else its weights are there from the unit before)
                 layer = t.layer;
                 const buffer_t partials = buffer_of(st.partials + static_cast<long long>(t.layer_first) * (NP * 2), W * NP * 16);
                 // the sum of entry e over the units u0, u0 + step, ... of the layer (which have all been sent, or will be)
@@ -396,7 +402,7 @@ __device__ __forceinline__ void redo_units(const Operands& ops, TO* out, const R
 #pragma unroll
                         for (int k = 0; k < kAhead; ++k) offset[k] = partial_at<NP>(u0 + k * step < W ? u0 + k * step : W - 1, e, W);
                         if constexpr (SAME_LAUNCH) {
-                            await(partials, offset, x, tag, kNoLimit);
+                            if (!await(partials, offset, x, tag, [&]() __attribute__((always_inline)) { return --looks > 0; })) *shLate = 1;
                         } else {
 #pragma unroll
                             for (int k = 0; k < kAhead; ++k) x[k] = __builtin_amdgcn_raw_buffer_load_b128(partials, offset[k], 0, 0);
@@ -441,6 +447,13 @@ __device__ __forceinline__ void redo_units(const Operands& ops, TO* out, const R
                 if (gram != nullptr && t.unit == t.layer_first)
                     for (int i = tid; i < R * R; i += kThreads) gram[static_cast<long long>(t.layer) * (R * R) + i] = shG[i];
                 __syncthreads();
+            }
+            if (SAME_LAUNCH && *shLate) {
+                const double nan = __builtin_nan("");
+                for (int j = tid; j < t.len; j += kThreads) store_elem(out + t.start + j, static_cast<typename Traits<TO>::acc_t>(nan));
+                if (tid == 0 && normparts != nullptr) normparts[t.unit] = nan;
+                if (tid == 0 && gram != nullptr) gram[static_cast<long long>(t.layer) * (R * R)] = nan;
+                continue;
             }
             acc_t w[R];
 #pragma unroll
@@ -554,7 +567,7 @@ resident_kernel(const ResidentArgs args) {
         if (at >= n_units) {
             redo_units<TI, TO, R, DELTA, true>(args.ops, static_cast<TO*>(args.out), args.units, n_units, at - n_units, n_redo, args.state,
                                                args.gram, args.normparts, static_cast<const TI*>(args.start), args.order, args.leaves, shR,
-                                               shG, shW, shQ, shNorm, shTodo);
+                                               shG, shW, shQ, shNorm, shTodo, &shSkip);
             return;
         }
     }
@@ -792,6 +805,7 @@ resident_kernel(const ResidentArgs args) {
     const int order = late->order, leaves = late->leaves, wait_us = late->wait_us;
     if (W > 1) {
         const long long deadline = static_cast<long long>(wall_clock64()) + static_cast<long long>(wait_us) * kTicksPerUs;
+        auto in_time = [&]() __attribute__((always_inline)) { return static_cast<long long>(wall_clock64()) <= deadline; };
         bool ok = wait_us >= 0;
         // the sum of entry e over the units u0, u0 + step, ... of the layer, kAhead of them looked at side by side
         auto sum_ahead = [&](auto ahead, int e, int u0, int step) __attribute__((always_inline)) {
@@ -802,7 +816,7 @@ resident_kernel(const ResidentArgs args) {
                 u32x4 x[kAhead];
 #pragma unroll
                 for (int k = 0; k < kAhead; ++k) offset[k] = partial_at<NP>(u0 + step * k < W ? u0 + step * k : W - 1, e, W);
-                ok = await(partials, offset, x, tag, deadline) && ok;
+                ok = await(partials, offset, x, tag, in_time) && ok;
 #pragma unroll
                 for (int k = 0; k < kAhead; ++k)
                     if (u0 + step * k < W) v += value(x[k]);
@@ -844,8 +858,8 @@ resident_kernel(const ResidentArgs args) {
             if (tid < NP) {
                 const int offset[1] = {tid * 16};
                 u32x4 x[1];
-                if (lane == 0) ok = await(sums, offset, x, tag, deadline) && ok;   // (one lane's looks are enough until then)
-                ok = await(sums, offset, x, tag, deadline) && ok;
+                if (lane == 0) ok = await(sums, offset, x, tag, in_time) && ok;   // (one lane's looks are enough until then)
+                ok = await(sums, offset, x, tag, in_time) && ok;
                 int a, b;
                 entry_to_ij<R, true>(tid, a, b);
                 shG[a * R + b] = shG[b * R + a] = value(x[0]);
@@ -932,7 +946,7 @@ resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict
         small_layers<TI, TO, R, DELTA>(ops, out, small, at - n_redo, gram, normparts, start, order, leaves, shSmall);
     else
         redo_units<TI, TO, R, DELTA, false>(ops, out, units, n_units, at, n_redo, st, gram, normparts, start, order, leaves, shR, shG,
-                                            shW, shQ, shNorm, shTodo);
+                                            shW, shQ, shNorm, shTodo, nullptr);
 }
 
 // One launch, and what became of this one: the thread's last error may be an older one, of a call that is not ours, and the second
