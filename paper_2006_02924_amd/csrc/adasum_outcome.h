@@ -27,6 +27,15 @@ ADASUM_ANYWHERE int await_outcome(Load&& load, unsigned tag, More&& more) {
     }
 }
 
+// What `load` says, for every wave of a workgroup alike: none goes on, and writes to what it reads, before all have looked.  (A branch
+// with barriers in it hangs on the answer: a wave that saw a later one would leave the others waiting there.)
+template <typename Load, typename Barrier>
+ADASUM_ANYWHERE bool same_answer(Load&& load, Barrier&& barrier) {
+    const bool answer = load();
+    barrier();
+    return answer;
+}
+
 }  // namespace adasum
 
 #undef ADASUM_ANYWHERE

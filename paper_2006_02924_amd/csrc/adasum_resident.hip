@@ -389,7 +389,11 @@ __device__ __forceinline__ void redo_units(const Operands& ops, TO* out, const R
             tile.layer = t.layer;
             const Split s = split_tile<G>(tile);
             const int W = t.layer_end - t.layer_first;
-            if (t.layer != layer && !(SAME_LAUNCH && *shLate)) {   // (else its weights are there from the unit before)
+            bool late = false;
+            if constexpr (SAME_LAUNCH)
+                late = same_answer([&]() __attribute__((always_inline)) { return *shLate != 0; },
+                                   []() __attribute__((always_inline)) { __syncthreads(); });
+            if (t.layer != layer && !late) {   // (else its weights are there from the unit before)
                 layer = t.layer;
                 const buffer_t partials = buffer_of(st.partials + static_cast<long long>(t.layer_first) * (NP * 2), W * NP * 16);
                 // the sum of entry e over the units u0, u0 + step, ... of the layer (which have all been sent, or will be)
@@ -447,8 +451,9 @@ __device__ __forceinline__ void redo_units(const Operands& ops, TO* out, const R
                 if (gram != nullptr && t.unit == t.layer_first)
                     for (int i = tid; i < R * R; i += kThreads) gram[static_cast<long long>(t.layer) * (R * R) + i] = shG[i];
                 __syncthreads();
+                if constexpr (SAME_LAUNCH) late = *shLate != 0;   // (no wave writes to it before all are at the next unit)
             }
-            if (SAME_LAUNCH && *shLate) {
+            if (late) {
                 const double nan = __builtin_nan("");
                 for (int j = tid; j < t.len; j += kThreads) store_elem(out + t.start + j, static_cast<typename Traits<TO>::acc_t>(nan));
                 if (tid == 0 && normparts != nullptr) normparts[t.unit] = nan;

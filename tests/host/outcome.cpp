@@ -1,6 +1,7 @@
 // The wait for a unit's outcome in the resident pass (adasum_outcome.h): it comes back with what the unit wrote in this call, and it
-// ends also where no such word ever comes.  Built and run by tests/test_outcome_cpu.py.
+// ends also where no such word ever comes; and waves that have to agree on what they see.  Built and run by tests/test_outcome_cpu.py.
 #include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <thread>
@@ -44,6 +45,23 @@ int main() {
     int looks = 100000;
     std::atomic<int> word{0};
     CHECK(await_outcome([&]() { word = outcome_word(3, kDone); word = 0; return word.load(); }, 3, [&]() { return --looks > 0; }) == kOverdue);
+    // a wave that looks late, beside one that changes what is looked at as soon as it may
+    for (int rep = 0; rep < 5; ++rep) {
+        std::atomic<int> late{0}, arrived{0};
+        auto barrier = [&]() {
+            ++arrived;
+            while (arrived < 2) std::this_thread::yield();
+        };
+        bool first = true, second = true;
+        std::thread quick([&]() {
+            first = same_answer([&]() { return late != 0; }, barrier);
+            late = 1;
+        });
+        std::this_thread::sleep_for(std::chrono::milliseconds(50));
+        second = same_answer([&]() { return late != 0; }, barrier);
+        quick.join();
+        CHECK(!first && !second);
+    }
     std::printf("outcomes ok\n");
     return 0;
 }

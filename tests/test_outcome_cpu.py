@@ -1,4 +1,4 @@
-"""Waits inside a launch end, whatever becomes of what is waited for (tests/host/outcome.cpp)."""
+"""Waits inside a launch end, whatever becomes of what is waited for, and its waves agree on it (tests/host/outcome.cpp)."""
 import os
 import shutil
 import subprocess
