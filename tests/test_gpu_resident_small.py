@@ -1,5 +1,7 @@
 """Layers of at most 16 elements in a reduction that is taken as a resident pass: by the definition, with the bits that the passes
-over memory give them, wherever a unit's boundary cuts them."""
+over memory give them, wherever a unit's boundary cuts them; and the larger layers beside them, which they must leave alone."""
+import math
+
 import pytest
 import torch
 
@@ -31,6 +33,20 @@ def table(K, dtype, big, **kw):
     return full, steps
 
 
+def assert_larger_layers_close(got, want, offs, K, dtype):
+    """Two ways of summing: runs of up to 128 products in the lanes' type at each of the tree's levels and a chain of K in the combine,
+    and a rounding of the result on either side.  Element by element too: a single wrong one hardly shows in a layer's norm."""
+    lane = 2.0 ** (-53 if dtype == torch.float64 else -24)
+    sums = (128 * math.ceil(math.log2(K)) + K) * lane if dtype != torch.float64 else 1e4 * lane    # (fp64: all sums, 4e5 terms in some 1e3 in a row)
+    ulp = {torch.bfloat16: 2.0 ** -7, torch.float16: 2.0 ** -10}.get(dtype, 0.0)
+    for l, (a, b) in enumerate(zip(offs, offs[1:])):
+        if b - a > 16:
+            x, y = got[a:b].double(), want[a:b].double()
+            assert float((x - y).norm()) <= (sums + ulp / 2) * float(y.norm()), (l, b - a)
+            atol = 6 * K * sums * float(y.norm()) / math.sqrt(b - a)      # (K weights off by `sums`, elements of six standard deviations)
+            assert bool(((x - y).abs() <= ulp * y.abs() + atol).all()), (l, b - a)
+
+
 CASES = [(2, torch.bfloat16), (3, torch.float16), (5, torch.float32), (8, torch.float32), (8, torch.float64), (7, torch.bfloat16),
          (9, torch.bfloat16), (12, torch.float32), (16, torch.bfloat16)]
 
@@ -53,6 +69,7 @@ def test_same_bits_as_the_passes_over_memory(K, dtype, big, order):
     B.adasum_reduce(w.grads, w.layer_offsets, again, noalloc=True, **kw)
     torch.cuda.synchronize()
     assert torch.equal(got, plain) and torch.equal(got, again)
+    assert_larger_layers_close(got, want, w.layer_offsets, K, dtype)
     for l, n in enumerate(sizes):
         if n <= 16:
             a, b = w.layer_offsets[l], w.layer_offsets[l + 1]
@@ -68,9 +85,12 @@ def test_after_optimizer_form_in_place(K, dtype, big):
     w = W.after_local_step(sizes, K, dtype=dtype, device=DEV, seed=3, step=0.25)
     start = w.meta["start"]
     want = B.adasum_reduce(w.grads, w.layer_offsets, delta_start=start, separate_passes=True)
+    beside = B.adasum_reduce(w.grads, w.layer_offsets, delta_start=start)
     got = start.clone()
     B.adasum_reduce(w.grads, w.layer_offsets, got, delta_start=got)
     torch.cuda.synchronize()
+    assert torch.equal(got, beside)
+    assert_larger_layers_close(got, want, w.layer_offsets, K, dtype)
     for l, n in enumerate(sizes):
         if n <= 16:
             a, b = w.layer_offsets[l], w.layer_offsets[l + 1]
