@@ -162,9 +162,10 @@ typedef struct adasum_options {
                                   wrote), so that only the first pass reads its operands twice;
                                   1: every pass makes a reduce pass of its own over its operands, and there is
                                   no resident pass (for measurements, and for programs whose other kernels hold
-                                  much of the chip meanwhile: ResNet-50 sizes of 8 or 16 workers reduced beside
-                                  a stream of small matrix products take 0.6 times as long this way, alone 1.1
-                                  to 1.4 times; the result is the same up to rounding).  A struct_bytes
+                                  much of the chip meanwhile: ResNet-50 sizes of 8 workers in fp32 reduced beside
+                                  a stream of small matrix products take 0.7 times as long this way, of 16 in bf16
+                                  beside a stream of copies 0.6 times; alone they take 1.4 to 1.6 times as long; the
+                                  result is the same up to rounding).  A struct_bytes
                                   that ends before this field reads as 0. */
     int32_t  reserved1;        /* must be 0 */
     int32_t  resident_wait_us; /* microseconds that the workgroups of a layer wait for each other in the resident pass before

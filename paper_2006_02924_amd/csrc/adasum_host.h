@@ -275,7 +275,7 @@ struct TileSet {
 // and for tables of tiny layers.  Form 2: three workgroups per compute unit; form 3: two, which keep more.  Smaller units
 // overlap better (K = 2 bf16, ResNet-50 sizes: 40 us in form 2, 62 in form 3; K = 6 binary16: 115 and 121), but a layer
 // that takes most of the chip stalls it (K = 8 fp32, whose largest layers have 75 of 84 MB: 260 us in form 2, 217 in
-// form 3): form 2 while the largest layer takes at most half of its workgroups.  More than 8 operands have forms 1 and 3
+// form 3; all of these with the exchange as it was at first): form 2 while the largest layer takes at most half of its workgroups.  More than 8 operands have forms 1 and 3
 // only (one step of 16 operands is 64 KB), and an even number: an odd one repeats an operand with weight 0.
 // plan_resident has the rules.
 constexpr int kResidentRadix = 16;       // operands at most
@@ -341,7 +341,9 @@ void order_units(const std::vector<adasum_tile>& tiles, const std::vector<int32_
 // What the workgroups of a resident pass share.  All zero before the first pass; every call has a tag of its own.
 struct ResidentState {
     int32_t* epoch;                 // calls so far
-    int32_t* outcome;               // [unit in launch order]: what became of it and in which call (outcome_word)
+    // [unit in launch order]: what became of it.  Form 1 says in which call too (outcome_word); in the others the word is 0, kGaveUp
+    // until the second launch of that call, or kRedone, for good.
+    int32_t* outcome;
     unsigned long long* partials;   // [unit][entry][2]
     unsigned long long* sums;       // [layer][entry][2]
 };

@@ -284,7 +284,11 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
     }
     for (int form = p.R <= 8 ? 2 : 3; form <= 3; ++form) {
         const int steps = resident_steps(dtype, p.R, delta, form), slots = resident_slots(dtype, p.R, form);
-        // (what suits the pass is judged by the steps in registers where LDS has one on top)
+        // What suits the pass is judged by the steps in registers where LDS has one on top: the line is from before there was that one, and
+        // refuses tables that fit in all steps.  What that gives away, us for this pass and for the others: BERT-Large / 8 (largest
+        // layer 636 units, 477 in all steps), K = 16 bf16 320 and 472 in the tree order (left to right 474 and 469: nothing); 300
+        // layers of 40000 elements and ten of 560 units (420 to 448 in all steps), K = 9 317 and 431, K = 12 378 and 522, K = 16
+        // 395 and 531.
         const int judged = resident_matrix(dtype, p.R) ? resident_register_steps(dtype, p.R, delta, form) : steps;
         const Count full = count(step * judged);
         if (full.most > resident_most(dtype, p.R, form)) continue;
@@ -306,10 +310,15 @@ ResidentPlan plan_resident(int K, const std::vector<int>& radices, int dtype, bo
                 return p;
             }
         // Layers of a little more than half the chip run alone on it, and the rest of it waits with them.  Where such layers
-        // hold most of a table, the other passes are faster: 20 layers of 300 units each, us for this pass and for those,
-        // K = 16 fp32 511 and 416, K = 16 bf16 452 and 419, K = 2 bf16 507 and 460 (fp32 and fp64 of at most 8 rows stay
-        // ahead: K = 8 fp32 431 and 472); of 370 units, K = 16 fp32 583 and 500, K = 16 bf16 515 and 513.  Two layers of 300:
-        // 58 and 81, 53 and 71, 57 and 55.
+        // hold most of a table, the other passes were faster when this line was drawn (K = 16 fp32 511 and 416, K = 16 bf16 452 and
+        // 419, K = 2 bf16 507 and 460; fp32 and fp64 of at most 8 rows stayed ahead: K = 8 fp32 431 and 472).  With the present exchange
+        // that still holds for fp32 of 12 and more rows and, by 1 %, for the lower end of some others (K = 4 and 8 bf16); for the rest it
+        // gives away up to a third.  20 layers of 270, 300, 340 and 370 units each, us for this pass and for those:
+        // K = 16 fp32 413 449 506 538 and 388 422 463 521; K = 12 fp32 322 357 396 417 and 312 349 379 422; K = 10 fp32
+        // 305 345 384 407 and 357 394 446 469; K = 16 bf16 274 305 323 453 and 400 434 488 528; K = 12 bf16 287 308 450 472 and
+        // 420 452 510 546; K = 8 bf16 454 476 504 555 and 450 485 553 608; K = 4 bf16 465 486 507 532 and 461 513 568 613;
+        // K = 2 bf16 308 468 495 539 and 420 470 531 579.  Five layers of 300: K = 16 fp32 117 and 142, K = 16 bf16 86 and
+        // 155, K = 2 bf16 126 and 125; two: 52 and 102, 37 and 97, 56 and 58.
         if (form == 3 && (p.R > 8 || dtype == ADASUM_BF16 || dtype == ADASUM_F16)) {
             int64_t alone = 0, units = 0;
             for (int l = 0; l < n_layers; ++l) {

@@ -6,9 +6,9 @@
 //
 // Its layers of some waves of units need the chip for themselves: beside other kernels units wait longer for each other,
 // and some give up (see redo_units).  Measured beside 8192^3 bf16 matrix products, copies of 1 GB and small
-// products (512 x 4096 x 4096) on another stream, us per reduction, three kernels in brackets: ResNet-50 sizes, K = 2 bf16 856
-// (1593), 68 (97), 56 (66); K = 8 fp32 1348 (1847), 368 (520), 503 (331); K = 16 bf16 1805 (1851), 1218 (529), 588 (366); a
-// quarter of them, K = 8 bf16, 1555 (1618), 96 (126), 72 (94).  So programs that reduce large models of 8 and more workers
+// products (512 x 4096 x 4096) on another stream, us per reduction, three kernels in brackets: ResNet-50 sizes, K = 2 bf16 1200
+// (1580), 67 (95), 55 (66); K = 8 fp32 1009 (2436), 333 (500), 441 (320); K = 16 bf16 1126 (2221), 890 (507), 337 (352); a
+// quarter of them, K = 8 bf16, 842 (3002), 74 (128), 56 (96).  So programs that reduce large models of 8 and more workers
 // beside small or streaming kernels are better off with separate_passes.
 //
 // What bounds it.  Re-reading is what the three kernels lose: the Infinity Cache gives a compute die no more bandwidth
@@ -20,7 +20,7 @@
 // hence as much as the register file takes per unit, LDS filled straight from memory beside it, an exchange without
 // atomics, flags or fences (a fence of agent scope cost 1.4 x the whole pass), and launch order (order_units).
 // Measured against the three kernels, us per reduction: ResNet-50 sizes, K = 8 fp32 298 -> 190, K = 2 bf16 51 -> 36,
-// K = 6 binary16 152 -> 88, K = 16 bf16 with statistics 316 -> 214; 400 odd tensors, K = 12 bf16, 182 -> 84.
+// K = 6 binary16 152 -> 88, K = 16 bf16 with statistics 316 -> 215; 400 odd tensors, K = 12 bf16, 182 -> 83.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -140,7 +140,9 @@ __device__ __forceinline__ int partial_at(int u, int e, int W) {
 // A workgroup sums a run: kRun lanes side by side per unit, kRunUnits units at a time.
 constexpr int kRunUnits = kThreads / kRun;
 // Units of a layer up to which every workgroup reads all partial sums itself.  (K = 2 bf16, ResNet-50 sizes: 37.4 us with 4,
-// 38.4 with 16, 40.7 with 170; K = 8 fp32 and K = 16 bf16 take the same with 4 to 32, 1.5 % longer with 2.)
+// 38.4 with 16, 40.7 with 170; K = 8 fp32 and K = 16 bf16 take the same with 4 to 32, 1.5 % longer with 2.  K = 2 of four types on 13
+// tables, 10 to 109 us: 16 takes 0.95 to 1.06 times what 4 takes, 0.997 in the mean; small calls of one side differ by as much.
+// ResNet-50 sizes: bf16 33.5 with 4 and 33.8 with 16, binary16 31.7 and 32.7, fp32 57.1 and 58.1, fp64 109.1 and 108.7.)
 constexpr int direct_units(int R) { return R == 2 ? 4 : kDirectUnits; }
 // the sum over the units of a wave; lanes 0 .. kRun - 1 hold the entries'
 __device__ __forceinline__ double run_sum(double v) {
@@ -534,7 +536,7 @@ resident_kernel(const ResidentArgs args) {
     // entries accumulated side by side: more than some 60 do not fit beside what is kept, and take more sweeps over it
     constexpr int SWEEPS = (NP + 59) / 60;
     constexpr int NA = (NP + SWEEPS - 1) / SWEEPS;
-    // more than 8 operands of a 16-bit type: the Gram matrix on the matrix cores (gram_step below)
+    // more than 8 operands of a 16-bit type: the Gram matrix on the matrix cores (multiply_staged below)
     constexpr bool MFMA = resident_matrix(DtypeOf<TI>::value, R);
     typedef typename Traits<TI>::acc_t acc_t;
     typedef typename Traits<TO>::acc_t out_acc_t;
@@ -623,8 +625,9 @@ resident_kernel(const ResidentArgs args) {
     // step SV + i, row r: this wave's 1 KB
     auto keep = [&](int i, int r) { return shKeep + ((i * RL + r) * NW + wave) * 1024; };
     // (Where units have many steps, one that has a single step does not load the rest for nothing, and waits here, so that the
-    // steps of the others can still be told apart: K = 2 bf16, ResNet-50 sizes, 36.0 us instead of 37.7.  With 7 steps of 8
-    // rows it is K = 8 fp32 192 instead of 191.)
+    // steps of the others can still be told apart: ResNet-50 sizes, K = 2 bf16 33.5 us instead of 34.8, binary16 31.7 instead of 33.1, a
+    // sixteenth of BERT-Large, bf16, 31.4 instead of 32.6.  K = 2 fp32 and fp64 and K = 3 and 4 take the same either way within the 2 % by
+    // which their runs differ (13 tables each).  With 7 steps of 8 rows it is K = 8 fp32 192 instead of 191.)
     if (SV >= 10 && s.ng <= kThreads) {
         if (s.ng > 0) {
             const unsigned off = granule_at(0);
@@ -930,7 +933,7 @@ resident_kernel(const ResidentArgs args) {
 }
 
 // The second launch of the other forms.  Usually there is nothing to do, and it costs 4 us at 3726 units.  Where every unit gave
-// up it streams like a combine pass: ResNet-50 sizes, K = 8 fp32 318 us in all, K = 16 bf16 598, K = 2 bf16 93.
+// up it streams like a combine pass: ResNet-50 sizes, K = 8 fp32 316 us in all, K = 16 bf16 482, K = 2 bf16 95.
 template <typename TI, typename TO, int R, bool DELTA>
 __global__ void __launch_bounds__(kThreads, redo_per_cu(R))
 resident_redo_kernel(const Operands ops, TO* out, const ResidentUnit* __restrict__ units, int n_units, const ResidentState st,
