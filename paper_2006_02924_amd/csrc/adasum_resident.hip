@@ -141,7 +141,7 @@ __device__ __forceinline__ int partial_at(int u, int e, int W) {
 constexpr int kRunUnits = kThreads / kRun;
 // Units of a layer up to which every workgroup reads all partial sums itself.  (K = 2 bf16, ResNet-50 sizes: 37.4 us with 4,
 // 38.4 with 16, 40.7 with 170; K = 8 fp32 and K = 16 bf16 take the same with 4 to 32, 1.5 % longer with 2.  K = 2 of four types on 13
-// tables, 10 to 109 us: 16 takes 0.95 to 1.06 times what 4 takes, 0.997 in the mean; small calls of one side differ by as much.
+// tables, 10 to 109 us: 16 takes 0.95 to 1.06 times what 4 takes, 0.999 in the mean; small calls of one side differ by as much.
 // ResNet-50 sizes: bf16 33.5 with 4 and 33.8 with 16, binary16 31.7 and 32.7, fp32 57.1 and 58.1, fp64 109.1 and 108.7.)
 constexpr int direct_units(int R) { return R == 2 ? 4 : kDirectUnits; }
 // the sum over the units of a wave; lanes 0 .. kRun - 1 hold the entries'
@@ -626,8 +626,9 @@ resident_kernel(const ResidentArgs args) {
     auto keep = [&](int i, int r) { return shKeep + ((i * RL + r) * NW + wave) * 1024; };
     // (Where units have many steps, one that has a single step does not load the rest for nothing, and waits here, so that the
     // steps of the others can still be told apart: ResNet-50 sizes, K = 2 bf16 33.5 us instead of 34.8, binary16 31.7 instead of 33.1, a
-    // sixteenth of BERT-Large, bf16, 31.4 instead of 32.6.  K = 2 fp32 and fp64 and K = 3 and 4 take the same either way within the 2 % by
-    // which their runs differ (13 tables each).  With 7 steps of 8 rows it is K = 8 fp32 192 instead of 191.)
+    // sixteenth of BERT-Large, bf16, 31.4 instead of 32.6.  K = 2 fp32 and fp64 and K = 3 and 4 take the same either way:
+    // without it 0.99 to 1.01 times on tables of more than 30 us, 0.95 to 1.08 on smaller ones, whose runs differ by as much, 0.988
+    // (K = 2 fp32) to 1.004 in the mean of 13 tables.  With 7 steps of 8 rows it is K = 8 fp32 192 instead of 191.)
     if (SV >= 10 && s.ng <= kThreads) {
         if (s.ng > 0) {
             const unsigned off = granule_at(0);
